@@ -23,97 +23,102 @@ __device__ __forceinline__ T kernel_w(T q)
     return T(0);
 }
 
-// psi(Q) = int_0^Q q w(q) dq differences on one polynomial branch, factored so
-// that a small b - a keeps relative accuracy (Appendix D inner integral).
-__device__ __forceinline__ double psi_piece(int br, double a, double b, double bma)
-{
-    const double c = 8.0 / kPi;
-    if (br == 0) {
-        double a2 = a * a, b2 = b * b;
-        double s1 = a + b;
-        double s3 = (a2 + b2) * s1;
-        double s4 = b2 * b2 + b2 * b * a + b2 * a2 + b * a2 * a + a2 * a2;
-        return c * bma * (0.5 * s1 - 1.5 * s3 + 1.2 * s4);
-    }
-    if (br == 1) {
-        double pa = 1.0 - a, pb = 1.0 - b;
-        double pa2 = pa * pa, pb2 = pb * pb;
-        double t3 = (pa2 + pb2) * (pa + pb);
-        double t4 = pa2 * pa2 + pa2 * pa * pb + pa2 * pb2 + pa * pb2 * pb + pb2 * pb2;
-        return c * bma * (0.5 * t3 - 0.4 * t4);
-    }
-    return 0.0;
-}
-
-// psi(b) - psi(a) for 0 <= a <= b (bma = b - a, formed by the caller without
-// cancellation): the part of [a, b] on each polynomial branch ([0, 1/2],
-// (1/2, 1]; psi is flat past 1), each by its factored difference.  Both
-// branch terms are formed without data-dependent control flow, so the
-// quadrature nodes of one piece evaluate side by side.
-__device__ __forceinline__ double psi_range(double a, double b, double bma)
-{
-    const bool a0 = a <= 0.5, a1 = a <= 1.0, b0 = b <= 0.5, b1 = b <= 1.0;
-    // branch 0 holds [a, min(b, 1/2)] when a <= 1/2
-    const double hi0 = b0 ? b : 0.5;
-    const double p0 = psi_piece(0, a, hi0, b0 ? bma : 0.5 - a);
-    // branch 1 holds [max(a, 1/2), min(b, 1)] when a <= 1 and b > 1/2
-    const double lo1 = a0 ? 0.5 : a, hi1 = b1 ? b : 1.0;
-    const double p1 = psi_piece(1, lo1, hi1, (!a0 && b1) ? bma : hi1 - lo1);
-    return (a0 ? p0 : 0.0) + ((a1 && !b0) ? p1 : 0.0);
-}
-
 // Overlap H(delta, eta) = h_b^3 g for the cubic spline (Appendix D):
-//   H = (2 pi / eta^3) int_0^1 ds s^2 w(s) F(s),
-//   F(s) = eta^2/(delta s) [psi((s+delta)/eta) - psi(|s-delta|/eta)].
-// Between consecutive breakpoints (where s, |s - delta|/eta or (s + delta)/eta
-// crosses a branch edge of w or psi) the integrand s w(s) (eta^2/delta)
-// [psi(b) - psi(a)] is one polynomial of degree 9 in s (8 for delta = 0), so
-// 5-point Gauss-Legendre on each piece is exact up to rounding.
+//   H = (2 pi / eta^3) int_0^1 ds s w(s) V(s),
+//   V(s) = eta^2/delta [psi((s+delta)/eta) - psi(|s-delta|/eta)],  psi(Q) = int_0^Q q w(q) dq.
+// V vanishes outside [max(0, delta - eta), min(1, delta + eta)].  Between
+// consecutive breakpoints (where s, a = |s - delta|/eta or b = (s + delta)/eta
+// crosses a branch edge of w or psi) the integrand is one polynomial of degree
+// 9 in s, so 5-point Gauss-Legendre on each piece is exact up to rounding.
+//
+// Bound by binary64 vector instructions, so the work is what the pieces hold:
+// at most five breakpoints can lie inside the support (1/2, delta,
+// delta + eta/2, |delta - eta/2| and, for delta < eta, eta - delta), those
+// outside are moved to its end, so that the sorted list has its pieces in front
+// and the loop ends with the wave's longest list (2 to 6 pieces).  On a piece
+// every branch is fixed, so its polynomials are picked once: w(s) and the tail
+// T(q) = int_q^1 q w dq (all terms of one sign near q = 1) as Horner forms in
+// q or 1 - q.  Where b >= 1, psi(b) - psi(a) = T(a); otherwise, with
+// X = max(s, delta)/eta and y = min(s, delta)/eta, the difference on one branch
+// is 2y times a form in X (or 1 - X) and y, free of the cancellation at small
+// delta (and of the division by delta: eta^2/delta 2y = 2 eta min(1, s/delta)),
+// and across the edge at 1/2, a piece no wider than 2 min(s, delta), T(a) - T(b).
+// All 8/pi of w and T are in the caller's factor.
+// Against nine pieces (those outside the support too) of five nodes, both
+// branches of both ends formed at each: a binary64 step of 80 021 gas + 320 009
+// DM 6.46 -> 3.12 ms, of the 4096 + 4096 box 1.64 -> 1.14 ms; the mean error
+// against 113-bit arithmetic is 5-30 % smaller.
+__device__ __forceinline__ double overlap_integral(double delta, double eta, double ie, double c_ed)
+{
+    // 5-point Gauss-Legendre: nodes 0, +-gx[0], +-gx[1] with weights gw[0..2]
+    constexpr double gx[2] = {0.5384693101056830910, 0.9061798459386639928};
+    constexpr double gw[3] = {0.5688888888888888889, 0.4786286704993664680, 0.2369268850561890875};
+    const double lo0 = fmax(delta - eta, 0.0), hi = fmin(delta + eta, 1.0);
+    double b1 = 0.5, b2 = delta, b3 = delta + 0.5 * eta, b4 = fabs(delta - 0.5 * eta), b5 = eta - delta;
+    auto clamp = [lo0, hi](double& v) { v = v > lo0 && v < hi ? v : hi; };
+    clamp(b1); clamp(b2); clamp(b3); clamp(b4); clamp(b5);
+    auto order = [](double& x, double& y) { const double t = fmin(x, y); y = fmax(x, y); x = t; };
+    order(b1, b2); order(b4, b5); order(b3, b5); order(b3, b4); order(b2, b5);
+    order(b1, b4); order(b1, b3); order(b2, b4); order(b2, b3);
+    const double id = c_ed * ie * ie;            // 1/delta (0 when delta = 0)
+    double lo = lo0, nx = b1, acc = 0.0;
+#pragma unroll 1
+    while (lo < hi) {
+        const double half = 0.5 * (nx - lo), mid = 0.5 * (nx + lo);
+        // the piece's branches, taken at its midpoint
+        const double am = fabs(mid - delta), bm = mid + delta;
+        const bool s1 = mid > 0.5, a1 = am > 0.5 * eta, inner = bm < eta, b1r = bm > 0.5 * eta, right = mid > delta;
+        // w(s)/(8/pi) = e3 t^3 + e2 t^2 + e0, t = 1 - s on the outer branch, else s
+        const double e3 = s1 ? 2.0 : 6.0, e2 = s1 ? 0.0 : -6.0, e0 = s1 ? 0.0 : 1.0;
+        // T(q)/(8/pi) = f0 + t^2 (f2 + t^2 (f4 + f5 t)), t = 1 - q on the outer branch, else q
+        const double f0 = a1 ? 0.0 : 0.0875, f2 = a1 ? 0.0 : -0.5, f4 = a1 ? 0.5 : 1.5, f5 = a1 ? -0.4 : -1.2;
+        // t of T(a), linear in s: (eta - |s - delta|)/eta on the outer branch, else |s - delta|/eta; like 1 - s
+        // below it is carried from its value at the midpoint, so that a narrow piece near contact, where both
+        // vanish, keeps its relative accuracy
+        const double tm = (a1 ? (right ? (delta + eta) - mid : mid - (delta - eta)) : am) * ie;
+        const double th = right != a1 ? half * ie : -half * ie;
+        const double um = s1 ? 1.0 - mid : mid, uh = s1 ? -half : half;
+        double sq[5], V[5];
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            const double xq = q == 0 ? 0.0 : (q == 1 ? -gx[0] : (q == 2 ? gx[0] : (q == 3 ? -gx[1] : gx[1])));
+            sq[q] = q == 0 ? mid : fma(half, xq, mid);
+            const double t = q == 0 ? tm : fma(th, xq, tm), t2 = t * t;
+            V[q] = c_ed * fma(t2, fma(t2, fma(f5, t, f4), f2), f0);
+        }
+        if (inner) {
+            const double p1 = a1 ? 0.0 : 1.0, p3 = a1 ? 2.0 : -6.0, p5 = a1 ? -0.4 : 1.2;
+            const bool same = a1 == b1r;
+#pragma unroll
+            for (int q = 0; q < 5; ++q) {
+                const double X = fmax(sq[q], delta) * ie, y = fmin(sq[q], delta) * ie, y2 = y * y;
+                const double Z = a1 ? 1.0 - X : X, Z2 = Z * Z;
+                const double br = fma(p5, fma(5.0 * Z2, fma(2.0, y2, Z2), y2 * y2), Z * fma(p3, Z2 + y2, p1));
+                const double p = 1.0 - (X + y), pp = p * p;
+                V[q] = same ? 2.0 * eta * (right ? 1.0 : sq[q] * id) * br : V[q] - c_ed * (pp * pp * fma(-0.4, p, 0.5));
+            }
+        }
+        double piece = 0.0;
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            const double wq = q == 0 ? gw[0] : (q < 3 ? gw[1] : gw[2]);
+            const double xq = q == 0 ? 0.0 : (q == 1 ? -gx[0] : (q == 2 ? gx[0] : (q == 3 ? -gx[1] : gx[1])));
+            const double u = q == 0 ? um : fma(uh, xq, um);
+            piece = fma(wq * sq[q] * fma(u * u, fma(e3, u, e2), e0), V[q], piece);
+        }
+        acc = fma(half, piece, acc);
+        lo = nx; nx = b2; b2 = b3; b3 = b4; b4 = b5; b5 = hi;
+    }
+    return acc;
+}
+
+constexpr double kOverlapScale = 128.0 / kPi;    // 2 pi (8/pi)^2
+
 __device__ double overlap_H_exact(double delta, double eta)
 {
     if (delta >= 1.0 + eta) return 0.0;
-    // 5-point Gauss-Legendre: nodes 0, +-gx[1], +-gx[2] with weights gw[0..2]
-    const double gx[3] = {0.0, 0.5384693101056830910, 0.9061798459386639928};
-    const double gw[3] = {0.5688888888888888889, 0.4786286704993664680, 0.2369268850561890875};
-    // breakpoints of the integrand inside (0, 1), clamped to [0, 1] (those outside give
-    // empty pieces), sorted by Batcher's odd-even merge network in registers
-    double bp[10] = {0.0, 0.5, delta, delta - 0.5 * eta, delta + 0.5 * eta, delta - eta, delta + eta,
-                     0.5 * eta - delta, eta - delta, 1.0};
-#pragma unroll
-    for (int k = 1; k < 9; ++k) bp[k] = fmin(fmax(bp[k], 0.0), 1.0);
-    constexpr int kNet[19][2] = {{1, 2}, {3, 4}, {5, 6}, {7, 8}, {1, 3}, {2, 4}, {5, 7}, {6, 8}, {2, 3}, {6, 7},
-                                 {1, 5}, {2, 6}, {3, 7}, {4, 8}, {3, 5}, {4, 6}, {2, 3}, {4, 5}, {6, 7}};
-#pragma unroll
-    for (int k = 0; k < 19; ++k) {
-        const double x = bp[kNet[k][0]], y = bp[kNet[k][1]];
-        bp[kNet[k][0]] = fmin(x, y);
-        bp[kNet[k][1]] = fmax(x, y);
-    }
-    // s^2 w(s) F(s) = s w(s) (eta^2/delta) [psi(b) - psi(a)]: one factor s cancels, and the
-    // two quotients are formed once per pair, so the nodes take no division
-    const double ie = 1.0 / eta, c_ed = delta > 0.0 ? eta * eta / delta : 0.0;
-    double acc = 0.0;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-        const double lo = bp[k], hi = bp[k + 1];
-        if (!(hi > lo)) continue;
-        double half = 0.5 * (hi - lo), mid = 0.5 * (hi + lo), piece = 0.0;
-#pragma unroll
-        for (int q = 0; q < 5; ++q) {
-            const double s = mid + half * (q < 2 ? -gx[2 - q] : gx[q - 2]);
-            const double wq = q < 2 ? gw[2 - q] : gw[q - 2];
-            double sF;
-            if (delta == 0.0) {
-                sF = 2.0 * s * kernel_w(s * ie);
-            } else {
-                const double a = fabs(s - delta) * ie, b = (s + delta) * ie, bma = 2.0 * fmin(s, delta) * ie;
-                sF = c_ed * psi_range(a, b, bma);
-            }
-            piece += wq * s * kernel_w(s) * sF;
-        }
-        acc += half * piece;
-    }
-    return 2.0 * kPi * acc / (eta * eta * eta);
+    const double ie = 1.0 / eta;
+    return kOverlapScale * overlap_integral(delta, eta, ie, delta > 0.0 ? eta * eta / delta : 0.0) * (ie * ie * ie);
 }
 
 // ---------------------------------------------------------------------------
@@ -230,11 +235,16 @@ __device__ __forceinline__ double overlap_g_gas(const float4* __restrict__ tab, 
     return g >= 1e-30f ? double(g) : overlap_g_table(tab, d2, h1, h2);
 }
 
+// g in binary64: delta and eta by division (near contact g goes as the eighth
+// power of 1 + eta - delta), the integral's other factors from 1/h_s and 1/d.
 template <typename T>
 __device__ __forceinline__ T overlap_g_exact(T d, T hi, T hj)
 {
-    double hb = double(hi > hj ? hi : hj), hs = double(hi > hj ? hj : hi);
-    return T(overlap_H_exact(double(d) / hb, hs / hb) / (hb * hb * hb));
+    const double hb = double(hi > hj ? hi : hj), hs = double(hi > hj ? hj : hi), dd = double(d);
+    const double delta = dd / hb, eta = hs / hb, is = 1.0 / hs;
+    if (delta >= 1.0 + eta) return T(0);
+    const double c_ed = dd > 0.0 ? eta * hs / dd : 0.0;
+    return T(kOverlapScale * overlap_integral(delta, eta, hb * is, c_ed) * (is * is * is));
 }
 
 // ---------------------------------------------------------------------------
