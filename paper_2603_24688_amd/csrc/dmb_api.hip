@@ -30,6 +30,7 @@ struct DevBuf {
 struct Species {
     int64_t n = 0, n_own = 0, ntile = 0, nsuper = 0, nmega = 0, nown_tile = 0, nchunk = 0;
     int sort_lo_bit = 0;
+    bool all_own = false;                  // every particle active: the owner list is the identity
     DevBuf sub_ccnt, sub_coff, sub_start, sub_cnt;   // sub-tiles (other role): per-chunk counts/offsets, ranges
     DevBuf keys, keys2, vals, vals2;       // sort
     DevBuf sx, sy, sz, sh;                 // sorted position, h
@@ -53,7 +54,7 @@ struct Pairs {                             // candidate lists: owner tiles of A 
     // groups of 64 owner tiles: bounds (box, h, support, nodes), candidate counts and lists, a spare max
     DevBuf gbox, gh, gsup, gq, gcnt, glist, gmax;
     // candidate sub-tiles: per-tile counts and starts, the lists, work items
-    DevBuf scnt, beg, swt, cand, icnt, ioff, it_tile, it_cb, it_ce;
+    DevBuf scnt, beg, swt, cand, icnt, ioff, it_tile, it_cb, it_ce, it_slice, slices;
     DevBuf it_key, it_key2, it_id, it_ord;  // item order (largest first): sort keys, item ids, order
     int pad_cap = 128;                     // grown from the largest count seen
     int64_t npairs = 0, total = 0, nitems = 0;
@@ -67,7 +68,6 @@ struct Scratch {
     DevBuf bbox_part;
     DevBuf counters_local;
     DevBuf pair_cnt;                       // pair export counts [gas pass, DM pass]
-    DevBuf rb_dev;                         // build-stage scalars for the host (one copy per stage)
 };
 
 // Cell structure and per-step buffers of one box (one periodic volume or
@@ -76,7 +76,6 @@ struct Scratch {
 struct Cells {
     Species gas, dm;
     Pairs gp, dp;                          // gas owners x DM tiles; DM owners x gas tiles
-    DevBuf boxL;                           // periodic side lengths (device, 4 doubles)
     DevBuf part_gas, part_p, part_pm, part_nb, psum_own;
     DevBuf qctr, slist;
     int64_t built_ngas = -1, built_ndm = -1;
@@ -122,7 +121,9 @@ struct dmb_ctx {
     int split = 32;                        // candidate sub-tiles per work item of the DM pass (tunable);
                                            // the gas pass, whose partial sums cost more to combine, twice that
     int item_target_per_cu = 32;           // small problems: split candidate lists into about this many
-                                           // work items per compute unit (0: always `split`)
+                                           // work items per compute unit, four times as many by the finer
+                                           // cuts of either pass (ItemCut; 0: always `split`)
+    bool fp64_sums = false;                // the build under way is for binary64 steps
     int item_share = 1;                    // boxes that share the chip in the build under way (batch)
     int subtile_delta = 1;                 // (tunable) sub-tile cut: Morton level below (median - delta)
     int group_cap = 1024;                  // candidate-search group list capacity (0: no group pass)
@@ -236,47 +237,50 @@ inline unsigned blocks_for(int64_t n, int bs) { return unsigned((n + bs - 1) / b
 
 // Exclusive scan of n values (TI in, TO out and partial sums) into out (out
 // may equal in when the types agree); inputs from n_in on (n_in <= n) read
-// as 0, so out[n_in] receives the total without touching in[n_in].
+// as 0, so out[n_in] receives the total without touching in[n_in].  A second
+// pair (in2, out2) of the same length is scanned by the same launches.
 template <typename TI = uint32_t, typename TO = uint32_t>
-dmb_status scan_excl(dmb_ctx* c, const TI* in, TO* out, int64_t n, int64_t n_in = -1, int level = 0)
+dmb_status scan_excl(dmb_ctx* c, const TI* in, TO* out, int64_t n, int64_t n_in = -1, const TI* in2 = nullptr,
+                     TO* out2 = nullptr, int level = 0)
 {
     if (n <= 0) return DMB_OK;
     if (n_in < 0 || n_in > n) n_in = n;
     int64_t nb = (n + kScanTile - 1) / kScanTile;
     if (level >= 4) return fail(c, DMB_EINVAL, "scan too large");
-    ENSURE(c, c->S->scan_tmp[level], size_t(nb + 1) * sizeof(TO));
+    ENSURE(c, c->S->scan_tmp[level], size_t(nb + 1) * sizeof(TO) * (in2 ? 2 : 1));
     TO* sums = c->S->scan_tmp[level].as<TO>();
-    hipLaunchKernelGGL((k_scan_block<TI, TO>), dim3(unsigned(nb)), dim3(kScanBlock), 0, c->stream, in, out, sums, n,
-                       n_in);
+    TO* sums2 = sums + nb + 1;
+    const dim3 grid(unsigned(nb), in2 ? 2u : 1u);
+    hipLaunchKernelGGL((k_scan_block<TI, TO>), grid, dim3(kScanBlock), 0, c->stream, in, out, sums, n, n_in, in2, out2,
+                       sums2);
     if (nb > 1 && nb <= kScanOwnMax) {
-        hipLaunchKernelGGL(k_scan_add_own<TO>, dim3(unsigned(nb)), dim3(kScanBlock), 0, c->stream, out,
-                           (const TO*)sums, n);
+        hipLaunchKernelGGL(k_scan_add_own<TO>, grid, dim3(kScanBlock), 0, c->stream, out, (const TO*)sums, n, out2,
+                           (const TO*)sums2);
     } else if (nb > 1) {
-        dmb_status s = scan_excl<TO, TO>(c, sums, sums, nb, nb, level + 1);
+        dmb_status s = scan_excl<TO, TO>(c, sums, sums, nb, nb, in2 ? sums2 : nullptr, sums2, level + 1);
         if (s != DMB_OK) return s;
-        hipLaunchKernelGGL(k_scan_add<TO>, dim3(unsigned(nb)), dim3(kScanBlock), 0, c->stream, out, sums, n);
+        hipLaunchKernelGGL(k_scan_add<TO>, grid, dim3(kScanBlock), 0, c->stream, out, sums, n, out2, sums2);
     }
     HIPCHK(c, hipGetLastError());
     return DMB_OK;
 }
 
-// Stable LSD radix sort of n (key, value) pairs by the key bits
-// [lo_bit, lo_bit + 8 passes), ping-ponging between (ka, va) and (kb, vb);
-// on return *ka, *va point at the sorted arrays.  A raised look-back error
-// is reported by the next build's first read-back.
 __global__ __launch_bounds__(256) void k_os_clear(uint32_t* __restrict__ w, int n)
 {
     for (int i = int(threadIdx.x); i < n; i += 256) w[i] = 0u;
 }
 
+// Stable LSD radix sort of n (key, value) pairs by the key bits
+// [lo_bit, lo_bit + 8 passes), ping-ponging between (ka, va) and (kb, vb);
+// on return *ka, *va point at the sorted arrays.  The caller's previous kernel has
+// cleared the kOsWords words of os_hist.  A raised look-back error is reported by the
+// next build's first read-back.
 dmb_status radix_sort(dmb_ctx* c, uint64_t** ka, uint32_t** va, uint64_t** kb, uint32_t** vb, int64_t n, int lo_bit,
                       int passes)
 {
     if (n <= 0 || passes <= 0) return DMB_OK;
     if (passes > kOsMaxPasses) return fail(c, DMB_EINVAL, "radix sort: %d passes", passes);
     const int64_t ntile = (n + kOsTile - 1) / kOsTile;
-    const int nw = kOsMaxPasses * 256 + kOsMaxPasses;
-    ENSURE(c, c->S->os_hist, size_t(nw) * 4);
     ENSURE(c, c->S->os_status, size_t(passes) * size_t(ntile) * 256 * 8);
     OsArgs a;
     a.n = n; a.passes = passes; a.lo_bit = lo_bit;
@@ -285,7 +289,6 @@ dmb_status radix_sort(dmb_ctx* c, uint64_t** ka, uint32_t** va, uint64_t** kb, u
     a.status = c->S->os_status.as<unsigned long long>();
     a.err = c->os_err.as<uint32_t>();
     a.ntile = ntile;
-    hipLaunchKernelGGL(k_os_clear, dim3(1), dim3(256), 0, c->stream, a.hist, nw);
     const int hb = int(std::min<int64_t>(2048, std::max<int64_t>(ntile, (int64_t(passes) * ntile * 256 + 4095) / 4096)));
     hipLaunchKernelGGL(k_os_hist, dim3(hb), dim3(kOsHistBlock), 0, c->stream, *ka, a);
     for (int p = 0; p < passes; ++p) {
@@ -326,19 +329,25 @@ dmb_status build_species(dmb_ctx* c, Species& S, const dmb_particles* p)
     ENSURE(c, S.keys, n * 8); ENSURE(c, S.keys2, n * 8);
     ENSURE(c, S.vals, n * 4); ENSURE(c, S.vals2, n * 4);
     ENSURE(c, S.cube, 8 * sizeof(double));
-    // bounding box (k_bbox_final takes [0, L) when L_x > 0, so the partial pass is skipped
-    // then); enough blocks to fill the chip
-    const bool periodic = c->X->built_L[0] > 0.0;
-    const int nparts = periodic ? 0 : int(std::min<int64_t>(2048, (n + 1023) / 1024));
-    ENSURE(c, c->S->bbox_part, std::max(nparts, 1) * 6 * sizeof(double));
-    if (nparts > 0)
+    // bounding box: [0, L) of a periodic box; of an open region by reduction, with enough
+    // blocks to fill the chip
+    KeyBox box;
+    for (int k = 0; k < 3; ++k) box.L[k] = c->X->built_L[k];
+    const double zero[3] = {0.0, 0.0, 0.0};
+    key_cube(zero, box.L, box.cube);
+    const bool periodic = box.L[0] > 0.0;
+    if (!periodic) {
+        const int nparts = int(std::min<int64_t>(2048, (n + 1023) / 1024));
+        ENSURE(c, c->S->bbox_part, nparts * 6 * sizeof(double));
         hipLaunchKernelGGL(k_bbox_partial, dim3(nparts), dim3(256), 0, c->stream, p->pos, n, c->S->bbox_part.as<double>());
-    hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(64), 0, c->stream, c->S->bbox_part.as<const double>(), nparts,
-                       c->X->boxL.as<const double>(), S.cube.as<double>());
+        hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(64), 0, c->stream, c->S->bbox_part.as<const double>(), nparts,
+                           S.cube.as<double>());
+    }
     ENSURE(c, S.prec, n * sizeof(double4));
+    ENSURE(c, c->S->os_hist, size_t(kOsWords) * 4);
     hipLaunchKernelGGL(k_morton, dim3(blocks_for(n, 256)), dim3(256), 0, c->stream, p->pos, p->h, n,
-                       S.cube.as<const double>(), c->X->boxL.as<const double>(), S.keys.as<uint64_t>(),
-                       S.vals.as<uint32_t>(), S.prec.as<double4>());
+                       periodic ? nullptr : S.cube.as<const double>(), box, S.keys.as<uint64_t>(),
+                       S.vals.as<uint32_t>(), S.prec.as<double4>(), c->S->os_hist.as<uint32_t>(), kOsWords);
     // radix sort on the top bits that resolve ~2^6 particles per cell
     int need = std::min(63, std::max(24, 3 * ((bits_for(n) + 6 + 2) / 3)));
     int passes = (need + 7) / 8;
@@ -361,27 +370,35 @@ dmb_status build_species(dmb_ctx* c, Species& S, const dmb_particles* p)
     ENSURE(c, S.sx, n * 8); ENSURE(c, S.sy, n * 8); ENSURE(c, S.sz, n * 8); ENSURE(c, S.sh, n * 8);
     // owners (active subset, Morton order)
     ENSURE(c, S.flag, (n + 1) * 4); ENSURE(c, S.flag_off, (n + 1) * 4); ENSURE(c, S.own, n * 4);
-    hipLaunchKernelGGL(k_active_flags, dim3(blocks_for(n + 1, 256)), dim3(256), 0, c->stream, S.perm, n, p->active,
-                       S.flag.as<uint32_t>());
-    dmb_status s = scan_excl(c, S.flag.as<const uint32_t>(), S.flag_off.as<uint32_t>(), n + 1);
-    if (s != DMB_OK) return s;
-    hipLaunchKernelGGL(k_compact, dim3(blocks_for(n, 256)), dim3(256), 0, c->stream, S.flag.as<const uint32_t>(),
-                       S.flag_off.as<const uint32_t>(), n, S.own.as<uint32_t>());
+    dmb_status s;
+    S.all_own = p->active == nullptr;
+    if (!S.all_own) {
+        hipLaunchKernelGGL(k_active_flags, dim3(blocks_for(n + 1, 256)), dim3(256), 0, c->stream, S.perm, n, p->active,
+                           S.flag.as<uint32_t>());
+        s = scan_excl(c, S.flag.as<const uint32_t>(), S.flag_off.as<uint32_t>(), n + 1);
+        if (s != DMB_OK) return s;
+        hipLaunchKernelGGL(k_compact, dim3(blocks_for(n, 256)), dim3(256), 0, c->stream, S.flag.as<const uint32_t>(),
+                           S.flag_off.as<const uint32_t>(), n, S.own.as<uint32_t>());
+    }
     // sub-tile counts per 64-chunk (other role); totals are read back by the caller
     S.nchunk = (n + kTile - 1) / kTile;
     ENSURE(c, S.sub_ccnt, (S.nchunk + 1) * 4); ENSURE(c, S.sub_coff, (S.nchunk + 1) * 4);
     hipLaunchKernelGGL(k_subtile_count, dim3(unsigned(S.nchunk)), dim3(64), 0, c->stream,
-                       S.keys.as<const uint64_t>(), n, S.sort_lo_bit, c->subtile_delta, S.sub_ccnt.as<uint32_t>());
+                       S.keys.as<const uint64_t>(), n, S.sort_lo_bit, c->subtile_delta, S.sub_ccnt.as<uint32_t>(),
+                       S.all_own ? S.own.as<uint32_t>() : nullptr, S.flag.as<uint32_t>(), S.flag_off.as<uint32_t>());
     s = scan_excl(c, S.sub_ccnt.as<const uint32_t>(), S.sub_coff.as<uint32_t>(), S.nchunk + 1, S.nchunk);
     if (s != DMB_OK) return s;
     HIPCHK(c, hipGetLastError());
     return DMB_OK;
 }
 
-// Sub-tile ranges and bounds, super-tiles (needs the sub-tile count).
-dmb_status build_subtiles(dmb_ctx* c, Species& S)
+// Sub-tile ranges and bounds, super- and mega-tiles (needs the sub-tile count), and the
+// bounds of the owner tiles; clears the word *maxcnt.
+dmb_status build_subtiles(dmb_ctx* c, Species& S, uint32_t* maxcnt)
 {
+    S.nown_tile = (S.n_own + kTile - 1) / kTile;
     if (S.n == 0) return DMB_OK;
+    ENSURE(c, S.obox, S.nown_tile * 48); ENSURE(c, S.oh, S.nown_tile * 8);
     ENSURE(c, S.sub_start, S.ntile * 4); ENSURE(c, S.sub_cnt, S.ntile * 4);
     S.nsuper = (S.ntile + kTile - 1) / kTile;
     ENSURE(c, S.tbox, S.ntile * 48); ENSURE(c, S.th, S.ntile * 8); ENSURE(c, S.tsup, S.ntile * 48);
@@ -392,32 +409,28 @@ dmb_status build_subtiles(dmb_ctx* c, Species& S)
                        S.sub_coff.as<const uint32_t>(), S.sub_start.as<uint32_t>(), S.sub_cnt.as<uint32_t>(),
                        S.perm, S.prec.as<const double4>(), S.sx.as<double>(), S.sy.as<double>(),
                        S.sz.as<double>(), S.sh.as<double>(), S.tbox.as<double>(), S.th.as<double>(),
-                       S.tsup.as<double>(), S.tq.as<float4>());
-    hipLaunchKernelGGL(k_super_bounds, dim3(unsigned(S.nsuper)), dim3(64), 0, c->stream, S.ntile,
-                       S.tbox.as<const double>(), S.th.as<const double>(), S.tsup.as<const double>(),
-                       S.sbox.as<double>(), S.shh.as<double>(), S.ssup.as<double>(), S.sq.as<float4>());
+                       S.tsup.as<double>(), S.tq.as<float4>(), S.all_own ? S.obox.as<double>() : nullptr,
+                       S.oh.as<double>());
     S.nmega = (S.nsuper + kTile - 1) / kTile;
     ENSURE(c, S.mbox, S.nmega * 48); ENSURE(c, S.mhh, S.nmega * 8); ENSURE(c, S.msup, S.nmega * 48);
     ENSURE(c, S.mq, S.nmega * 64);
+    hipLaunchKernelGGL(k_super_bounds, dim3(unsigned(S.nsuper)), dim3(64), 0, c->stream, S.ntile,
+                       S.tbox.as<const double>(), S.th.as<const double>(), S.tsup.as<const double>(),
+                       S.sbox.as<double>(), S.shh.as<double>(), S.ssup.as<double>(), S.sq.as<float4>(), maxcnt);
     hipLaunchKernelGGL(k_super_bounds, dim3(unsigned(S.nmega)), dim3(64), 0, c->stream, S.nsuper,
                        S.sbox.as<const double>(), S.shh.as<const double>(), S.ssup.as<const double>(),
-                       S.mbox.as<double>(), S.mhh.as<double>(), S.msup.as<double>(), S.mq.as<float4>());
+                       S.mbox.as<double>(), S.mhh.as<double>(), S.msup.as<double>(), S.mq.as<float4>(), maxcnt);
+    if (!S.all_own && S.nown_tile > 0)
+        hipLaunchKernelGGL(k_tile_bounds, dim3(unsigned(S.nown_tile)), dim3(64), 0, c->stream,
+                           S.own.as<const uint32_t>(), S.n_own, S.sx.as<const double>(), S.sy.as<const double>(),
+                           S.sz.as<const double>(), S.sh.as<const double>(), S.obox.as<double>(), S.oh.as<double>());
     HIPCHK(c, hipGetLastError());
     return DMB_OK;
 }
 
-// Owner tiles need n_own, known after a read-back.
-dmb_status build_owner_tiles(dmb_ctx* c, Species& S)
-{
-    S.nown_tile = (S.n_own + kTile - 1) / kTile;
-    if (S.nown_tile == 0) return DMB_OK;
-    ENSURE(c, S.obox, S.nown_tile * 48); ENSURE(c, S.oh, S.nown_tile * 8);
-    hipLaunchKernelGGL(k_tile_bounds, dim3(unsigned(S.nown_tile)), dim3(64), 0, c->stream, S.own.as<const uint32_t>(),
-                       S.n_own, S.sx.as<const double>(), S.sy.as<const double>(), S.sz.as<const double>(),
-                       S.sh.as<const double>(), S.obox.as<double>(), S.oh.as<double>());
-    HIPCHK(c, hipGetLastError());
-    return DMB_OK;
-}
+// Lists per group of owner tiles spare each tile the walk over the mega-tiles; with one mega-tile
+// (up to 4096 sub-tiles) that walk is one round of 64 node tests, as reading a list would be.
+bool use_groups(const dmb_ctx* c, const Species& B) { return c->group_cap > 0 && B.nmega > 1; }
 
 CandArgs cand_args(dmb_ctx* c, Species& A, Species& B, Pairs& P)
 {
@@ -430,8 +443,8 @@ CandArgs cand_args(dmb_ctx* c, Species& A, Species& B, Pairs& P)
     a.pad = P.pad.as<uint32_t>(); a.pad_cap = P.pad_cap; a.maxcnt = P.maxcnt.as<uint32_t>();
     a.cand = P.psup.as<uint32_t>(); a.ptile = P.ptile.as<uint32_t>();
     a.gcap = c->group_cap;
-    a.gcnt = c->group_cap > 0 ? P.gcnt.as<const uint32_t>() : nullptr;
-    a.glist = c->group_cap > 0 ? P.glist.as<const uint32_t>() : nullptr;
+    a.gcnt = use_groups(c, B) ? P.gcnt.as<const uint32_t>() : nullptr;
+    a.glist = use_groups(c, B) ? P.glist.as<const uint32_t>() : nullptr;
     return a;
 }
 
@@ -450,16 +463,15 @@ dmb_status cand_count(dmb_ctx* c, Species& A, Species& B, Pairs& P)
     constexpr int64_t kPadBytes = int64_t(3) << 30;
     P.pad_cap = int(std::max<int64_t>(0, std::min<int64_t>(P.pad_cap, kPadBytes / (4 * nt))));
     ENSURE(c, P.pad, std::max<int64_t>(1, nt * P.pad_cap) * 4);
-    ENSURE(c, P.maxcnt, 4);
-    HIPCHK(c, hipMemsetAsync(P.maxcnt.p, 0, 4, c->stream));
     // group lists: a count pass over groups of 64 owner tiles, their lists kept in glist
-    if (c->group_cap > 0) {
+    if (use_groups(c, B)) {
         const int64_t ng = (nt + kTile - 1) / kTile;
         ENSURE(c, P.gbox, ng * 48); ENSURE(c, P.gh, ng * 8); ENSURE(c, P.gsup, ng * 48); ENSURE(c, P.gq, ng * 64);
         ENSURE(c, P.gcnt, ng * 4); ENSURE(c, P.glist, ng * c->group_cap * 4); ENSURE(c, P.gmax, 4);
         hipLaunchKernelGGL(k_super_bounds, dim3(unsigned(ng)), dim3(64), 0, c->stream, nt,
                            A.obox.as<const double>(), A.oh.as<const double>(), A.obox.as<const double>(),
-                           P.gbox.as<double>(), P.gh.as<double>(), P.gsup.as<double>(), P.gq.as<float4>());
+                           P.gbox.as<double>(), P.gh.as<double>(), P.gsup.as<double>(), P.gq.as<float4>(),
+                           P.gmax.as<uint32_t>());
         CandArgs ga = cand_args(c, A, B, P);
         ga.nown_tile = ng; ga.obox = P.gbox.as<const double>(); ga.oh = P.gh.as<const double>();
         ga.cnt = P.gcnt.as<uint32_t>(); ga.pad = P.glist.as<uint32_t>(); ga.pad_cap = c->group_cap;
@@ -503,19 +515,19 @@ dmb_status cand_subs(dmb_ctx* c, Species& A, Species& B, Pairs& P)
     m.mask = P.mask.as<uint64_t>(); m.pcnt = P.pcnt.as<uint32_t>(); m.pw = P.pw.as<uint32_t>();
     hipLaunchKernelGGL(k_sub_masks, dim3(unsigned((np + kSubPairs - 1) / kSubPairs)), dim3(64), 0, c->stream, m);
     // candidate offsets in 64 bits (totals pass 2^32 at Milky-Way sizes)
-    dmb_status s =
-        scan_excl<uint32_t, uint64_t>(c, P.pcnt.as<const uint32_t>(), P.soff.as<uint64_t>(), np + 1, np);
+    dmb_status s = scan_excl<uint32_t, uint64_t>(c, P.pcnt.as<const uint32_t>(), P.soff.as<uint64_t>(), np + 1, np,
+                                                 P.pw.as<const uint32_t>(), P.woff.as<uint64_t>());
     if (s != DMB_OK) return s;
-    s = scan_excl<uint32_t, uint64_t>(c, P.pw.as<const uint32_t>(), P.woff.as<uint64_t>(), np + 1, np);
-    if (s != DMB_OK) return s;
-    hipLaunchKernelGGL(k_tile_subs, dim3(blocks_for(nt + 1, 256)), dim3(256), 0, c->stream, nt,
+    const uint32_t target = uint32_t(int64_t(c->item_target_per_cu) * c->num_cu / std::max(1, c->item_share));
+    const bool gas_pass = &P == &c->X->gp;
+    const uint32_t split = uint32_t(gas_pass ? 2 * c->split : c->split);
+    const ItemCut cut = gas_pass || c->fp64_sums ? ItemCut{split, 1u, 4u * target, 0u}
+                                                 : ItemCut{split, 4u, target, 4u * target};
+    ENSURE(c, P.slices, 4);
+    hipLaunchKernelGGL(k_tile_items, dim3(blocks_for(nt + 1, 256)), dim3(256), 0, c->stream, nt,
                        P.off.as<const uint64_t>(), P.soff.as<const uint64_t>(), P.woff.as<const uint64_t>(),
-                       P.scnt.as<uint32_t>(), P.beg.as<uint64_t>(), P.swt.as<uint32_t>());
-    hipLaunchKernelGGL(k_item_count, dim3(blocks_for(nt + 1, 256)), dim3(256), 0, c->stream,
-                       P.scnt.as<const uint32_t>(), nt, uint32_t(&P == &c->X->gp ? 2 * c->split : c->split),
-                       P.soff.as<const uint64_t>() + np,
-                       uint32_t(int64_t(c->item_target_per_cu) * c->num_cu / std::max(1, c->item_share)),
-                       P.icnt.as<uint32_t>());
+                       P.scnt.as<uint32_t>(), P.beg.as<uint64_t>(), P.swt.as<uint32_t>(),
+                       cut, P.icnt.as<uint32_t>(), P.slices.as<uint32_t>());
     s = scan_excl(c, P.icnt.as<const uint32_t>(), P.ioff.as<uint32_t>(), nt + 1);
     if (s != DMB_OK) return s;
     HIPCHK(c, hipGetLastError());
@@ -528,6 +540,7 @@ dmb_status cand_write(dmb_ctx* c, Species& A, Species& B, Pairs& P)
     int64_t nt = A.nown_tile;
     ENSURE(c, P.cand, std::max<int64_t>(P.total, 1) * 4);
     ENSURE(c, P.it_tile, std::max<int64_t>(P.nitems, 1) * 4);
+    ENSURE(c, P.it_slice, std::max<int64_t>(P.nitems, 1) * 4);
     ENSURE(c, P.it_cb, std::max<int64_t>(P.nitems, 1) * 8);
     ENSURE(c, P.it_ce, std::max<int64_t>(P.nitems, 1) * 8);
     if (nt == 0 || B.ntile == 0 || P.total == 0) return DMB_OK;
@@ -536,11 +549,13 @@ dmb_status cand_write(dmb_ctx* c, Species& A, Species& B, Pairs& P)
                        P.cand.as<uint32_t>());
     const int64_t ni = P.nitems;
     ENSURE(c, P.it_key, std::max<int64_t>(ni, 1) * 8); ENSURE(c, P.it_key2, std::max<int64_t>(ni, 1) * 8);
+    ENSURE(c, c->S->os_hist, size_t(kOsWords) * 4);
     ENSURE(c, P.it_id, std::max<int64_t>(ni, 1) * 4); ENSURE(c, P.it_ord, std::max<int64_t>(ni, 1) * 4);
     hipLaunchKernelGGL(k_item_write, dim3(blocks_for(ni, 256)), dim3(256), 0, c->stream, P.beg.as<const uint64_t>(),
                        P.scnt.as<const uint32_t>(), P.swt.as<const uint32_t>(), P.ioff.as<const uint32_t>(), nt, ni,
+                       P.slices.as<const uint32_t>(), P.it_slice.as<uint32_t>(),
                        P.it_tile.as<uint32_t>(), P.it_cb.as<uint64_t>(), P.it_ce.as<uint64_t>(),
-                       P.it_key.as<uint64_t>(), P.it_id.as<uint32_t>());
+                       P.it_key.as<uint64_t>(), P.it_id.as<uint32_t>(), c->S->os_hist.as<uint32_t>(), kOsWords);
     uint64_t *ka = P.it_key.as<uint64_t>(), *kb = P.it_key2.as<uint64_t>();
     uint32_t *va = P.it_id.as<uint32_t>(), *vb = P.it_ord.as<uint32_t>();
     dmb_status s = radix_sort(c, &ka, &va, &kb, &vb, ni, 0, 1);   // one pass: the order lands in it_ord
@@ -616,7 +631,7 @@ PassGeom geom(Cells& X, Species& A, Species& B, Pairs& P, uint64_t* counters)
     g.item_off = P.ioff.as<const uint32_t>();
     g.item_order = P.it_ord.as<const uint32_t>();
     g.it_tile = P.it_tile.as<const uint32_t>(); g.it_cb = P.it_cb.as<const uint64_t>();
-    g.it_ce = P.it_ce.as<const uint64_t>(); g.n_items = P.nitems;
+    g.it_ce = P.it_ce.as<const uint64_t>(); g.it_slice = P.it_slice.as<const uint32_t>(); g.n_items = P.nitems;
     g.queue_ctr = X.qctr.as<uint32_t>();
     for (int k = 0; k < 3; ++k) g.L[k] = X.built_L[k];
     g.counters = counters;
@@ -687,8 +702,8 @@ dmb_status both(dmb_ctx* c, FA&& a, FB&& b)
 }
 
 // Per-step gathers into Morton order and the clearing of outputs, counters
-// and the box's queue counters (qctr: [0, 8) gas queue, [8, 16) DM queue,
-// [16] scatter count).  Buffers are sized first; with `overlap` the gas
+// and the box's queue counters (qctr: eight of the gas queue, eight of the DM
+// queue and the scatter count, kQueueStride words apart).  Buffers are sized first; with `overlap` the gas
 // gather runs on the side stream beside the DM gather (both are bound by
 // the latency of their indexed reads).
 template <typename Real, int RM>
@@ -704,7 +719,7 @@ dmb_status gather_and_fill(dmb_ctx* c, Cells& X, const dmb_particles* gas, const
         ENSURE(c, G.rec, G.n * (sizeof(Real) == 4 ? sizeof(GasRec<float>) : sizeof(GasRec<double>)));
     }
     if (D.n > 0) ENSURE(c, D.rec, D.n * (sizeof(Real) == 4 ? sizeof(DmRec<float>) : sizeof(DmRec<double>)));
-    ENSURE(c, X.qctr, (2 * kXcd + 4) * 4);
+    ENSURE(c, X.qctr, kQueueWords * 4);
     if (X.gp.nitems > 0) ENSURE(c, X.part_gas, size_t(X.gp.nitems) * kTile * gas_sums<RM>() * 8);
     if (X.dp.nitems > 0) {
         ENSURE(c, X.part_p, size_t(X.dp.nitems) * kTile * 8);
@@ -742,10 +757,10 @@ dmb_status gather_and_fill(dmb_ctx* c, Cells& X, const dmb_particles* gas, const
         da.rec = D.rec.p;
         hipLaunchKernelGGL(k_gather_dm<Real>, dim3(blocks_for(D.n, 256)), dim3(256), 0, c->stream, da);
     }
-    int64_t nfill = std::max<int64_t>(std::max<int64_t>(G.n, D.n), 2 * kXcd + 4);
+    int64_t nfill = std::max<int64_t>(std::max<int64_t>(G.n, D.n), kQueueWords);
     hipLaunchKernelGGL(k_fill_out, dim3(blocks_for(nfill, 256)), dim3(256), 0, c->stream, G.n, D.n, out->dp_gas,
                        out->de_gas, out->dv_dm, out->partner, out->p_sum, out->p_max, counters,
-                       X.qctr.as<uint32_t>(), 2 * kXcd + 4);
+                       X.qctr.as<uint32_t>(), kQueueWords);
     if (side) {
         dmb_status s = join(c);
         if (s != DMB_OK) return s;
@@ -813,7 +828,7 @@ DmPassArgs dm_pass_args(dmb_ctx* c, Cells& X, const dmb_params* par, dmb_out* ou
     Species& D = X.dm;
     DmPassArgs a;
     a.g = geom(X, D, G, X.dp, counters);
-    a.g.queue_ctr = X.qctr.as<uint32_t>() + kXcd;
+    a.g.queue_ctr = X.qctr.as<uint32_t>() + kXcd * kQueueStride;
     a.drec = D.rec.p; a.dm_perm = D.perm;
     a.Vx = G.v0.as<const double>(); a.Vy = G.v1.as<const double>(); a.Vz = G.v2.as<const double>();
     a.grec = G.rec.p;
@@ -822,7 +837,7 @@ DmPassArgs dm_pass_args(dmb_ctx* c, Cells& X, const dmb_params* par, dmb_out* ou
     a.step_off = step_off;
     a.part_p = X.part_p.as<double>(); a.part_pm = X.part_pm.as<float>(); a.part_nb = X.part_nb.as<uint8_t>();
     a.psum_own = X.psum_own.as<double>(); a.psum = out->p_sum; a.pmax = out->p_max;
-    a.scount = X.qctr.as<uint32_t>() + 2 * kXcd; a.slist = X.slist.as<uint32_t>();
+    a.scount = X.qctr.as<uint32_t>() + 2 * kXcd * kQueueStride; a.slist = X.slist.as<uint32_t>();
     return a;
 }
 
@@ -972,9 +987,9 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
     P.ga.resize(nbox);
     P.da.resize(nbox);
     std::vector<int64_t> gi(nbox + 1, 0), di(nbox + 1, 0);
-    // global queues [0, 16) and the Philox step offset [16]
-    ENSURE(c, c->bstep, 32 * sizeof(uint32_t));
-    const uint32_t* step_off = c->bstep.as<const uint32_t>() + 2 * kXcd;
+    // global queues (gas, DM), then the Philox step offset
+    ENSURE(c, c->bstep, kQueueWords * sizeof(uint32_t));
+    const uint32_t* step_off = c->bstep.as<const uint32_t>() + 2 * kXcd * kQueueStride;
     for (int b = 0; b < nbox; ++b) {
         Cells& X = *c->boxes[b];
         // buffers the step writes (sized here so that enqueueing allocates nothing)
@@ -986,7 +1001,7 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
             ENSURE(c, X.psum_own, size_t(X.dm.n_own) * 8);
             ENSURE(c, X.slist, size_t(X.dm.n_own) * 4);
         }
-        ENSURE(c, X.qctr, (2 * kXcd + 4) * 4);
+        ENSURE(c, X.qctr, kQueueWords * 4);
         const int rs = int(sizeof(Real));
         Species& G = X.gas;
         Species& D = X.dm;
@@ -1036,7 +1051,7 @@ void batch_dm_side(dmb_ctx* c, const dmb_particles* gas, const dmb_params* par, 
 {
     constexpr bool kExact = sizeof(Real) == 8;
     DmPassArgs a0 = P.da[0];
-    a0.g.queue_ctr = c->bstep.as<uint32_t>() + kXcd;
+    a0.g.queue_ctr = c->bstep.as<uint32_t>() + kXcd * kQueueStride;
     a0.g.n_items = P.dm_items;
     {
         Phase ph(c, DMB_PH_PASS_DM);
@@ -1063,9 +1078,9 @@ dmb_status batch_enqueue(dmb_ctx* c, const dmb_particles* gas, const dmb_particl
         dmb_status s = gather_and_fill<Real, RM>(c, *c->boxes[b], gas + b, dm + b, par + b, out + b, out[b].counters);
         if (s != DMB_OK) return s;
     }
-    hipLaunchKernelGGL(k_fill_out, dim3(1), dim3(256), 0, c->stream, int64_t(0), int64_t(0), (double*)nullptr,
+    hipLaunchKernelGGL(k_fill_out, dim3(blocks_for(2 * kXcd * kQueueStride, 256)), dim3(256), 0, c->stream, int64_t(0), int64_t(0), (double*)nullptr,
                        (double*)nullptr, (double*)nullptr, (int32_t*)nullptr, (double*)nullptr, (double*)nullptr,
-                       (uint64_t*)nullptr, c->bstep.as<uint32_t>(), 2 * kXcd);
+                       (uint64_t*)nullptr, c->bstep.as<uint32_t>(), 2 * kXcd * kQueueStride);
     // as in the single-box step, the DM side (enqueued first) and the gas side run on two
     // streams, forked after the gathers and joined at the end (also inside a captured graph)
     const bool side = c->pass_overlap && P.gas_items > 0 && P.dm_items > 0;
@@ -1114,7 +1129,7 @@ dmb_status batch_run(dmb_ctx* c, int nbox, const dmb_particles* gas, const dmb_p
     BatchPlan P;
     dmb_status s = batch_prepare<Real, N, RM>(c, nbox, gas, dm, par, out, P);
     if (s != DMB_OK) return s;
-    uint32_t* step_off = c->bstep.as<uint32_t>() + 2 * kXcd;
+    uint32_t* step_off = c->bstep.as<uint32_t>() + 2 * kXcd * kQueueStride;
     HIPCHK(c, hipMemsetAsync(step_off, 0, sizeof(uint32_t), c->stream));
     if (!graph) {
         for (int k = 0; k < nsteps; ++k) {
@@ -1308,10 +1323,10 @@ void free_cells(Cells& X)
         DevBuf* all[] = {&P->cnt, &P->off, &P->cand, &P->icnt, &P->ioff, &P->it_tile, &P->it_cb, &P->it_ce,
                          &P->pad, &P->maxcnt, &P->beg, &P->psup, &P->ptile, &P->mask, &P->pcnt, &P->soff,
                          &P->scnt, &P->pw, &P->woff, &P->swt, &P->it_key, &P->it_key2, &P->it_id,
-                         &P->it_ord, &P->gbox, &P->gh, &P->gsup, &P->gq, &P->gcnt, &P->glist, &P->gmax};
+                         &P->it_ord, &P->it_slice, &P->slices, &P->gbox, &P->gh, &P->gsup, &P->gq, &P->gcnt, &P->glist, &P->gmax};
         for (DevBuf* b : all) fr(*b);
     }
-    DevBuf* rest[] = {&X.boxL, &X.part_gas, &X.part_p, &X.part_pm, &X.part_nb, &X.psum_own, &X.qctr, &X.slist};
+    DevBuf* rest[] = {&X.part_gas, &X.part_p, &X.part_pm, &X.part_nb, &X.psum_own, &X.qctr, &X.slist};
     for (DevBuf* b : rest) fr(*b);
 }
 
@@ -1399,7 +1414,7 @@ dmb_status dmb_create(dmb_ctx** out, int device, void* hip_stream)
     size_t tb = size_t(kTabCells) * 4 * sizeof(float4);
     const int64_t nnodes = 2 * int64_t(kTabNodesRegion);
     DevBuf nodes;
-    if (ensure(c, c->gtab, tb) != DMB_OK || ensure(c, c->X->boxL, 4 * sizeof(double)) != DMB_OK ||
+    if (ensure(c, c->gtab, tb) != DMB_OK ||
         ensure(c, c->os_err, sizeof(uint32_t)) != DMB_OK || ensure(c, c->tilt_gl, 32 * sizeof(double)) != DMB_OK ||
         ensure(c, nodes, size_t(nnodes) * 3 * sizeof(double)) != DMB_OK) {
         snprintf(g_create_err, sizeof(g_create_err), "%s", c->err);
@@ -1449,7 +1464,7 @@ dmb_status dmb_destroy(dmb_ctx* c)
     for (auto& b : c->heap.scan_tmp) fr(b);
     for (auto& b : c->heap2.scan_tmp) fr(b);
     DevBuf* side_bufs[] = {&c->heap2.os_hist, &c->heap2.os_status, &c->heap2.bbox_part, &c->heap2.counters_local,
-                           &c->heap2.pair_cnt, &c->heap2.rb_dev};
+                           &c->heap2.pair_cnt};
     for (DevBuf* b : side_bufs) fr(*b);
     if (c->side) hipStreamDestroy(c->side);
     if (c->ev_fork) hipEventDestroy(c->ev_fork);
@@ -1462,7 +1477,7 @@ dmb_status dmb_destroy(dmb_ctx* c)
     if (c->train_stream) hipStreamDestroy(c->train_stream);
     DevBuf* rest[] = {&c->gl64, &c->gl32, &c->gtab, &c->tilt_gl, &c->heap.os_hist, &c->heap.os_status, &c->os_err,
                       &c->heap.bbox_part, &c->heap.counters_local, &c->heap.pair_cnt, &c->bstep, &c->bgeom,
-                      &c->bitem, &c->heap.rb_dev};
+                      &c->bitem};
     for (DevBuf* b : rest) fr(*b);
     if (c->rb_host) hipHostFree(c->rb_host);
     if (c->run_dt_host) hipHostFree(c->run_dt_host);
@@ -1559,15 +1574,13 @@ struct Readback {
     void dmax(const void* p, int64_t n) { a.src[a.cnt] = p; a.n[a.cnt++] = n; }
 };
 
-// Runs the gather, copies the values into pinned memory and waits for them.
+// Writes the values into pinned memory and waits for them.
 dmb_status readback(dmb_ctx* c, const Readback& r, uint64_t* out)
 {
     if (r.a.cnt == 0) return DMB_OK;
-    ENSURE(c, c->S->rb_dev, kReadbackMax * sizeof(uint64_t));
     if (!c->rb_host) HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->rb_host), kReadbackMax * sizeof(uint64_t)));
-    hipLaunchKernelGGL(k_readback, dim3(1), dim3(256), 0, c->stream, r.a, c->S->rb_dev.as<uint64_t>());
+    hipLaunchKernelGGL(k_readback, dim3(1), dim3(256), 0, c->stream, r.a, c->rb_host);
     HIPCHK(c, hipGetLastError());
-    HIPCHK(c, hipMemcpyAsync(c->rb_host, c->S->rb_dev.p, r.a.cnt * sizeof(uint64_t), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     std::memcpy(out, c->rb_host, r.a.cnt * sizeof(uint64_t));
     return DMB_OK;
@@ -1578,11 +1591,9 @@ dmb_status build_cells_impl(dmb_ctx* c, const dmb_particles* gas, const dmb_part
 {
     dmb_status s;
     const bool periodic = par->box[0] > 0.0 || par->box[1] > 0.0 || par->box[2] > 0.0;
-    ENSURE(c, c->X->boxL, 4 * sizeof(double));
+    c->fp64_sums = par->precision == DMB_FP64;
     Phase ph(c, DMB_PH_BUILD);
     for (int k = 0; k < 3; ++k) c->X->built_L[k] = periodic ? par->box[k] : 0.0;
-    double Lh[4] = {c->X->built_L[0], c->X->built_L[1], c->X->built_L[2], 0.0};
-    HIPCHK(c, hipMemcpyAsync(c->X->boxL.p, Lh, sizeof(Lh), hipMemcpyHostToDevice, c->stream));
     Cells& X = *c->X;
     s = both(c, [&] { return build_species(c, X.gas, gas); }, [&] { return build_species(c, X.dm, dm); });
     if (s != DMB_OK) return s;
@@ -1607,16 +1618,9 @@ dmb_status build_cells_impl(dmb_ctx* c, const dmb_particles* gas, const dmb_part
         c->X->dm.n_own = int64_t(v[2]);
         c->X->dm.ntile = int64_t(v[3]);
     }
-    s = both(
-        c,
-        [&] {
-            dmb_status t = build_subtiles(c, X.gas);
-            return t == DMB_OK ? build_owner_tiles(c, X.gas) : t;
-        },
-        [&] {
-            dmb_status t = build_subtiles(c, X.dm);
-            return t == DMB_OK ? build_owner_tiles(c, X.dm) : t;
-        });
+    ENSURE(c, X.gp.maxcnt, 4); ENSURE(c, X.dp.maxcnt, 4);
+    s = both(c, [&] { return build_subtiles(c, X.gas, X.gp.maxcnt.as<uint32_t>()); },
+             [&] { return build_subtiles(c, X.dm, X.dp.maxcnt.as<uint32_t>()); });
     if (s != DMB_OK) return s;
     s = both(c, [&] { return cand_count(c, X.gas, X.dm, X.gp); }, [&] { return cand_count(c, X.dm, X.gas, X.dp); });
     if (s != DMB_OK) return s;
@@ -1632,10 +1636,10 @@ dmb_status build_cells_impl(dmb_ctx* c, const dmb_particles* gas, const dmb_part
             r.u64(A.nown_tile > 0 ? P.off.as<uint64_t>() + A.nown_tile : nullptr);
             r.u32(A.nown_tile > 0 && B.ntile > 0 ? P.maxcnt.p : nullptr);
         }
-        // largest h of each species from the super-tile maxima (periodic boxes)
+        // largest h of each species from the mega-tile maxima (periodic boxes)
         for (int sp = 0; sp < 2; ++sp) {
             Species& S = sp == 0 ? c->X->gas : c->X->dm;
-            r.dmax(periodic && S.nsuper > 0 ? S.shh.p : nullptr, periodic ? S.nsuper : 0);
+            r.dmax(periodic && S.nmega > 0 ? S.mhh.p : nullptr, periodic ? S.nmega : 0);
         }
         uint64_t v[6];
         if ((s = readback(c, r, v)) != DMB_OK) return s;
@@ -1953,7 +1957,11 @@ dmb_status dmb_sort_pairs(dmb_ctx* c, int64_t n, const uint64_t* keys_in, const 
         if (hipMemcpyAsync(k0, keys_in, size_t(n) * 8, hipMemcpyDeviceToDevice, c->stream) != hipSuccess ||
             hipMemcpyAsync(v0, vals_in, size_t(n) * 4, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
             s = fail(c, DMB_EHIP, "sort_pairs: copy failed");
-        if (s == DMB_OK) s = radix_sort(c, &k0, &v0, &k1, &v1, n, lo_bit, passes);
+        if (s == DMB_OK) s = ensure(c, c->S->os_hist, size_t(kOsWords) * 4);
+        if (s == DMB_OK) {
+            hipLaunchKernelGGL(k_os_clear, dim3(1), dim3(256), 0, c->stream, c->S->os_hist.as<uint32_t>(), kOsWords);
+            s = radix_sort(c, &k0, &v0, &k1, &v1, n, lo_bit, passes);
+        }
         uint32_t err = 0;
         if (s == DMB_OK && (hipMemcpyAsync(&err, c->os_err.p, 4, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
                             hipStreamSynchronize(c->stream) != hipSuccess))

@@ -9,6 +9,21 @@
 
 namespace dmb {
 
+// Selects by bit masks (m all ones or zero).  The compiler turns a select whose
+// operand is costly into a branch around the operand's computation; a mask keeps
+// straight-line code one block for the scheduler.
+__device__ __forceinline__ uint32_t bits(bool c) { return c ? ~0u : 0u; }
+__device__ __forceinline__ float masked(float x, uint32_t m) { return __uint_as_float(__float_as_uint(x) & m); }
+__device__ __forceinline__ double masked(double x, uint32_t m)
+{
+    const uint64_t b = uint64_t(__double_as_longlong(x));
+    return __longlong_as_double((long long)((uint64_t(uint32_t(b >> 32) & m) << 32) | (uint32_t(b) & m)));
+}
+__device__ __forceinline__ float either(uint32_t m, float x, float y)      // m: x, else y
+{
+    return __uint_as_float((__float_as_uint(x) & m) | (__float_as_uint(y) & ~m));
+}
+
 constexpr double kPi = 3.14159265358979323846;
 constexpr double kSqrtPi = 1.7724538509055160273;
 
@@ -198,41 +213,52 @@ __device__ __forceinline__ double overlap_g_table(const float4* __restrict__ tab
 // P_ij built from them would.  The gas pass (binary64 terms) takes the
 // binary64 lookup for such pairs (overlap_g_gas), so an owner whose every
 // neighbour is that close to contact keeps its relative accuracy.
+// In two halves, so that a pass can put other work between them: begin() finds
+// the cell and issues its loads, value() takes them.
+struct Overlap32 {
+    float4 q0, q2, q3;
+    float2 q1;
+    float a, b, env, ib;
+    __device__ __forceinline__ void begin(const float4* __restrict__ tab, double d2, double h1, double h2)
+    {
+        const double hbd = h1 > h2 ? h1 : h2, hsd = h1 > h2 ? h2 : h1;
+        // binary32 root (x times its reciprocal root), then one Newton step in binary64
+        const float d2f = float(d2), ir = __builtin_amdgcn_rsqf(d2f);
+        const double d0 = double(d2f * ir);
+        const double d = masked(fma(fma(-d0, d0, d2), double(0.5f * ir), d0), bits(d2f > 0.f));
+        const double innerd = hbd - d;
+        const bool shell = innerd < hsd;
+        const uint32_t ms = bits(shell);
+        const float hb = float(hbd), hs = float(hsd), inner = float(innerd);
+        const float num = either(ms, float((hbd + hsd) - d), hs);
+        ib = __builtin_amdgcn_rcpf(hb);
+        const float r = num * __builtin_amdgcn_rcpf(either(ms, hs, inner));   // rho (shell) or kappa (core)
+        const float eta = hs * ib;
+        const float x = either(ms, 0.5f * r, float(d) * ib), y = either(ms, eta, r);
+        const float fx = fminf(x, 1.f) * float(kTabN), fy = fminf(y, 1.f) * float(kTabN);
+        const int i = min(int(fx), kTabN - 1), j = min(int(fy), kTabN - 1);
+        a = fx - float(i);
+        b = fy - float(j);
+        const float4* c = tab + 4 * ((shell ? 0 : kTabCellsRegion) + j * kTabN + i);
+        q0 = c[0]; q2 = c[1]; q3 = c[2];
+        q1 = *reinterpret_cast<const float2*>(c + 3);
+        const float r2 = r * r, r4 = r2 * r2, tc = inner * ib;
+        env = either(ms, eta * eta * eta * (r4 * r4), tc * tc * tc);
+    }
+    __device__ __forceinline__ float value() const
+    {
+        auto cubic = [this](float4 q) { return fmaf(fmaf(fmaf(q.w, a, q.z), a, q.y), a, q.x); };
+        const float p0 = cubic(q0), p2 = cubic(q2), p3 = cubic(q3), p1 = fmaf(q1.y, a, q1.x);
+        const float Q = fmaf(fmaf(fmaf(p3, b, p2), b, p1), b, p0);
+        return Q * env * (ib * ib * ib);
+    }
+};
+
 __device__ __forceinline__ float overlap_g_table32(const float4* __restrict__ tab, double d2, double h1, double h2)
 {
-    const double hbd = h1 > h2 ? h1 : h2, hsd = h1 > h2 ? h2 : h1;
-    const float d0f = __builtin_amdgcn_sqrtf(float(d2));
-    const double d0 = double(d0f);
-    const double d = d0f > 0.f ? fma(d2 - d0 * d0, double(0.5f * __builtin_amdgcn_rcpf(d0f)), d0) : 0.0;
-    const double innerd = hbd - d;
-    const bool shell = innerd < hsd;
-    const float num = float(shell ? (hbd + hsd) - d : hsd);
-    const float hb = float(hbd), hs = float(hsd), inner = float(innerd);
-    const float ib = __builtin_amdgcn_rcpf(hb);
-    const float r = num * __builtin_amdgcn_rcpf(shell ? hs : inner);   // rho (shell) or kappa (core)
-    const float eta = hs * ib;
-    const float x = shell ? 0.5f * r : float(d) * ib, y = shell ? eta : r;
-    const float fx = fminf(x, 1.f) * float(kTabN), fy = fminf(y, 1.f) * float(kTabN);
-    const int i = min(int(fx), kTabN - 1), j = min(int(fy), kTabN - 1);
-    const float a = fx - float(i), b = fy - float(j);
-    const float4* c = tab + 4 * ((shell ? 0 : kTabCellsRegion) + j * kTabN + i);
-    const float4 q0 = c[0], q2 = c[1], q3 = c[2], q1 = c[3];
-    auto cubic = [a](float4 q) { return fmaf(fmaf(fmaf(q.w, a, q.z), a, q.y), a, q.x); };
-    const float p0 = cubic(q0), p2 = cubic(q2), p3 = cubic(q3), p1 = fmaf(q1.y, a, q1.x);
-    const float Q = fmaf(fmaf(fmaf(p3, b, p2), b, p1), b, p0);
-    const float r2 = r * r, r4 = r2 * r2, tc = inner * ib;
-    const float env = shell ? eta * eta * eta * (r4 * r4) : tc * tc * tc;
-    return Q * env * (ib * ib * ib);
-}
-
-// For the gas pass (binary64 terms): the binary32 lookup, and the binary64
-// one for the rare pair so close to contact that its binary32 value nears
-// the bottom of the binary32 range, so every overlap keeps its relative
-// accuracy.
-__device__ __forceinline__ double overlap_g_gas(const float4* __restrict__ tab, double d2, double h1, double h2)
-{
-    const float g = overlap_g_table32(tab, d2, h1, h2);
-    return g >= 1e-30f ? double(g) : overlap_g_table(tab, d2, h1, h2);
+    Overlap32 o;
+    o.begin(tab, d2, h1, h2);
+    return o.value();
 }
 
 // g in binary64: delta and eta by division (near contact g goes as the eighth
@@ -253,21 +279,28 @@ __device__ __forceinline__ T overlap_g_exact(T d, T hi, T hj)
 // constants between rounds.
 struct U4 { uint32_t x, y, z, w; };
 
-__device__ __forceinline__ U4 philox4x32_10(U4 c, uint32_t k0, uint32_t k1)
+// x ^ y ^ z in one instruction (v_bitop3_b32)
+__device__ __forceinline__ uint32_t xor3(uint32_t x, uint32_t y, uint32_t z)
+{
+    return uint32_t(__builtin_amdgcn_bitop3_b32(x, y, z, 0x96));
+}
+
+template <int R>
+__device__ __forceinline__ U4 philox_rounds(U4 c, uint32_t k0, uint32_t k1)
 {
     // the key schedule is rebuilt per call (scalar adds): hoisted, its 20 words
     // would occupy scalar registers for a whole pass.  Keys are wave-uniform.
-    asm volatile("" : "+s"(k0), "+s"(k1));
+    asm("" : "+s"(k0), "+s"(k1) : "v"(c.x));
 #pragma unroll
-    for (int r = 0; r < 10; ++r) {
+    for (int r = 0; r < R; ++r) {
         // one 32x32->64 multiply (v_mad_u64_u32) gives both halves
         const uint64_t p0 = uint64_t(c.x) * 0xD2511F53u, p1 = uint64_t(c.z) * 0xCD9E8D57u;
         const uint32_t lo0 = uint32_t(p0), hi0 = uint32_t(p0 >> 32);
         const uint32_t lo1 = uint32_t(p1), hi1 = uint32_t(p1 >> 32);
         U4 n;
-        n.x = hi1 ^ c.y ^ k0;
+        n.x = xor3(hi1, c.y, k0);
         n.y = lo1;
-        n.z = hi0 ^ c.w ^ k1;
+        n.z = xor3(hi0, c.w, k1);
         n.w = lo0;
         c = n;
         k0 += 0x9E3779B9u;
@@ -276,9 +309,16 @@ __device__ __forceinline__ U4 philox4x32_10(U4 c, uint32_t k0, uint32_t k1)
     return c;
 }
 
+__device__ __forceinline__ U4 philox4x32_10(U4 c, uint32_t k0, uint32_t k1) { return philox_rounds<10>(c, k0, k1); }
+
 // 24-bit centred uniform ((r >> 8) + 1/2) 2^-24, exactly representable.
 template <typename T>
-__device__ __forceinline__ T u24(uint32_t r) { return (T(r >> 8) + T(0.5)) * T(1.0 / 16777216.0); }
+__device__ __forceinline__ T u24(uint32_t r)
+{
+    // one rounding of the 25-bit sum either way; the scale is a power of two
+    if constexpr (sizeof(T) == 4) return fmaf(float(r >> 8), 1.f / 16777216.f, 0.5f / 16777216.f);
+    else return (T(r >> 8) + T(0.5)) * T(1.0 / 16777216.0);
+}
 
 // Stream layout shared with every consumer of the random numbers:
 // counter = (dm index, gas index, step, tag | box << 8), key = seed.
@@ -290,6 +330,50 @@ __device__ __forceinline__ U4 philox_block(uint32_t i, uint32_t j, uint32_t step
     U4 c{i, j, step, tag | (box << 8)};
     return philox4x32_10(c, k0, k1);
 }
+
+// The blocks philox_block(i, j, step, tag, box) of many pairs (i, j): the first
+// three rounds hold five of the ten-round block's twenty products that depend
+// on i alone or on j alone, formed once per i (owner) and once per j (other)
+// instead of per pair.  With z, w, ... as the counter words after a round,
+//   round 1: x = hi(step M1) ^ j ^ k0 (j alone), y = lo(step M1),
+//            z = hi(i M0) ^ (tag | box << 8) ^ k1, w = lo(i M0) (i alone);
+//   round 2: x M0 is j's, z M1 is i's; x, y are i's, w is j's;
+//   round 3: x M0 is i's.
+// pair() takes the rest, seven rounds and one product.
+struct PhiloxPair {
+    uint32_t x1, y1, w0, k0, k1;
+    __device__ __forceinline__ PhiloxPair(uint32_t step, uint32_t tag, uint32_t box, uint32_t k0_, uint32_t k1_)
+        : k0(k0_), k1(k1_)
+    {
+        const uint64_t p = uint64_t(step) * 0xCD9E8D57u;
+        x1 = uint32_t(p >> 32) ^ k0;
+        y1 = uint32_t(p);
+        w0 = (tag | (box << 8)) ^ k1;
+    }
+    // j's part: the two halves of its round-2 product
+    __device__ __forceinline__ void other(uint32_t j, uint32_t* a, uint32_t* b) const
+    {
+        const uint64_t p = uint64_t(x1 ^ j) * 0xD2511F53u;
+        *a = uint32_t(p >> 32);
+        *b = uint32_t(p);
+    }
+    // i's part: (w after round 1 ^ key, y after round 2 ^ key, high and low half of the round-3 product (high ^ key))
+    __device__ __forceinline__ uint4 owner(uint32_t i) const
+    {
+        const uint64_t p = uint64_t(i) * 0xD2511F53u;
+        const uint64_t q = uint64_t(uint32_t(p >> 32) ^ w0) * 0xCD9E8D57u;
+        const uint32_t x2 = uint32_t(q >> 32) ^ y1 ^ (k0 + 0x9E3779B9u);
+        const uint64_t r = uint64_t(x2) * 0xD2511F53u;
+        return make_uint4(uint32_t(p) ^ (k1 + 0xBB67AE85u), uint32_t(q) ^ (k0 + 2u * 0x9E3779B9u),
+                          uint32_t(r >> 32) ^ (k1 + 2u * 0xBB67AE85u), uint32_t(r));
+    }
+    __device__ __forceinline__ U4 pair(uint4 o, uint32_t a, uint32_t b) const
+    {
+        const uint64_t p = uint64_t(a ^ o.x) * 0xCD9E8D57u;
+        U4 c{uint32_t(p >> 32) ^ o.y, uint32_t(p), o.z ^ b, o.w};
+        return philox_rounds<7>(c, k0 + 3u * 0x9E3779B9u, k1 + 3u * 0xBB67AE85u);
+    }
+};
 
 // cos(2 pi u), sin(2 pi u): the gfx950 transcendental unit takes turns.
 __device__ __forceinline__ void sincos_turns(float u, float* s, float* c)
@@ -305,6 +389,9 @@ __device__ __forceinline__ void sincos_turns(double u, double* s, double* c) { s
 // subnormal arguments is not needed.
 __device__ __forceinline__ float log_real(float x) { return __builtin_amdgcn_logf(x) * 0.693147180559945309f; }
 __device__ __forceinline__ double log_real(double x) { return log(x); }
+// -2 ln x; the factor -2 only moves exponents, so it joins ln 2 without a change of rounding
+__device__ __forceinline__ float neg2log_real(float x) { return __builtin_amdgcn_logf(x) * (-2.f * 0.693147180559945309f); }
+__device__ __forceinline__ double neg2log_real(double x) { return -2.0 * log(x); }
 __device__ __forceinline__ float sqrt_real(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ double sqrt_real(double x) { return sqrt(x); }
 __device__ __forceinline__ float rcp_real(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -315,7 +402,7 @@ template <typename T>
 __device__ __forceinline__ void normals3(U4 r, T z[3])
 {
     T u0 = u24<T>(r.x), u1 = u24<T>(r.y), u2 = u24<T>(r.z), u3 = u24<T>(r.w);
-    T r0 = sqrt_real(T(-2) * log_real(u0)), r1 = sqrt_real(T(-2) * log_real(u2));
+    T r0 = sqrt_real(neg2log_real(u0)), r1 = sqrt_real(neg2log_real(u2));
     T s, c, s2, c2;
     sincos_turns(u1, &s, &c);
     sincos_turns(u3, &s2, &c2);
@@ -412,21 +499,23 @@ __device__ __forceinline__ float exp_neg(float x) { return __expf(-x); }
 __device__ __forceinline__ double exp_neg(double x) { return exp(-x); }
 
 template <int N, typename T>
-__device__ __forceinline__ void rate_1f1(T x, T* FA, T* FB)
+__device__ __forceinline__ void rate_1f1_small(T x, T* FA, T* FB)      // x < 1: Taylor series
 {
     constexpr RateCoef<N> C{};
-    if (x < T(1)) {
-        constexpr int K = RealTraits<T>::template taylor<N>();
-        T fa = T(C.ca[K - 1]), fb = T(C.cb[K - 1]);
+    constexpr int K = RealTraits<T>::template taylor<N>();
+    T fa = T(C.ca[K - 1]), fb = T(C.cb[K - 1]);
 #pragma unroll
-        for (int k = K - 2; k >= 0; --k) {
-            fa = fa * x + T(C.ca[k]);
-            fb = fb * x + T(C.cb[k]);
-        }
-        *FA = fa;
-        *FB = fb;
-        return;
+    for (int k = K - 2; k >= 0; --k) {
+        fa = fa * x + T(C.ca[k]);
+        fb = fb * x + T(C.cb[k]);
     }
+    *FA = fa;
+    *FB = fb;
+}
+
+template <int N, typename T>
+__device__ __forceinline__ void rate_1f1_large(T x, T* FA, T* FB)      // x >= 1: closed forms
+{
     T t, r, it;
     if constexpr (sizeof(T) == 4) {
         it = __builtin_amdgcn_rsqf(x);   // x >= 1 here
@@ -457,6 +546,13 @@ __device__ __forceinline__ void rate_1f1(T x, T* FA, T* FB)
         *FB = (spE * (((T(8) * x + T(60)) * x + T(90)) * x + T(15)) * it + T(2) * ((T(4) * x + T(28)) * x + T(33)) * ex) *
               T(1.0 / 96.0);
     }
+}
+
+template <int N, typename T>
+__device__ __forceinline__ void rate_1f1(T x, T* FA, T* FB)
+{
+    if (x < T(1)) rate_1f1_small<N, T>(x, FA, FB);
+    else rate_1f1_large<N, T>(x, FA, FB);
 }
 
 // Rate integrals by quadrature (for any momentum-transfer cross section;

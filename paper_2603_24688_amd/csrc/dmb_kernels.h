@@ -182,9 +182,10 @@ __global__ __launch_bounds__(256) void k_bbox_partial(const double* __restrict__
     }
 }
 
-// Scalars the host reads after a build stage, gathered into one buffer so
-// that one copy brings them back: a 4- or 8-byte value, or the maximum of n
-// binary64 values (h maxima).  A null source reads as 0.  One block.
+// Scalars the host reads after a build stage, written straight into its pinned
+// buffer (a copy after the kernel costs another 10 us of latency): a 4- or 8-byte
+// value, or the maximum of n binary64 values (h maxima).  A null source reads as
+// 0.  One block.
 constexpr int kReadbackMax = 8;
 struct ReadbackArgs {
     const void* src[kReadbackMax];
@@ -220,9 +221,18 @@ __global__ __launch_bounds__(256) void k_readback(ReadbackArgs a, uint64_t* __re
     }
 }
 
-// cube[0..2] = origin, cube[3] = 2^21 / side (quantisation scale).  One wave.
-__global__ __launch_bounds__(64) void k_bbox_final(const double* __restrict__ part, int nparts,
-                                                   const double* __restrict__ boxL, double* __restrict__ cube)
+// Cube that holds [lo, hi]: cube[0..2] = origin, cube[3] = 2^21 / side (quantisation scale).
+__host__ __device__ inline void key_cube(const double lo[3], const double hi[3], double* cube)
+{
+    double side = 0.0;
+    for (int a = 0; a < 3; ++a) side = fmax(side, hi[a] - lo[a]);
+    side = side > 0.0 ? side * (1.0 + 1e-9) + 1e-300 : 1.0;
+    for (int a = 0; a < 3; ++a) cube[a] = lo[a];
+    cube[3] = 2097152.0 / side;
+}
+
+// The cube of an open region from the partial bounds.  One wave.
+__global__ __launch_bounds__(64) void k_bbox_final(const double* __restrict__ part, int nparts, double* __restrict__ cube)
 {
     double lo[3], hi[3];
     for (int a = 0; a < 3; ++a) { lo[a] = 1e300; hi[a] = -1e300; }
@@ -236,16 +246,7 @@ __global__ __launch_bounds__(64) void k_bbox_final(const double* __restrict__ pa
             lo[a] = fmin(lo[a], __shfl_xor(lo[a], d));
             hi[a] = fmax(hi[a], __shfl_xor(hi[a], d));
         }
-    if (lane_id() != 0) return;
-    bool periodic = boxL[0] > 0.0;
-    double side = 0.0;
-    for (int a = 0; a < 3; ++a) {
-        if (periodic) { lo[a] = 0.0; hi[a] = boxL[a]; }
-        side = fmax(side, hi[a] - lo[a]);
-    }
-    side = side > 0.0 ? side * (1.0 + 1e-9) + 1e-300 : 1.0;
-    for (int a = 0; a < 3; ++a) cube[a] = lo[a];
-    cube[3] = 2097152.0 / side;
+    if (lane_id() == 0) key_cube(lo, hi, cube);
 }
 
 __device__ __forceinline__ uint64_t spread21(uint64_t x)
@@ -259,22 +260,29 @@ __device__ __forceinline__ uint64_t spread21(uint64_t x)
     return x;
 }
 
+// Box sides (0: open) and, of a periodic box, the cube of its keys.
+struct KeyBox { double L[3], cube[4]; };
+
 // Morton key of each particle (input order), plus a packed copy of its
 // position (wrapped into [0, L) when periodic) and h, so that the gather into
 // Morton order (in k_subtile_write) reads one 32-byte record per particle.
+// Also clears the counters of the radix sort that follows.
 __global__ __launch_bounds__(256) void k_morton(const double* __restrict__ pos, const double* __restrict__ h, int64_t n,
-                                                const double* __restrict__ cube, const double* __restrict__ boxL,
+                                                const double* __restrict__ open_cube, KeyBox box,
                                                 uint64_t* __restrict__ keys, uint32_t* __restrict__ vals,
-                                                double4* __restrict__ rec)
+                                                double4* __restrict__ rec, uint32_t* __restrict__ os_words, int n_os)
 {
+    if (blockIdx.x == 0)
+        for (int k = int(threadIdx.x); k < n_os; k += 256) os_words[k] = 0u;
     int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= n) return;
     uint64_t q[3];
     double p[3];
     for (int a = 0; a < 3; ++a) {
         double x = pos[3 * i + a];
-        if (boxL[a] > 0.0) x -= boxL[a] * floor(x / boxL[a]);
+        if (box.L[a] > 0.0) x -= box.L[a] * floor(x / box.L[a]);
         p[a] = x;
+        const double* cube = open_cube ? open_cube : box.cube;
         double f = (x - cube[a]) * cube[3];
         f = fmin(fmax(f, 0.0), 2097151.0);
         q[a] = uint64_t(f);
@@ -289,7 +297,7 @@ __global__ __launch_bounds__(256) void k_active_flags(const uint32_t* __restrict
 {
     int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (k > n) return;
-    flag[k] = (k < n) ? (active ? (active[perm[k]] != 0 ? 1u : 0u) : 1u) : 0u;
+    flag[k] = k < n && active[perm[k]] != 0 ? 1u : 0u;
 }
 
 __global__ __launch_bounds__(256) void k_compact(const uint32_t* __restrict__ flag, const uint32_t* __restrict__ off,
@@ -299,32 +307,37 @@ __global__ __launch_bounds__(256) void k_compact(const uint32_t* __restrict__ fl
     if (k < n && flag[k]) own[off[k]] = uint32_t(k);
 }
 
-// Tile bounds: one wave per tile of 64 consecutive entries of `list`
-// (identity when list == nullptr).  box = {lo xyz, hi xyz}, hmax.
-__global__ __launch_bounds__(64) void k_tile_bounds(const uint32_t* __restrict__ list, int64_t n,
-                                                    const double* __restrict__ sx, const double* __restrict__ sy,
-                                                    const double* __restrict__ sz, const double* __restrict__ sh,
-                                                    double* __restrict__ box, double* __restrict__ hmax)
+// Bounds of up to 64 particles, one per lane (v: the lane has one): box = {lo xyz, hi xyz}, hmax.
+__device__ __forceinline__ void tile_bounds(int lane, bool v, double px, double py, double pz, double ph, double* box,
+                                            double* hmax)
 {
-    int64_t t = blockIdx.x;
-    int64_t k = t * kTile + lane_id();
-    bool v = k < n;
-    int64_t p = v ? (list ? int64_t(list[k]) : k) : 0;
-    double x = v ? sx[p] : 1e300, y = v ? sy[p] : 1e300, z = v ? sz[p] : 1e300;
-    double X = v ? sx[p] : -1e300, Y = v ? sy[p] : -1e300, Z = v ? sz[p] : -1e300;
-    double hh = v ? sh[p] : 0.0;
+    double x = v ? px : 1e300, y = v ? py : 1e300, z = v ? pz : 1e300;
+    double X = v ? px : -1e300, Y = v ? py : -1e300, Z = v ? pz : -1e300;
+    double hh = v ? ph : 0.0;
     // minima / maxima over the wave in registers; totals at lane 63
-    seg_scan_up(lane_id(), 0, [&](auto ctl, auto rows, bool take) {
+    seg_scan_up(lane, 0, [&](auto ctl, auto rows, bool take) {
         constexpr int C = decltype(ctl)::value, R = decltype(rows)::value;
         x = dpp_take_min<C, R>(x, take); y = dpp_take_min<C, R>(y, take); z = dpp_take_min<C, R>(z, take);
         X = dpp_take_max<C, R>(X, take); Y = dpp_take_max<C, R>(Y, take); Z = dpp_take_max<C, R>(Z, take);
         hh = dpp_take_max<C, R>(hh, take);
     });
-    if (lane_id() == 63) {
-        box[6 * t + 0] = x; box[6 * t + 1] = y; box[6 * t + 2] = z;
-        box[6 * t + 3] = X; box[6 * t + 4] = Y; box[6 * t + 5] = Z;
-        hmax[t] = hh;
+    if (lane == 63) {
+        box[0] = x; box[1] = y; box[2] = z;
+        box[3] = X; box[4] = Y; box[5] = Z;
+        *hmax = hh;
     }
+}
+
+// Tile bounds: one wave per tile of 64 consecutive entries of `list`.
+__global__ __launch_bounds__(64) void k_tile_bounds(const uint32_t* __restrict__ list, int64_t n,
+                                                    const double* __restrict__ sx, const double* __restrict__ sy,
+                                                    const double* __restrict__ sz, const double* __restrict__ sh,
+                                                    double* __restrict__ box, double* __restrict__ hmax)
+{
+    const int64_t t = blockIdx.x, k = t * kTile + lane_id();
+    const bool v = k < n;
+    const int64_t p = v ? int64_t(list[k]) : 0;
+    tile_bounds(lane_id(), v, v ? sx[p] : 0.0, v ? sy[p] : 0.0, v ? sz[p] : 0.0, v ? sh[p] : 0.0, box + 6 * t, hmax + t);
 }
 
 // Binary32 copy of a node's bounds for the candidate search, rounded
@@ -338,15 +351,17 @@ __device__ __forceinline__ void write_node_q(float4* q, const double b[6], doubl
     q[3] = make_float4(__double2float_ru(u[3]), __double2float_ru(u[4]), __double2float_ru(u[5]), 0.f);
 }
 
-// Super-tile bounds over 64 consecutive tiles: box, max h, support box.
+// Super-tile bounds over 64 consecutive tiles: box, max h, support box; clears *word.
 __global__ __launch_bounds__(64) void k_super_bounds(int64_t ntile, const double* __restrict__ tbox,
                                                      const double* __restrict__ th, const double* __restrict__ tsup,
                                                      double* __restrict__ box, double* __restrict__ hmax,
-                                                     double* __restrict__ sup, float4* __restrict__ q)
+                                                     double* __restrict__ sup, float4* __restrict__ q,
+                                                     uint32_t* __restrict__ word)
 {
     int64_t s = blockIdx.x;
     int64_t t = s * kTile + lane_id();
     bool v = t < ntile;
+    if (t == 0) *word = 0u;
     double b[6], u[6];
     for (int a = 0; a < 3; ++a) {
         b[a] = v ? tbox[6 * t + a] : 1e300;
@@ -403,10 +418,20 @@ __device__ __forceinline__ uint64_t subtile_cuts(const uint64_t* __restrict__ ke
     return __ballot(valid && (lane == 0 || lvl < med - cut_delta));
 }
 
-// cnt[c] = number of sub-tiles of chunk c.
+// cnt[c] = number of sub-tiles of chunk c.  With every particle active (own not
+// null) also the owner list, which is the identity, and its flags and offsets.
 __global__ __launch_bounds__(64) void k_subtile_count(const uint64_t* __restrict__ keys, int64_t n, int lo_bit,
-                                                      int cut_delta, uint32_t* __restrict__ cnt)
+                                                      int cut_delta, uint32_t* __restrict__ cnt,
+                                                      uint32_t* __restrict__ own, uint32_t* __restrict__ flag,
+                                                      uint32_t* __restrict__ flag_off)
 {
+    const int64_t k = int64_t(blockIdx.x) * kTile + lane_id();
+    if (own && k < n) {
+        own[k] = uint32_t(k);
+        flag[k] = 1u;
+        flag_off[k] = uint32_t(k);
+        if (k == n - 1) flag_off[n] = uint32_t(n);
+    }
     const uint64_t cm = subtile_cuts(keys, n, lo_bit, cut_delta, blockIdx.x);
     if (lane_id() == 0) cnt[blockIdx.x] = uint32_t(__popcll(cm));
 }
@@ -419,7 +444,8 @@ __device__ __forceinline__ double sup_hi(double x, double h) { const double v = 
 // Starts, counts and bounds of the sub-tiles of chunk c at off[c]...: box,
 // max h and support box (union of the particles' [x - h, x + h]), each a
 // segmented reduction over the sub-tile's run of lanes.  Also writes the
-// chunk's sorted SoA position and h, gathered from the packed records.
+// chunk's sorted SoA position and h, gathered from the packed records, and, with
+// every particle active (obox not null), the chunk's bounds as owner tile c.
 __global__ __launch_bounds__(64) void k_subtile_write(const uint64_t* __restrict__ keys, int64_t n, int lo_bit,
                                                       int cut_delta, const uint32_t* __restrict__ off,
                                                       uint32_t* __restrict__ sub_start, uint32_t* __restrict__ sub_cnt,
@@ -428,7 +454,8 @@ __global__ __launch_bounds__(64) void k_subtile_write(const uint64_t* __restrict
                                                       double* __restrict__ sy, double* __restrict__ sz,
                                                       double* __restrict__ sh, double* __restrict__ box,
                                                       double* __restrict__ hmax, double* __restrict__ sup,
-                                                      float4* __restrict__ q)
+                                                      float4* __restrict__ q, double* __restrict__ obox,
+                                                      double* __restrict__ oh)
 {
     const int lane = lane_id();
     const int64_t c = blockIdx.x;
@@ -477,6 +504,7 @@ __global__ __launch_bounds__(64) void k_subtile_write(const uint64_t* __restrict
         hmax[idx] = hm;
         write_node_q(q + 4 * idx, b, hm, u);
     }
+    if (obox) tile_bounds(lane, valid, x3[0], x3[1], x3[2], hh, obox + 6 * c, oh + c);
 }
 
 // Squared gap between two boxes (minimum over periodic images).
@@ -749,55 +777,61 @@ __global__ __launch_bounds__(256) void k_expand(int64_t npairs, const uint32_t* 
     for (int k = 0; m; ++k, m &= m - 1) dst[k] = s0 + uint32_t(__ffsll((unsigned long long)m) - 1);
 }
 
+// How a pass's candidate lists are cut into work items: equal pieces of at most
+// `split` sub-tiles, fewer in a small problem (down to min_split) so that about
+// `target` pieces keep every compute unit busy; then, while there are fewer than
+// `items` of them, each piece into up to kMaxSlices slices, which share its chunks of
+// sub-tiles and take its groups of 64 slots in turn.  Binary64 sums (the gas pass, and
+// the DM pass of a structure built for binary64) are cut down to one sub-tile.  The DM pass in binary32 adds up to 64 terms of a group
+// in binary32, so where its groups begin is part of its result: its pieces stay as
+// coarse as that order was laid down (32 per compute unit, at least 4 sub-tiles), and
+// slices, which begin no group anew, give the rest: 0.33 instead of 0.59 ms for the DM
+// pass of a galaxy of 12k + 48k.
+struct ItemCut { uint32_t split, min_split, target, items; };
+constexpr uint32_t kMaxSlices = 4;
+
 // Per owner tile: its candidate sub-tile count, where its list starts and
 // the particles of its candidates (poff: pair offsets per tile, soff and
-// woff: sub-tile and particle offsets per pair).
-__global__ __launch_bounds__(256) void k_tile_subs(int64_t nt, const uint64_t* __restrict__ poff,
-                                                   const uint64_t* __restrict__ soff, const uint64_t* __restrict__ woff,
-                                                   uint32_t* __restrict__ scnt, uint64_t* __restrict__ sbeg,
-                                                   uint32_t* __restrict__ swt)
+// woff: sub-tile and particle offsets per pair), and its work items; also the
+// number of slices.
+__global__ __launch_bounds__(256) void k_tile_items(int64_t nt, const uint64_t* __restrict__ poff,
+                                                    const uint64_t* __restrict__ soff, const uint64_t* __restrict__ woff,
+                                                    uint32_t* __restrict__ scnt, uint64_t* __restrict__ sbeg,
+                                                    uint32_t* __restrict__ swt, ItemCut cut,
+                                                    uint32_t* __restrict__ icnt, uint32_t* __restrict__ slices)
 {
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (t > nt) return;
-    if (t == nt) { scnt[t] = 0u; return; }
+    const uint64_t total = soff[poff[nt]];
+    uint32_t s = cut.split;
+    if (cut.target > 0 && s > cut.min_split)
+        s = uint32_t(max<uint64_t>(cut.min_split, min<uint64_t>(s, (total + cut.target - 1) / cut.target)));
+    const uint32_t ns = uint32_t(max<uint64_t>(1, min<uint64_t>(kMaxSlices, uint64_t(cut.items) * s / max<uint64_t>(total, 1))));
+    if (t == nt) { scnt[t] = 0u; icnt[t] = 0u; *slices = ns; return; }
     const uint64_t b = soff[poff[t]], e = soff[poff[t + 1]];
     sbeg[t] = b;
     scnt[t] = uint32_t(e - b);
     swt[t] = uint32_t(min<uint64_t>(woff[poff[t + 1]] - woff[poff[t]], 0xFFFFFFFFull));
+    icnt[t] = (uint32_t(e - b) + s - 1) / s * ns;
 }
 
-// Work items: each tile's candidate list cut into equal pieces of at most
-// `split` sub-tiles.  A small problem (fewer than `target` x `split` candidate
-// sub-tiles in all, `total`) gets a smaller piece size, down to kItemMinSplit,
-// so that about `target` items keep every compute unit busy.
-constexpr uint32_t kItemMinSplit = 4;
-__global__ __launch_bounds__(256) void k_item_count(const uint32_t* __restrict__ cnt, int64_t nt, uint32_t split,
-                                                    const uint64_t* __restrict__ total, uint32_t target,
-                                                    uint32_t* __restrict__ icnt)
-{
-    int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t > nt) return;
-    uint32_t s = split;
-    if (target > 0 && split > kItemMinSplit) {
-        const uint64_t want = (*total + target - 1) / target;
-        s = uint32_t(max<uint64_t>(kItemMinSplit, min<uint64_t>(split, want)));
-    }
-    icnt[t] = t < nt ? (cnt[t] + s - 1) / s : 0u;
-}
-
-// Item it: its tile t (binary search over item_off), and the piece of t's
-// list (cnt[t] sub-tiles from beg[t]) it covers: piece k of n holds
-// candidates [k cnt / n, (k + 1) cnt / n).  Also a sort key that orders the
+// Item it: its tile t (binary search over item_off), the piece of t's
+// list (cnt[t] sub-tiles from beg[t]) it covers, piece k of n holding
+// candidates [k cnt / n, (k + 1) cnt / n), and its slice of the piece.  Also a sort key that orders the
 // items by decreasing candidate particles (wt: per tile; the item takes its
 // share of the tile's), so that a pass starts the largest ones first and
-// ends on small ones.
+// ends on small ones, and the cleared counters of the sort by it.
 __global__ __launch_bounds__(256) void k_item_write(const uint64_t* __restrict__ beg, const uint32_t* __restrict__ cnt,
                                                     const uint32_t* __restrict__ wt,
                                                     const uint32_t* __restrict__ item_off, int64_t nt, int64_t nitems,
+                                                    const uint32_t* __restrict__ slices, uint32_t* __restrict__ it_slice,
                                                     uint32_t* __restrict__ it_tile, uint64_t* __restrict__ it_cb,
                                                     uint64_t* __restrict__ it_ce, uint64_t* __restrict__ it_key,
-                                                    uint32_t* __restrict__ it_id)
+                                                    uint32_t* __restrict__ it_id, uint32_t* __restrict__ os_words,
+                                                    int n_os)
 {
+    if (blockIdx.x == 0)
+        for (int k = int(threadIdx.x); k < n_os; k += 256) os_words[k] = 0u;
     const int64_t it = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (it >= nitems) return;
     int64_t lo = 0, hi = nt;      // largest t with item_off[t] <= it
@@ -805,13 +839,15 @@ __global__ __launch_bounds__(256) void k_item_write(const uint64_t* __restrict__
         const int64_t mid = (lo + hi) >> 1;
         if (int64_t(item_off[mid]) <= it) lo = mid; else hi = mid;
     }
-    const uint64_t n = item_off[lo + 1] - item_off[lo], k = uint64_t(it - int64_t(item_off[lo])), c = cnt[lo];
+    const uint32_t ns = *slices, kt = uint32_t(it - int64_t(item_off[lo]));
+    const uint64_t n = (item_off[lo + 1] - item_off[lo]) / ns, k = kt / ns, c = cnt[lo];
+    it_slice[it] = (kt % ns) | (ns << 16);
     const uint64_t cb = k * c / n, ce = (k + 1) * c / n;
     it_tile[it] = uint32_t(lo);
     it_cb[it] = beg[lo] + cb;
     it_ce[it] = beg[lo] + ce;
     // 8-bit key, 1/12 octave per step: 255 for an empty item, smaller for larger ones
-    const double w = double(wt[lo]) * double(ce - cb) / double(max<uint64_t>(c, 1));
+    const double w = double(wt[lo]) * double(ce - cb) / (double(max<uint64_t>(c, 1)) * double(ns));
     it_key[it] = 255u - uint32_t(fmin(255.0, 12.0 * log2(w + 1.0)));
     it_id[it] = uint32_t(it);
 }
@@ -971,10 +1007,11 @@ struct PassGeom {
     const uint32_t* sub_start; const uint32_t* sub_cnt;                       // other sub-tiles
     const uint32_t* cand;         // candidate other sub-tiles
     const uint32_t* it_tile; const uint64_t* it_cb; const uint64_t* it_ce;
+    const uint32_t* it_slice;     // slice of the piece, number of slices << 16
     const uint32_t* item_off;     // [owner tiles + 1] item ranges per owner tile
     const uint32_t* item_order;   // items in the order they are dealt (largest first)
     int64_t n_items;
-    uint32_t* queue_ctr;          // [kXcd] work counters
+    uint32_t* queue_ctr;          // [kXcd] work counters, kQueueStride words apart
     double L[3];
     uint64_t* counters;
     // pair export (the PAIRS variants of the passes only): every visited pair
@@ -1041,38 +1078,31 @@ __device__ __forceinline__ double pair_d2(double ax, double ay, double az, doubl
 // next item from an atomic counter.
 constexpr int kXcdChunk = 32;
 
-template <int W = 1>
-__device__ __forceinline__ bool item_next(uint32_t* queue_ctr, int64_t n_items, int64_t* it)
-{
-    const int x = blockIdx.x % kXcd;
-    if constexpr (W == 1) {
-        __shared__ int64_t s_it;
-        if (threadIdx.x == 0) {
-            const int64_t k = int64_t(atomicAdd(&queue_ctr[x], 1u));
-            s_it = (k / kXcdChunk) * (int64_t(kXcd) * kXcdChunk) + int64_t(x) * kXcdChunk + (k % kXcdChunk);
-        }
-        __syncthreads();
-        *it = s_it;
-        __syncthreads();
-    } else {
-        int64_t v = 0;
-        if (lane_id() == 0) {
-            const int64_t k = int64_t(atomicAdd(&queue_ctr[x], 1u));
-            v = (k / kXcdChunk) * (int64_t(kXcd) * kXcdChunk) + int64_t(x) * kXcdChunk + (k % kXcdChunk);
-        }
-        *it = __shfl(v, 0);
+// Atomics on one 128-byte line complete about one every 12 ns wherever they come
+// from, so the eight counters sit on lines of their own (kQueueStride words
+// apart): side by side, the 108 508 items of a galaxy's DM pass (1M + 4M) kept
+// it at 1.29 ms with every candidate test and pair evaluation taken out.  (Asking
+// for the next item's number ahead of time does not pay: the numbers that busy
+// waves hold at the end keep their items from idle ones, 2.60 against 2.49 ms.)
+constexpr int kQueueStride = 64;
+constexpr int kQueueWords = (2 * kXcd + 1) * kQueueStride;   // gas queues, DM queues, one more counter
+
+struct ItemQueue {
+    uint32_t* ctr;
+    int64_t n_items;
+    __device__ __forceinline__ ItemQueue(uint32_t* queue_ctr, int64_t n)
+        : ctr(queue_ctr + (blockIdx.x % kXcd) * kQueueStride), n_items(n) {}
+    // The wave's next item (wave-uniform); false when the queue is drained.
+    __device__ __forceinline__ bool take(int64_t* it)
+    {
+        uint32_t k = 0u;
+        if (lane_id() == 0) k = atomicAdd(ctr, 1u);
+        k = uint32_t(__builtin_amdgcn_readfirstlane(int(k)));
+        *it = int64_t(k / kXcdChunk) * (int64_t(kXcd) * kXcdChunk) + int64_t(blockIdx.x % kXcd) * kXcdChunk +
+              int64_t(k % kXcdChunk);
+        return *it < n_items;
     }
-    return *it < n_items;
-}
-
-
-// Bits [b, e) of a wave-uniform mask, tested for any set bit (0 <= b <= e <= 64).
-__device__ __forceinline__ bool any_bits(uint64_t m, int b, int e)
-{
-    const int n = e - b;
-    const uint64_t w = n >= 64 ? ~0ull : (1ull << n) - 1ull;
-    return n > 0 && ((m >> b) & w) != 0ull;
-}
+};
 
 // Index of the r-th set bit (r < popcount(m)).
 __device__ __forceinline__ int select_bit(uint64_t m, int r)
@@ -1094,7 +1124,7 @@ struct TestLds {
     uint32_t dsh[64];             // periodic image of each chunk sub-tile: shift / L per axis, a signed byte each
     int dbase[64];                // first sorted index of each chunk sub-tile; bit 31: every pair of the
                                   // sub-tile is at its tile-level image (clean)
-    int dpre[64], dincl[64];      // exclusive / inclusive slot prefix over the reached sub-tiles
+    uint32_t dpre[64];            // exclusive (low half) and inclusive slot prefix over the reached sub-tiles
     int sj[64];                   // slot -> chunk sub-tile (prefix-max scratch)
     double px[64], py[64], pz[64], ph[64];   // slot particles: shifted position and h
     uint32_t pq[64];              // slot -> sorted index of the other particle; bit 31: the slot's sub-tile is clean
@@ -1109,6 +1139,7 @@ struct PairTest {
     uint64_t c0, ce;              // next chunk start, end of the item's candidate list
     uint64_t actA, actB;          // chunk sub-tiles reached by some owner of lanes 0-31 / 32-63
     int total, Ps;                // slots of the chunk, start of the next group
+    int slice, nslice;            // this item takes groups slice, slice + nslice, ... of every chunk
 };
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -1164,12 +1195,13 @@ __device__ __forceinline__ void half_operands(const float c[6], float out[2][3])
 }
 
 __device__ __forceinline__ void test_begin(PairTest& T, bool ov, float fx, float fy, float fz, float fh, uint64_t cb,
-                                           uint64_t ce)
+                                           uint64_t ce, int slice = 0, int nslice = 1)
 {
     T.ov = ov; T.fx = fx; T.fy = fy; T.fz = fz; T.fh = fh;
     T.c0 = cb; T.ce = ce;
     T.actA = T.actB = 0ull;
     T.total = 0; T.Ps = 0;
+    T.slice = slice; T.nslice = nslice;
 }
 
 // Next chunk of up to 64 candidate sub-tiles: descriptors to LDS (lane = sub-tile),
@@ -1250,17 +1282,19 @@ __device__ __forceinline__ void test_chunk(PairTest& T, TestLds& S, const PassGe
     const bool act = ((actA | actB) >> lane) & 1ull;
     const int ca = act ? cnt : 0;
     const int incl = wave_incl_scan(ca);
-    S.dpre[lane] = incl - ca;
-    S.dincl[lane] = incl;
-    T.total = __shfl(incl, 63);
-    T.Ps = 0;
+    S.dpre[lane] = uint32_t(incl - ca) | (uint32_t(incl) << 16);
+    T.total = __builtin_amdgcn_readlane(incl, 63);
+    T.Ps = 64 * T.slice;
 }
 
 // Test the next group of slots against the tile's owners.  Returns the group's
 // hit count (wave-uniform), -1 when the item's candidates are exhausted.
-template <int W>
+// stage(s, q, write) is called twice per lane that holds a slot s (particle q):
+// first to load what the pass needs of the particle, then, after the test has
+// hidden the loads, to put it into the slot's row in LDS.
+template <int W, typename Stage>
 __device__ __forceinline__ int test_next(PairTest& T, TestLds& S, const PassGeom& G, const double* A,
-                                         const double cen[3], const float Lf[3])
+                                         const double cen[3], const float Lf[3], Stage& stage)
 {
     const int lane = lane_id();
     while (T.Ps >= T.total) {
@@ -1271,10 +1305,10 @@ __device__ __forceinline__ int test_next(PairTest& T, TestLds& S, const PassGeom
     // reached sub-tiles whose slots overlap [Ps, Ps + 64): a contiguous run, the first of which
     // may have begun in the previous group and the last may go on in the next (full groups)
     const bool act = ((T.actA | T.actB) >> lane) & 1ull;
-    const int pre = S.dpre[lane], inc = S.dincl[lane];
+    const int pre = int(S.dpre[lane] & 0xffffu), inc = int(S.dpre[lane] >> 16);
     const bool mem = act && inc > T.Ps && pre < T.Ps + 64;
     const uint64_t gm = __ballot(mem);
-    const int end = min(S.dincl[63 - __clzll(gm)], T.Ps + 64);
+    const int end = min(__builtin_amdgcn_readlane(inc, 63 - __clzll(gm)), T.Ps + 64);
     const int ns = end - T.Ps;
     const bool tileA = (T.actA & gm) != 0ull, tileB = (T.actB & gm) != 0ull;
     S.sj[lane] = 0;
@@ -1290,12 +1324,13 @@ __device__ __forceinline__ int test_next(PairTest& T, TestLds& S, const PassGeom
     float c[6] = {0.f, 0.f, 0.f, 0.f, 1.f, __builtin_inff()};
     if (sv) {
         const uint32_t db = uint32_t(S.dbase[j]);
-        const int64_t q = int64_t(db & 0x7fffffffu) + (s - (S.dpre[j] - T.Ps));
+        const int64_t q = int64_t(db & 0x7fffffffu) + (s - (int(S.dpre[j] & 0xffffu) - T.Ps));
         cl = int(db >> 31);
         const uint32_t pk = S.dsh[j];
         const double X = G.tx[q] + double(int8_t(pk)) * G.L[0], Y = G.ty[q] + double(int8_t(pk >> 8)) * G.L[1],
                      Z = G.tz[q] + double(int8_t(pk >> 16)) * G.L[2];
         const double Hh = G.th[q];
+        stage.load(q);
         S.px[s] = X; S.py[s] = Y; S.pz[s] = Z; S.ph[s] = Hh;
         S.pq[s] = uint32_t(q) | (cl ? 0x80000000u : 0u);
         const float qx = float(X - cen[0]), qy = float(Y - cen[1]), qz = float(Z - cen[2]), qh = float(Hh);
@@ -1354,13 +1389,14 @@ __device__ __forceinline__ int test_next(PairTest& T, TestLds& S, const PassGeom
             if (T.ov && hit) m |= 1ull << t;
         }
     }
+    if (sv) stage.store(s);
     S.mask[lane] = m;
     const int tot = __popcll(m);
     const int incl = wave_incl_scan(tot);
     S.offs[lane] = incl - tot;
-    const int H = __shfl(incl, 63);
+    const int H = __builtin_amdgcn_readlane(incl, 63);
     if (lane == 63) S.offs[64] = H;
-    T.Ps = end;
+    T.Ps += 64 * T.nslice;
     stage_sync<W>();
     return H;
 }
@@ -1429,6 +1465,92 @@ __device__ __forceinline__ int run_first(int lane, int key, bool* last)
     return int(wave_incl_umax(first ? uint32_t(lane + 1) : 0u)) - 1;
 }
 
+// Walks a group's H hits.  acc (the lane's running partial) provides add(term),
+// flush(owner) (adds the partial to the owner's row and clears it) and
+// scan(lane, first lane of the run) (the segmented scan of open partials);
+// eval(owner, slot, live, round) gives a hit's term on every lane (a lane without
+// a hit gets owner 0, slot 0 and live = false and returns the zero term).
+template <typename Acc, typename Eval>
+__device__ __forceinline__ void walk_group(TestLds& S, int lane, int H, Acc& acc, Eval& eval)
+{
+    const int R = (H + 63) >> 6;
+    HitWalk w;
+    walk_begin(S, lane, H, R, w);
+    bool open = false;
+    for (int r = 0; r < R; ++r) {
+        const bool live = r < w.n;
+        const int o = live ? w.o : 0, sl = live ? int(__builtin_ctzll(w.rem)) : 0;
+        if (live) w.rem &= w.rem - 1ull;
+        const bool done = live && w.rem == 0ull;
+        if (done) {
+            w.o = next_owner(w.own, w.o);
+            w.rem = w.o < 64 ? S.mask[w.o] : 0ull;
+        }
+        acc.add(eval(o, sl, live, r));
+        if (live) open = !done;
+        if (done) acc.flush(o);      // the owner's last hit of the group
+    }
+    // open partials: lanes whose range ended inside an owner's hits
+    if (__ballot(open) != 0ull) {
+        bool last;
+        const int lo = run_first(lane, open ? w.o : 64 + lane, &last);
+        acc.scan(lane, lo);
+        if (open && last) acc.flush(w.o);
+        acc.clear();
+    }
+}
+
+// What a pass reads of a pair's other particle, one row per slot of the group
+// in LDS, loaded once per group (about 5.5 rounds of 64 pairs) by consecutive
+// lanes.  Read per pair from memory the records cost 192 of a round's 448 16-byte
+// addresses, and the vector L1, which takes one per clock, was busy 94 % of the
+// DM pass (galaxy of 1M + 4M).  The rows take the binary32 passes from 10 to
+// 13 KB per wave, so three waves share a SIMD instead of four; the L1 is then busy
+// 63 %, the vector units 72 %, and the passes take 2.46 and 2.14 ms instead of 2.50
+// and 2.17 (2.68 for the DM pass with four waves and records read per pair). 
+template <typename Real>
+struct SlotDm {                   // DM, in the gas pass
+    double vx[64], vy[64], vz[64];
+    Real m[64];
+};
+struct NoRows {};
+struct alignas(16) MlpRows { unsigned char b[kMlpInferBytes]; };
+template <typename Real>
+struct StageDm {
+    const DmRec<Real>* rec;
+    SlotDm<Real>& R;
+    DmRec<Real> r;
+    __device__ __forceinline__ StageDm(const DmRec<Real>* rec_, SlotDm<Real>& R_) : rec(rec_), R(R_) {}
+    __device__ __forceinline__ void load(int64_t q) { r = rec[q]; }
+    __device__ __forceinline__ void store(int s) { R.vx[s] = r.vx; R.vy[s] = r.vy; R.vz[s] = r.vz; R.m[s] = r.m; }
+};
+template <typename Real>
+struct SlotGas {                  // gas, in the DM pass
+    double Vx[64], Vy[64], Vz[64];
+    Real vs[64], K[64], crit[64];
+    uint32_t pa[64], pb[64];      // the gas index's part of the pair's Philox block (PhiloxPair)
+};
+template <typename Real, bool RB>
+struct StageGas {
+    const GasRec<Real>* rec;
+    SlotGas<Real>& R;
+    const PhiloxPair& ph;
+    GasRec<Real> r;
+    __device__ __forceinline__ StageGas(const GasRec<Real>* rec_, SlotGas<Real>& R_, const PhiloxPair& ph_)
+        : rec(rec_), R(R_), ph(ph_) {}
+    __device__ __forceinline__ void load(int64_t q) { r = rec[q]; }
+    __device__ __forceinline__ void store(int s)
+    {
+        R.Vx[s] = r.Vx; R.Vy[s] = r.Vy; R.Vz[s] = r.Vz;
+        R.vs[s] = r.vs; R.K[s] = r.K; R.crit[s] = r.crit;
+        if constexpr (!RB) {
+            uint32_t a, b;
+            ph.other(r.perm, &a, &b);
+            R.pa[s] = a; R.pb[s] = b;
+        }
+    }
+};
+
 // ---------------------------------------------------------------------------
 // Gas (mean-field) pass: owners = active gas, others = DM.
 // Box of global work item `it` in a batched pass: box_items[b] is the first
@@ -1469,6 +1591,40 @@ struct GasPassArgs {
 // (sum M g A w, sum M g (w^2 A - r B)); the closure keeps the DM moments
 // (sum M g w, sum M g |w|^2, sum M g).
 template <int RM> constexpr int gas_sums() { return RM == kRatesClosure ? 5 : 4; }
+
+// The lane's partial sums of the gas pass; rows: the item's per-owner sums in LDS.
+template <int NS>
+struct GasAcc {
+    struct Term { double v[NS]; };
+    double p[NS];
+    double* rows;
+    __device__ __forceinline__ explicit GasAcc(double* rows_) : rows(rows_) { clear(); }
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int k = 0; k < NS; ++k) p[k] = 0.0;
+    }
+    __device__ __forceinline__ void add(const Term& t)
+    {
+#pragma unroll
+        for (int k = 0; k < NS; ++k) p[k] += t.v[k];
+    }
+    __device__ __forceinline__ void flush(int o)
+    {
+        double* q = rows + NS * o;
+#pragma unroll
+        for (int k = 0; k < NS; ++k) q[k] += p[k];
+        clear();
+    }
+    __device__ __forceinline__ void scan(int lane, int lo)
+    {
+        seg_scan_up(lane, lo, [&](auto ctl, auto rws, bool take) {
+            constexpr int C = decltype(ctl)::value, RW = decltype(rws)::value;
+#pragma unroll
+            for (int k = 0; k < NS; ++k) p[k] = dpp_take_add<C, RW>(p[k], take);
+        });
+    }
+};
 
 // Per-gas Maxwellian closure (Appendix F rates applied per gas particle): the
 // DM around the gas particle form one Maxwellian population of kernel-weighted
@@ -1540,10 +1696,153 @@ __device__ __forceinline__ void gas_write_out(const GasPassArgs& a, uint32_t o, 
     gas_store<N, RM>(w, o, acc);
 }
 
-// Occupancy: the binary32 passes fit 128 VGPRs and < 10 KB of LDS per
-// one-wave block, so four waves share each SIMD (16 blocks per CU).
+// Evaluation of one hit of the gas pass (walk_group).  Terms and the lane's
+// partial sums are binary64: the overlap near contact is far below the binary32
+// range, and sums of terms that cancel keep their accuracy.  main() is one
+// straight line in binary32; finish() mends the rare lanes its formulas do not
+// hold for and zeroes the lanes without a pair.
+template <typename Real, int N, bool EXACT_G, int RM, bool PAIRS>
+struct GasEval {
+    static constexpr int NS = gas_sums<RM>();
+    const GasPassArgs& a; const GasPassArgs& a0; const PassGeom& G;
+    TestLds& S; SlotDm<Real>& SR;
+    const double* o_x; const double* o_y; const double* o_z; const double* o_h;
+    const double* o_Vx; const double* o_Vy; const double* o_Vz;
+    const OwnRate<Real>* o_rate;
+    const Real* s_gx; const Real* s_gw;
+    const unsigned char* s_mlp;
+    int64_t t;
+    int H;
+    uint32_t& npairs;
+    struct Value { bool hit; Real g, x, FA, FB; double g64; OwnRate<Real> orr; Real wx, wy, wz, w2; };
+
+    __device__ __forceinline__ GasEval(const GasPassArgs& a_, const GasPassArgs& a0_, const PassGeom& G_, TestLds& S_,
+                                       SlotDm<Real>& SR_, const double* ox, const double* oy, const double* oz,
+                                       const double* oh, const double* oVx, const double* oVy, const double* oVz,
+                                       const OwnRate<Real>* rate, const Real* gx, const Real* gw,
+                                       const unsigned char* mlp, int64_t t_, int H_, uint32_t& np)
+        : a(a_), a0(a0_), G(G_), S(S_), SR(SR_), o_x(ox), o_y(oy), o_z(oz), o_h(oh), o_Vx(oVx), o_Vy(oVy), o_Vz(oVz),
+          o_rate(rate), s_gx(gx), s_gw(gw), s_mlp(mlp), t(t_), H(H_), npairs(np) {}
+
+    __device__ __forceinline__ double dist2(int o, int sl) const
+    {
+        return pair_d2(o_x[o], o_y[o], o_z[o], S.px[sl], S.py[sl], S.pz[sl], (S.pq[sl] >> 31) != 0u, G.L);
+    }
+
+    __device__ __forceinline__ Value main(int o, int sl, bool live, int r)
+    {
+        Value v;
+        // the owner's rate record, issued before the distance work that hides its latency
+        if constexpr (RM != kRatesClosure) v.orr = o_rate[o];
+        const double qh = S.ph[sl], oh = o_h[o], hs = oh + qh;
+        const double d2p = dist2(o, sl);
+        v.hit = live && d2p < hs * hs;
+        if constexpr (PAIRS) pair_export(G, v.hit, G.own[t * kTile + o], S.pq[sl] & 0x7fffffffu);
+        npairs += v.hit ? 1u : 0u;
+        // lanes without a pair run along at distance 0 (every table index stays in range) and drop out in
+        // finish(); the binary64 overlap and the quadrature, whole loops, leave them out instead
+        const double d2 = masked(d2p, bits(v.hit));
+        v.g = 0; v.g64 = 0.0;
+        // the rates are formed between the overlap's loads and their use
+        Overlap32 ov;
+        if constexpr (EXACT_G) {
+            if (v.hit) v.g64 = double(overlap_g_exact<Real>(sqrt_real(Real(d2)), Real(qh), Real(oh)));
+        } else {
+            ov.begin(a.gtab, d2, qh, oh);
+        }
+        if constexpr (RM != kRatesClosure) {
+            v.wx = Real(SR.vx[sl] - o_Vx[o]); v.wy = Real(SR.vy[sl] - o_Vy[o]); v.wz = Real(SR.vz[sl] - o_Vz[o]);
+            v.w2 = v.wx * v.wx + v.wy * v.wy + v.wz * v.wz;
+            v.x = v.w2 * v.orr.i2;                 // infinite (or NaN) for cold gas
+            v.FA = v.FB = 0;
+            if constexpr (RM == kRatesExact && sizeof(Real) == 4) {
+                rate_1f1_large<N, Real>(v.x, &v.FA, &v.FB);
+            } else if constexpr (RM == kRatesMlp) {
+                // the network over the whole wave
+                const bool cold = isinf(v.orr.i2);
+                const float u = cold ? 0.f : sqrt_real(2.f * v.x);
+                const bool net = v.hit && !cold && u <= kMlpUMax;
+                float yA = 0.f, yB = 0.f;
+                if (__ballot(net) != 0ull) {
+                    // an opaque zero offset keeps the weight reads inside the loop
+                    // (hoisted, they would pin ~90 registers for the kernel's lifetime)
+                    int zoff = 0;
+                    asm volatile("" : "+v"(zoff));
+                    const MlpBlob* Wl = reinterpret_cast<const MlpBlob*>(s_mlp + zoff);
+                    // the round's pairs occupy lanes 0 .. nlive-1 (the lanes whose range
+                    // reaches round r): evaluate only the 16-column blocks that hold some
+                    const int R = (H + 63) >> 6, nlive = min((H - r + R - 1) / R, 64);
+                    if (nlive > 32)
+                        mlp_forward64<4, 4>(Wl, mlp_input(u), a0.mlp_nidx, &yA, &yB);
+                    else if (nlive > 16)
+                        mlp_forward64<2, 2>(Wl, mlp_input(u), a0.mlp_nidx, &yA, &yB);
+                    else
+                        mlp_forward64<1, 1>(Wl, mlp_input(u), a0.mlp_nidx, &yA, &yB);
+                }
+                if (net) {
+                    float bA, bB;
+                    mlp_base<N>(u * u, a0.mlp_c0A, a0.mlp_c1A, a0.mlp_c0B, a0.mlp_c1B, &bA, &bB);
+                    v.FA = a0.mlp_kA * bA * __expf(yA);
+                    v.FB = a0.mlp_kB * bB * __expf(yB);
+                } else if (v.hit && !cold) {
+                    quad(u, v);
+                }
+            } else if (v.hit && !isinf(v.orr.i2)) {
+                if constexpr (RM == kRatesQuad) quad(sqrt_real(Real(2) * v.x), v);
+                else rate_1f1<N, Real>(v.x, &v.FA, &v.FB);
+            }
+        }
+        if constexpr (!EXACT_G) v.g = ov.value();
+        return v;
+    }
+
+    __device__ __forceinline__ void quad(Real u, Value& v)
+    {
+        rate_quad<N, Real>(u, s_gx, s_gw, a0.gl_k, Real(a0.inv_alpha), Real(a0.gl_hw), Real(a0.gl_bmin), &v.FA, &v.FB);
+    }
+
+    __device__ __forceinline__ typename GasAcc<NS>::Term operator()(int o, int sl, bool live, int r)
+    {
+        Value v = main(o, sl, live, r);
+        return finish(v, o, sl);
+    }
+
+    __device__ __forceinline__ typename GasAcc<NS>::Term finish(Value& v, int o, int sl)
+    {
+        typename GasAcc<NS>::Term c;
+        double gg = EXACT_G ? v.g64 : double(v.g);
+        if constexpr (!EXACT_G) {
+            // so close to contact that the binary32 value nears the bottom of its range
+            if (v.hit && !(v.g >= 1e-30f)) gg = overlap_g_table(a.gtab, dist2(o, sl), S.ph[sl], o_h[o]);
+        }
+        const double mg = double(SR.m[sl]) * gg;
+        if constexpr (RM == kRatesClosure) {
+            // the closure's DM moments: kernel-weighted mass, momentum and |w|^2
+            const double wx = SR.vx[sl] - o_Vx[o], wy = SR.vy[sl] - o_Vy[o], wz = SR.vz[sl] - o_Vz[o];
+            c.v[0] = mg * wx; c.v[1] = mg * wy; c.v[2] = mg * wz;
+            c.v[3] = mg * (wx * wx + wy * wy + wz * wz);
+            c.v[NS - 1] = mg;
+        } else {
+            if constexpr (RM == kRatesExact && sizeof(Real) == 4) {
+                if (v.hit && v.x < Real(1)) rate_1f1_small<N, Real>(v.x, &v.FA, &v.FB);
+            }
+            Real Ar = v.orr.a * v.FA, Br = v.orr.b * v.FB;
+            if (isinf(v.orr.i2)) {       // cold gas: A = w^{n+1}, B = w^{n+3}
+                Ar = pow_np1<N>(sqrt_real(v.w2));
+                Br = Ar * v.w2;
+            }
+            const double mgA = mg * double(Ar);
+            c.v[0] = mgA * double(v.wx); c.v[1] = mgA * double(v.wy); c.v[2] = mgA * double(v.wz);
+            c.v[3] = mg * double(v.w2 * Ar - v.orr.r * Br);
+        }
+#pragma unroll
+        for (int k = 0; k < NS; ++k) c.v[k] = masked(c.v[k], bits(v.hit));
+        return c;
+    }
+};
+
 template <typename Real, int N, bool EXACT_G, int RM, bool BATCH = false, bool PAIRS = false>
-__global__ __launch_bounds__(RM == kRatesMlp ? 64 * kMlpPassWaves : 64, RM == kRatesMlp ? 2 : (sizeof(Real) == 4 ? 4 : (RM == kRatesExact ? 1 : 2)))
+__global__ __launch_bounds__(RM == kRatesMlp ? 64 * kMlpPassWaves : 64, RM == kRatesMlp ? 2 : (sizeof(Real) == 4 ? 3 : 2))
 void k_pass_gas(
     GasPassArgs a0, const GasPassArgs* __restrict__ boxes, const int64_t* __restrict__ box_items, int nbox)
 {
@@ -1558,11 +1857,14 @@ void k_pass_gas(
     __shared__ double o_x_[W][64], o_y_[W][64], o_z_[W][64], o_h_[W][64], o_Vx_[W][64], o_Vy_[W][64], o_Vz_[W][64];
     constexpr int NS = gas_sums<RM>();
     __shared__ double osum_[W][64 * NS];
-    __shared__ __align__(16) unsigned char s_mlp[RM == kRatesMlp ? kMlpInferBytes : 16];
+    __shared__ SlotDm<Real> SR_[W];
+    __shared__ std::conditional_t<RM == kRatesMlp, MlpRows, NoRows> s_w;
+    unsigned char* s_mlp = reinterpret_cast<unsigned char*>(&s_w);
     const int wv = W == 1 ? 0 : int(threadIdx.x) >> 6;
     TestLds& S = S_[wv];
     double* o_x = o_x_[wv]; double* o_y = o_y_[wv]; double* o_z = o_z_[wv]; double* o_h = o_h_[wv];
     double* o_Vx = o_Vx_[wv]; double* o_Vy = o_Vy_[wv]; double* o_Vz = o_Vz_[wv];
+    SlotDm<Real>& SR = SR_[wv];
     const int lane = lane_id();
     if constexpr (RM == kRatesQuad || RM == kRatesMlp) {
         if (int(threadIdx.x) < a0.gl_k) {
@@ -1576,20 +1878,23 @@ void k_pass_gas(
         for (int k = int(threadIdx.x); k < int(kMlpInferBytes / 16); k += 64 * W) dst[k] = src[k];
         __syncthreads();
     }
-    const Real inv_alpha = Real(a0.inv_alpha), q_hw = Real(a0.gl_hw), q_bmin = Real(a0.gl_bmin);
     int64_t it;
-    uint64_t npairs = 0;
+    uint32_t npairs = 0;          // per lane and box: a lane visits far fewer than 2^32 pairs of one call
     int cur_b = 0;
-    while (item_next<W>(a0.g.queue_ctr, a0.g.n_items, &it)) {
+    auto flush = [&](uint64_t* counters) {
+        uint64_t n = npairs;
+        for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d);
+        if (lane == 0 && n) atomicAdd((unsigned long long*)&counters[0], (unsigned long long)n);
+        npairs = 0;
+    };
+    ItemQueue queue(a0.g.queue_ctr, a0.g.n_items);
+    while (queue.take(&it)) {
         int b = 0;
         if constexpr (BATCH) {
             b = box_of_item(box_items, nbox, it);
             it -= box_items[b];
             if (b != cur_b) {   // counters belong to the box: flush when the box changes
-                for (int d = 32; d >= 1; d >>= 1) npairs += __shfl_xor(npairs, d);
-                if (lane == 0 && npairs)
-                    atomicAdd((unsigned long long*)&boxes[cur_b].g.counters[0], (unsigned long long)npairs);
-                npairs = 0;
+                flush(boxes[cur_b].g.counters);
                 cur_b = b;
             }
         }
@@ -1608,6 +1913,7 @@ void k_pass_gas(
         stage_sync<W>();
         o_x[lane] = mx; o_y[lane] = my; o_z[lane] = mz; o_h[lane] = mh;
         o_Vx[lane] = ov ? a.Vx[sp] : 0.0; o_Vy[lane] = ov ? a.Vy[sp] : 0.0; o_Vz[lane] = ov ? a.Vz[sp] : 0.0;
+        StageDm<Real> stage(reinterpret_cast<const DmRec<Real>*>(a.drec), SR);
         double A[6];
         for (int k = 0; k < 6; ++k) A[k] = G.obox[6 * t + k];
         const double cen[3] = {0.5 * (A[0] + A[3]), 0.5 * (A[1] + A[4]), 0.5 * (A[2] + A[5])};
@@ -1617,213 +1923,29 @@ void k_pass_gas(
         for (int k = 0; k < NS; ++k) osum[k] = 0.0;
         PairTest T;
         test_begin(T, ov, fx, fy, fz, fh, cb, ce);
+        GasAcc<NS> ga(osum_[wv]);
         for (;;) {
-            const int H = test_next<W>(T, S, G, A, cen, Lf);
+            const int H = test_next<W>(T, S, G, A, cen, Lf, stage);
             if (H < 0) break;
             if (H == 0) continue;
-            const int R = (H + 63) >> 6;
-            HitWalk hw;
-            walk_begin(S, lane, H, R, hw);
-            // per-pair terms and the lane's partial sums in binary64 (the overlap near contact is
-            // far below the binary32 range; sums of terms that cancel keep their accuracy)
-            double p0 = 0.0, p1 = 0.0, p2 = 0.0, p3 = 0.0, p4 = 0.0;
-            bool open = false;
-            for (int r = 0; r < R; ++r) {
-                const bool live = r < hw.n;
-                const int o = live ? hw.o : 0;
-                const int sl = live ? int(__builtin_ctzll(hw.rem)) : 0;
-                double c0 = 0, c1 = 0, c2 = 0, c3 = 0, c4 = 0;
-                if constexpr (RM == kRatesClosure) {
-                    // the closure's DM moments: kernel-weighted mass, momentum and |w|^2
-                    bool hit = false;
-                    uint32_t e_o = 0u, e_q = 0u;
-                    if (live) {
-                        const uint32_t pqv = S.pq[sl];
-                        const int64_t q = int64_t(pqv & 0x7fffffffu);
-                        const DmRec<Real> r = reinterpret_cast<const DmRec<Real>*>(a.drec)[q];
-                        const double qx = S.px[sl], qy = S.py[sl], qz = S.pz[sl], qh = S.ph[sl];
-                        const double d2 = pair_d2(o_x[o], o_y[o], o_z[o], qx, qy, qz, (pqv >> 31) != 0u, G.L);
-                        const double hs = o_h[o] + qh;
-                        if constexpr (PAIRS) {
-                            hit = d2 < hs * hs;
-                            e_o = G.own[t * kTile + o];
-                            e_q = uint32_t(q);
-                        }
-                        if (d2 < hs * hs) {
-                            npairs++;
-                            const double gg = EXACT_G ? double(overlap_g_exact<Real>(sqrt_real(Real(d2)), Real(qh), Real(o_h[o])))
-                                                      : overlap_g_gas(a.gtab, d2, qh, o_h[o]);
-                            const double wx = r.vx - o_Vx[o], wy = r.vy - o_Vy[o], wz = r.vz - o_Vz[o];
-                            const double mg = double(r.m) * gg;
-                            c0 = mg * wx; c1 = mg * wy; c2 = mg * wz;
-                            c3 = mg * (wx * wx + wy * wy + wz * wz);
-                            c4 = mg;
-                        }
-                    }
-                    if constexpr (PAIRS) pair_export(G, hit, e_o, e_q);
-                } else if constexpr (RM != kRatesMlp) {
-                    bool hit = false;
-                    uint32_t e_o = 0u, e_q = 0u;
-                    if (live) {
-                        const uint32_t pqv = S.pq[sl];
-                        const int64_t q = int64_t(pqv & 0x7fffffffu);
-                        // the pair's records, issued before the distance work that hides their latency
-                        const DmRec<Real> r = reinterpret_cast<const DmRec<Real>*>(a.drec)[q];
-                        const OwnRate<Real> orr = orate[o];
-                        const double qx = S.px[sl], qy = S.py[sl], qz = S.pz[sl], qh = S.ph[sl];
-                        const double d2 = pair_d2(o_x[o], o_y[o], o_z[o], qx, qy, qz, (pqv >> 31) != 0u, G.L);
-                        const double hs = o_h[o] + qh;
-                        if constexpr (PAIRS) {
-                            hit = d2 < hs * hs;
-                            e_o = G.own[t * kTile + o];
-                            e_q = uint32_t(q);
-                        }
-                        if (d2 < hs * hs) {
-                            npairs++;
-                            const double gg = EXACT_G ? double(overlap_g_exact<Real>(sqrt_real(Real(d2)), Real(qh), Real(o_h[o])))
-                                                      : overlap_g_gas(a.gtab, d2, qh, o_h[o]);
-                            const Real wx = Real(r.vx - o_Vx[o]), wy = Real(r.vy - o_Vy[o]), wz = Real(r.vz - o_Vz[o]);
-                            const Real w2 = wx * wx + wy * wy + wz * wz;
-                            Real FA, FB, Ar, Br;
-                            const Real i2 = orr.i2;
-                            if (isinf(i2)) {  // cold gas: A = w^{n+1}, B = w^{n+3}
-                                const Real wn = sqrt_real(w2);
-                                Ar = pow_np1<N>(wn);
-                                Br = Ar * w2;
-                            } else {
-                                if constexpr (RM == kRatesQuad)
-                                    rate_quad<N, Real>(sqrt_real(Real(2) * w2 * i2), s_gx, s_gw, a0.gl_k, inv_alpha,
-                                                       q_hw, q_bmin, &FA, &FB);
-                                else
-                                    rate_1f1<N, Real>(w2 * i2, &FA, &FB);
-                                Ar = orr.a * FA;
-                                Br = orr.b * FB;
-                            }
-                            const double mg = double(r.m) * gg;
-                            const double mgA = mg * double(Ar);
-                            c0 = mgA * double(wx); c1 = mgA * double(wy); c2 = mgA * double(wz);
-                            c3 = mg * double(w2 * Ar - orr.r * Br);
-                        }
-                    }
-                    if constexpr (PAIRS) pair_export(G, hit, e_o, e_q);
-                } else {
-                    // pair geometry per lane, then the network over the whole wave
-                    bool live2 = false;
-                    int64_t q = 0;
-                    double gg = 0.0;
-                    float wx = 0.f, wy = 0.f, wz = 0.f, w2 = 0.f, i2 = 0.f, u = 0.f, mq = 0.f;
-                    OwnRate<float> orr{0.f, 0.f, 0.f, 0.f};
-                    if (live) {
-                        const uint32_t pqv = S.pq[sl];
-                        q = int64_t(pqv & 0x7fffffffu);
-                        const double qx = S.px[sl], qy = S.py[sl], qz = S.pz[sl], qh = S.ph[sl];
-                        const double d2 = pair_d2(o_x[o], o_y[o], o_z[o], qx, qy, qz, (pqv >> 31) != 0u, G.L);
-                        const double hs = o_h[o] + qh;
-                        if (d2 < hs * hs) {
-                            live2 = true;
-                            npairs++;
-                            gg = overlap_g_gas(a.gtab, d2, qh, o_h[o]);
-                            const DmRec<float> r = reinterpret_cast<const DmRec<float>*>(a.drec)[q];
-                            wx = float(r.vx - o_Vx[o]);
-                            wy = float(r.vy - o_Vy[o]);
-                            wz = float(r.vz - o_Vz[o]);
-                            mq = r.m;
-                            w2 = wx * wx + wy * wy + wz * wz;
-                            orr = reinterpret_cast<const OwnRate<float>*>(orate)[o];
-                            i2 = orr.i2;
-                            u = isinf(i2) ? 0.f : sqrt_real(2.f * w2 * i2);
-                        }
-                    }
-                    const bool net = live2 && !isinf(i2) && u <= kMlpUMax;
-                    float yA = 0.f, yB = 0.f;
-                    if (__ballot(net) != 0ull) {
-                        // an opaque zero offset keeps the weight reads inside the loop
-                        // (hoisted, they would pin ~90 registers for the kernel's lifetime)
-                        int zoff = 0;
-                        asm volatile("" : "+v"(zoff));
-                        const MlpBlob* Wl = reinterpret_cast<const MlpBlob*>(s_mlp + zoff);
-                        // the round's pairs occupy lanes 0 .. nlive-1 (the lanes whose range
-                        // reaches round r): evaluate only the 16-column blocks that hold some
-                        const int nlive = min((H - r + R - 1) / R, 64);
-                        if (nlive > 32)
-                            mlp_forward64<4, 4>(Wl, mlp_input(u), a0.mlp_nidx, &yA, &yB);
-                        else if (nlive > 16)
-                            mlp_forward64<2, 2>(Wl, mlp_input(u), a0.mlp_nidx, &yA, &yB);
-                        else
-                            mlp_forward64<1, 1>(Wl, mlp_input(u), a0.mlp_nidx, &yA, &yB);
-                    }
-                    if (live2) {
-                        float Ar, Br;
-                        if (isinf(i2)) {
-                            Ar = pow_np1<N>(sqrt_real(w2));
-                            Br = Ar * w2;
-                        } else {
-                            float FA, FB;
-                            if (net) {
-                                float bA, bB;
-                                mlp_base<N>(u * u, a0.mlp_c0A, a0.mlp_c1A, a0.mlp_c0B, a0.mlp_c1B, &bA, &bB);
-                                FA = a0.mlp_kA * bA * __expf(yA);
-                                FB = a0.mlp_kB * bB * __expf(yB);
-                            } else {
-                                rate_quad<N, float>(u, s_gx, s_gw, a0.gl_k, inv_alpha, q_hw, q_bmin, &FA, &FB);
-                            }
-                            Ar = orr.a * FA;
-                            Br = orr.b * FB;
-                        }
-                        const double mg = double(mq) * gg;
-                        const double mgA = mg * double(Ar);
-                        c0 = mgA * double(wx); c1 = mgA * double(wy); c2 = mgA * double(wz);
-                        c3 = mg * double(w2 * Ar - orr.r * Br);
-                    }
-                }
-                p0 += c0; p1 += c1; p2 += c2; p3 += c3;
-                if constexpr (NS == 5) p4 += c4;
-                if (live) hw.rem &= hw.rem - 1ull;
-                const bool done = live && hw.rem == 0ull;
-                if (live) open = !done;
-                if (__ballot(done) != 0ull && done) {
-                    // the owner's last hit of the group: its partial goes to the owner's row
-                    double* q = osum_[wv] + NS * hw.o;
-                    q[0] += p0; q[1] += p1; q[2] += p2; q[3] += p3;
-                    if constexpr (NS == 5) q[4] += p4;
-                    p0 = 0.0; p1 = 0.0; p2 = 0.0; p3 = 0.0; p4 = 0.0;
-                    hw.o = next_owner(hw.own, hw.o);
-                    hw.rem = hw.o < 64 ? S.mask[hw.o] : 0ull;
-                }
-            }
-            // open partials: lanes whose range ended inside an owner's hits
-            if (__ballot(open) != 0ull) {
-                bool last;
-                const int lo = run_first(lane, open ? hw.o : 64 + lane, &last);
-                seg_scan_up(lane, lo, [&](auto ctl, auto rows, bool take) {
-                    constexpr int C = decltype(ctl)::value, RW = decltype(rows)::value;
-                    p0 = dpp_take_add<C, RW>(p0, take);
-                    p1 = dpp_take_add<C, RW>(p1, take);
-                    p2 = dpp_take_add<C, RW>(p2, take);
-                    p3 = dpp_take_add<C, RW>(p3, take);
-                    if constexpr (NS == 5) p4 = dpp_take_add<C, RW>(p4, take);
-                });
-                if (open && last) {
-                    double* q = osum_[wv] + NS * hw.o;
-                    q[0] += p0; q[1] += p1; q[2] += p2; q[3] += p3;
-                    if constexpr (NS == 5) q[4] += p4;
-                }
-            }
+            GasEval<Real, N, EXACT_G, RM, PAIRS> eval(a, a0, G, S, SR, o_x, o_y, o_z, o_h, o_Vx, o_Vy, o_Vz, orate,
+                                                      s_gx, s_gw, s_mlp, t, H, npairs);
+            walk_group(S, lane, H, ga, eval);
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
         double acc[NS];
         for (int k = 0; k < NS; ++k) acc[k] = osum[k];
-        if (G.item_off[t + 1] - G.item_off[t] == 1u) {
+        // the closure's rates per gas particle (binary64 powers, erf) stay out of this kernel: inlined,
+        // their constants took 160 registers of spills
+        if (RM != kRatesClosure && G.item_off[t + 1] - G.item_off[t] == 1u) {
             if (ov) gas_write_out<N, RM>(a, a.perm[sp], acc);
         } else {
             double* P = a.part + (it * kTile + lane) * NS;
             for (int k = 0; k < NS; ++k) P[k] = acc[k];
         }
     }
-    for (int d = 32; d >= 1; d >>= 1) npairs += __shfl_xor(npairs, d);
-    uint64_t* cnt = BATCH ? boxes[cur_b].g.counters : a0.g.counters;
-    if (lane == 0 && npairs) atomicAdd((unsigned long long*)&cnt[0], (unsigned long long)npairs);
+    flush(BATCH ? boxes[cur_b].g.counters : a0.g.counters);
 }
 
 // ---------------------------------------------------------------------------
@@ -1846,25 +1968,18 @@ struct DmPassArgs {
 };
 
 // P_ij for one (DM, gas) pair: one Maxwellian gas-velocity sample (Philox tag
-// 0) and P = K_j g v_rel^{n+1} dt_i (eq. dm-update-prob).  `urel` returns
-// v_i - v^B_ij.  Shared by the DM pass and the partner resolve so both see
-// identical values.
-template <typename Real, int N, bool EXACT_G>
-__device__ __forceinline__ Real pair_P(double d2, double dh, double gh, double vx, double vy, double vz, double Vx,
-                                       double Vy, double Vz, Real vs, Real K, Real dt, uint32_t i, uint32_t j,
-                                       uint32_t step, uint32_t box, uint32_t k0, uint32_t k1, const float4* gtab,
-                                       Real urel[3])
+// 0, the block `r`) and P = K_j g v_rel^{n+1} dt_i (eq. dm-update-prob).
+// Shared by the DM pass and the partner resolve so both see identical values;
+// g() gives the pair's overlap (pair_g).
+template <typename Real, int N, typename G>
+__device__ __forceinline__ Real pair_P(G&& g, double vx, double vy, double vz, double Vx, double Vy, double Vz, Real vs,
+                                       Real K, Real dt, const U4& r)
 {
-    U4 r = philox_block(i, j, step, kTagGasVel, box, k0, k1);
-    Real g = EXACT_G ? overlap_g_exact<Real>(sqrt_real(Real(d2)), Real(dh), Real(gh))
-                     : Real(overlap_g_table32(gtab, d2, dh, gh));
     Real z[3];
     normals3<Real>(r, z);
-    urel[0] = Real(vx - Vx) - vs * z[0];
-    urel[1] = Real(vy - Vy) - vs * z[1];
-    urel[2] = Real(vz - Vz) - vs * z[2];
+    const Real urel[3] = {Real(vx - Vx) - vs * z[0], Real(vy - Vy) - vs * z[1], Real(vz - Vz) - vs * z[2]};
     Real vrel = sqrt_real(urel[0] * urel[0] + urel[1] * urel[1] + urel[2] * urel[2]);
-    return K * g * pow_np1<N>(vrel) * dt;
+    return K * g() * pow_np1<N>(vrel) * dt;
 }
 
 // Rao-Blackwellised P_ij (an exact-in-law variant of the per-pair draw):
@@ -1874,14 +1989,11 @@ __device__ __forceinline__ Real pair_P(double d2, double dh, double gh, double v
 // alpha_{n-2} vs^{n+1} 1F1(-(n+1)/2, 3/2, -w^2/(2 vs^2)); the gas record
 // carries i2 = 1/(2 vs^2) (infinite for cold gas, where E = |w|^{n+1}) and
 // Kb = K_j alpha_{n-2} vs^{n+1}.  Shared by the DM pass and the resolve.
-template <typename Real, int N, bool EXACT_G>
-__device__ __forceinline__ Real pair_Pbar(double d2, double dh, double gh, double vx, double vy, double vz,
-                                          double Vx, double Vy, double Vz, Real i2, Real Kb, Real dt,
-                                          const float4* gtab)
+template <typename Real, int N, typename G>
+__device__ __forceinline__ Real pair_Pbar(G&& g, double vx, double vy, double vz, double Vx, double Vy, double Vz,
+                                          Real i2, Real Kb, Real dt)
 {
     static_assert(N > -4, "the expectation diverges for n = -4");
-    const Real g = EXACT_G ? overlap_g_exact<Real>(sqrt_real(Real(d2)), Real(dh), Real(gh))
-                           : Real(overlap_g_table32(gtab, d2, dh, gh));
     const Real wx = Real(vx - Vx), wy = Real(vy - Vy), wz = Real(vz - Vz);
     const Real w2 = wx * wx + wy * wy + wz * wz;
     Real E;
@@ -1892,7 +2004,15 @@ __device__ __forceinline__ Real pair_Pbar(double d2, double dh, double gh, doubl
         rate_1f1<N - 2, Real>(w2 * i2, &FA, &FB);
         E = FB;
     }
-    return Kb * g * E * dt;
+    return Kb * g() * E * dt;
+}
+
+// A pair's overlap as the DM pass and the resolve use it.
+template <typename Real, bool EXACT_G>
+__device__ __forceinline__ Real pair_g(const float4* gtab, double d2, double dh, double gh)
+{
+    return EXACT_G ? overlap_g_exact<Real>(sqrt_real(Real(d2)), Real(dh), Real(gh))
+                   : Real(overlap_g_table32(gtab, d2, dh, gh));
 }
 
 // Decision of eq. dm-update-vels for one DM owner: U_i (tag 2) against P_i;
@@ -1920,44 +2040,150 @@ __device__ __forceinline__ uint32_t dm_decide(uint32_t o, int64_t s, double P, f
     return f;
 }
 
+// The lane's partial of the DM pass: the sum of P_ij in the pair precision
+// (binary32: at most 64 terms, a relative error below 6 units of 2^-24), its
+// maximum and near-boundary flag; the owner rows accumulate the partials in
+// binary64.
+template <typename Real>
+struct DmAcc {
+    struct Term { Real P; int nb; bool hit; };
+    Real P, M;
+    int nb;
+    double* rP; Real* rM; int* rN;
+    __device__ __forceinline__ DmAcc(double* rP_, Real* rM_, int* rN_) : rP(rP_), rM(rM_), rN(rN_) { clear(); }
+    __device__ __forceinline__ void clear() { P = 0; M = 0; nb = 0; }
+    __device__ __forceinline__ void add(const Term& t)
+    {
+        P += t.P;
+        M = bool(uint32_t(t.hit) & uint32_t(!(M > t.P))) ? t.P : M;
+        nb |= t.nb;
+    }
+    __device__ __forceinline__ void flush(int o)
+    {
+        rP[o] += double(P);
+        rM[o] = rM[o] > M ? rM[o] : M;
+        rN[o] |= nb;
+        clear();
+    }
+    __device__ __forceinline__ void scan(int lane, int lo)
+    {
+        seg_scan_up(lane, lo, [&](auto ctl, auto rws, bool take) {
+            constexpr int C = decltype(ctl)::value, RW = decltype(rws)::value;
+            P = dpp_take_add<C, RW>(P, take);
+            M = dpp_take_max<C, RW>(M, take);
+            nb |= int(dpp_u32<C, RW>(uint32_t(nb))) & -int(take);
+        });
+    }
+};
+
+// Evaluation of one hit of the DM pass (walk_group): P_ij, whether the pair
+// exceeds the criterion, and whether it sits at the boundary.
+template <typename Real, int N, bool EXACT_G, bool RB, bool PAIRS>
+struct DmEval {
+    const DmPassArgs& a; const PassGeom& G;
+    TestLds& S; SlotGas<Real>& SR;
+    const double* o_x; const double* o_y; const double* o_z; const double* o_h;
+    const double* o_vx; const double* o_vy; const double* o_vz;
+    const Real* o_dt;
+    const uint4* o_ph;
+    const PhiloxPair& ph;
+    int64_t t;
+    uint32_t& npairs; uint32_t& ncrit;
+    using Value = typename DmAcc<Real>::Term;
+
+    __device__ __forceinline__ DmEval(const DmPassArgs& a_, const PassGeom& G_, TestLds& S_, SlotGas<Real>& SR_,
+                                      const double* ox, const double* oy, const double* oz, const double* oh,
+                                      const double* ovx, const double* ovy, const double* ovz, const Real* odt,
+                                      const uint4* oph, const PhiloxPair& ph_, int64_t t_, uint32_t& np, uint32_t& nc)
+        : a(a_), G(G_), S(S_), SR(SR_), o_x(ox), o_y(oy), o_z(oz), o_h(oh), o_vx(ovx), o_vy(ovy), o_vz(ovz), o_dt(odt),
+          o_ph(oph), ph(ph_), t(t_), npairs(np), ncrit(nc) {}
+
+    struct Pair { double vx, vy, vz, Vx, Vy, Vz; Real vs, K, crit, dt; uint4 po; uint32_t pa, pb; };
+    template <typename G_>
+    __device__ __forceinline__ Real prob(const Pair& q, G_&& g) const
+    {
+        if constexpr (RB) {
+            return pair_Pbar<Real, N>(g, q.vx, q.vy, q.vz, q.Vx, q.Vy, q.Vz, q.vs, q.K, q.dt);
+        } else {
+            const U4 rnd = ph.pair(q.po, q.pa, q.pb);
+            return pair_P<Real, N>(g, q.vx, q.vy, q.vz, q.Vx, q.Vy, q.Vz, q.vs, q.K, q.dt, rnd);
+        }
+    }
+
+    __device__ __forceinline__ Value operator()(int o, int sl, bool live, int)
+    {
+        Value c;
+        // every LDS read of the pair first, so that they are waited for together
+        Pair q;
+        q.Vx = SR.Vx[sl]; q.Vy = SR.Vy[sl]; q.Vz = SR.Vz[sl];
+        q.vs = SR.vs[sl]; q.K = SR.K[sl]; q.crit = SR.crit[sl];
+        if constexpr (!RB) { q.pa = SR.pa[sl]; q.pb = SR.pb[sl]; q.po = o_ph[o]; }
+        q.vx = o_vx[o]; q.vy = o_vy[o]; q.vz = o_vz[o]; q.dt = o_dt[o];
+        const double qh = S.ph[sl], oh = o_h[o], hs = oh + qh, hs2 = hs * hs;
+        const double d2p = pair_d2(o_x[o], o_y[o], o_z[o], S.px[sl], S.py[sl], S.pz[sl],
+                                   (S.pq[sl] >> 31) != 0u, G.L);
+        const double e = d2p - hs2;
+        c.hit = live && e < 0.0;
+        c.nb = live && fabs(e) <= 1e-6 * hs2 ? 1 : 0;
+        if constexpr (PAIRS) pair_export(G, c.hit, G.own[t * kTile + o], S.pq[sl] & 0x7fffffffu);
+        npairs += c.hit ? 1u : 0u;
+        // lanes without a pair run along at distance 0 (every table index stays in range) and drop out
+        // at the end; the binary64 evaluation leaves them out instead
+        const double d2 = masked(d2p, bits(c.hit));
+        Real P = 0;
+        if constexpr (EXACT_G) {
+            if (c.hit) P = prob(q, [&] { return overlap_g_exact<Real>(sqrt_real(Real(d2)), Real(oh), Real(qh)); });
+        } else {
+            Overlap32 ov;
+            ov.begin(a.gtab, d2, oh, qh);
+            P = prob(q, [&] { return ov.value(); });
+        }
+        ncrit += uint32_t(c.hit) & uint32_t(P >= q.crit);
+        c.P = masked(P, bits(c.hit));
+        return c;
+    }
+
+};
+
 template <typename Real, int N, bool EXACT_G, bool BATCH = false, bool PAIRS = false, bool RB = false>
-__global__ __launch_bounds__(64, sizeof(Real) == 4 ? 4 : 3) void k_pass_dm(DmPassArgs a0, const DmPassArgs* __restrict__ boxes,
+__global__ __launch_bounds__(64, sizeof(Real) == 4 ? 3 : 2) void k_pass_dm(DmPassArgs a0, const DmPassArgs* __restrict__ boxes,
                                                    const int64_t* __restrict__ box_items, int nbox)
 {
     __shared__ TestLds S;
     __shared__ double o_x[64], o_y[64], o_z[64], o_h[64], o_vx[64], o_vy[64], o_vz[64];
     __shared__ Real o_dt[64];
-    __shared__ uint32_t o_id[64];
+    __shared__ SlotGas<Real> SR;
+    __shared__ uint4 o_ph[RB ? 1 : 64];       // the DM index's part of its pairs' Philox blocks (PhiloxPair)
     __shared__ double osP[64];
     __shared__ Real osM[64];
     __shared__ int osNB[64];
     const int lane = lane_id();
     int64_t it;
-    uint64_t npairs = 0, ncrit = 0, nnear = 0, nscat = 0, npge1 = 0, nnonf = 0, nneard = 0;
+    // pairs and criterion violations per lane and box (a lane visits far fewer than 2^32 pairs of one
+    // call); the per-owner counts, formed once per item, are wave-uniform
+    uint32_t npairs = 0, ncrit = 0;
+    uint32_t nnear = 0, nscat = 0, npge1 = 0, nnonf = 0, nneard = 0;
     int cur_b = 0;
     // counters belong to the box: flushed when the box changes and at the end
     auto flush = [&](uint64_t* counters) {
+        uint64_t np = npairs, nc = ncrit;
         for (int d = 32; d >= 1; d >>= 1) {
-            npairs += __shfl_xor(npairs, d);
-            ncrit += __shfl_xor(ncrit, d);
-            nnear += __shfl_xor(nnear, d);
-            nscat += __shfl_xor(nscat, d);
-            npge1 += __shfl_xor(npge1, d);
-            nnonf += __shfl_xor(nnonf, d);
-            nneard += __shfl_xor(nneard, d);
+            np += __shfl_xor(np, d);
+            nc += __shfl_xor(nc, d);
         }
         if (lane == 0) {
-            if (npairs) atomicAdd((unsigned long long*)&counters[1], (unsigned long long)npairs);
+            if (np) atomicAdd((unsigned long long*)&counters[1], (unsigned long long)np);
             if (nscat) atomicAdd((unsigned long long*)&counters[2], (unsigned long long)nscat);
             if (nnear) atomicAdd((unsigned long long*)&counters[3], (unsigned long long)nnear);
             if (nneard) atomicAdd((unsigned long long*)&counters[4], (unsigned long long)nneard);
-            if (ncrit) atomicAdd((unsigned long long*)&counters[5], (unsigned long long)ncrit);
+            if (nc) atomicAdd((unsigned long long*)&counters[5], (unsigned long long)nc);
             if (npge1) atomicAdd((unsigned long long*)&counters[6], (unsigned long long)npge1);
             if (nnonf) atomicAdd((unsigned long long*)&counters[7], (unsigned long long)nnonf);
         }
         npairs = ncrit = nnear = nscat = npge1 = nnonf = nneard = 0;
     };
-    while (item_next(a0.g.queue_ctr, a0.g.n_items, &it)) {
+    ItemQueue queue(a0.g.queue_ctr, a0.g.n_items);
+    while (queue.take(&it)) {
         int b = 0;
         if constexpr (BATCH) {
             b = box_of_item(box_items, nbox, it);
@@ -1974,6 +2200,7 @@ __global__ __launch_bounds__(64, sizeof(Real) == 4 ? 4 : 3) void k_pass_dm(DmPas
         it = G.item_order[it];
         const int64_t t = G.it_tile[it];
         const uint64_t cb = G.it_cb[it], ce = G.it_ce[it];
+        const uint32_t sl = __builtin_amdgcn_readfirstlane(G.it_slice[it]);
         const int64_t slot = t * kTile + lane;
         const bool ov = slot < G.n_own;
         const int64_t sp = ov ? int64_t(G.own[slot]) : 0;
@@ -1987,7 +2214,10 @@ __global__ __launch_bounds__(64, sizeof(Real) == 4 ? 4 : 3) void k_pass_dm(DmPas
             o_vx[lane] = orc.vx; o_vy[lane] = orc.vy; o_vz[lane] = orc.vz;
             o_dt[lane] = orc.dt;
         }
-        o_id[lane] = ov ? a.dm_perm[sp] : 0u;
+        const uint32_t oid = ov ? a.dm_perm[sp] : 0u;
+        const PhiloxPair ph(step, kTagGasVel, a.box, a.k0, a.k1);
+        if constexpr (!RB) o_ph[lane] = ph.owner(oid);
+        StageGas<Real, RB> stage(reinterpret_cast<const GasRec<Real>*>(a.grec), SR, ph);
         double A[6];
         for (int k = 0; k < 6; ++k) A[k] = G.obox[6 * t + k];
         const double cen[3] = {0.5 * (A[0] + A[3]), 0.5 * (A[1] + A[4]), 0.5 * (A[2] + A[5])};
@@ -1995,88 +2225,15 @@ __global__ __launch_bounds__(64, sizeof(Real) == 4 ? 4 : 3) void k_pass_dm(DmPas
         // the item's per-owner sums (row = owner lane)
         osP[lane] = 0.0; osM[lane] = Real(0); osNB[lane] = 0;
         PairTest T;
-        test_begin(T, ov, fx, fy, fz, fh, cb, ce);
+        test_begin(T, ov, fx, fy, fz, fh, cb, ce, int(sl & 0xffffu), int(sl >> 16));
+        DmAcc<Real> da(osP, osM, osNB);
         for (;;) {
-            const int H = test_next<1>(T, S, G, A, cen, Lf);
+            const int H = test_next<1>(T, S, G, A, cen, Lf, stage);
             if (H < 0) break;
             if (H == 0) continue;
-            const int R = (H + 63) >> 6;
-            HitWalk hw;
-            walk_begin(S, lane, H, R, hw);
-            // the lane's partial sum of P_ij in the pair precision (binary32: at most 64 terms, a
-            // relative error below 6 units of 2^-24), its maximum and near-boundary flag; the
-            // owner rows accumulate the partials in binary64
-            Real pP = 0, pM = 0;
-            int pNB = 0;
-            bool open = false;
-            for (int r = 0; r < R; ++r) {
-                const bool live = r < hw.n;
-                const int o = live ? hw.o : 0;
-                const int sl = live ? int(__builtin_ctzll(hw.rem)) : 0;
-                bool hit = false;
-                uint32_t e_o = 0u, e_q = 0u;
-                if (live) {
-                    const uint32_t pqv = S.pq[sl];
-                    const int64_t q = int64_t(pqv & 0x7fffffffu);
-                    // the pair's gas record, issued before the distance work that hides its latency
-                    const GasRec<Real> r = reinterpret_cast<const GasRec<Real>*>(a.grec)[q];
-                    const double qx = S.px[sl], qy = S.py[sl], qz = S.pz[sl], qh = S.ph[sl];
-                    const double d2 = pair_d2(o_x[o], o_y[o], o_z[o], qx, qy, qz, (pqv >> 31) != 0u, G.L);
-                    const double hs = o_h[o] + qh;
-                    const double hs2 = hs * hs;
-                    if constexpr (PAIRS) {
-                        hit = d2 < hs2;
-                        e_o = G.own[t * kTile + o];
-                        e_q = uint32_t(q);
-                    }
-                    if (fabs(d2 - hs2) <= 1e-6 * hs2) pNB = 1;
-                    if (d2 < hs2) {
-                        npairs++;
-                        Real P;
-                        if constexpr (RB) {
-                            P = pair_Pbar<Real, N, EXACT_G>(d2, o_h[o], qh, o_vx[o], o_vy[o], o_vz[o], r.Vx, r.Vy, r.Vz,
-                                                            r.vs, r.K, o_dt[o], a.gtab);
-                        } else {
-                            Real urel[3];
-                            P = pair_P<Real, N, EXACT_G>(d2, o_h[o], qh, o_vx[o], o_vy[o], o_vz[o], r.Vx, r.Vy, r.Vz,
-                                                         r.vs, r.K, o_dt[o], o_id[o], r.perm, step, a.box, a.k0, a.k1,
-                                                         a.gtab, urel);
-                        }
-                        pP += P;
-                        pM = pM > P ? pM : P;
-                        if (P >= r.crit) ncrit++;
-                    }
-                    hw.rem &= hw.rem - 1ull;
-                }
-                if constexpr (PAIRS) pair_export(G, hit, e_o, e_q);
-                const bool done = live && hw.rem == 0ull;
-                if (live) open = !done;
-                if (__ballot(done) != 0ull && done) {
-                    // the owner's last hit of the group: its partial goes to the owner's row
-                    osP[hw.o] += double(pP);
-                    osM[hw.o] = osM[hw.o] > pM ? osM[hw.o] : pM;
-                    osNB[hw.o] |= pNB;
-                    pP = 0; pM = 0; pNB = 0;
-                    hw.o = next_owner(hw.own, hw.o);
-                    hw.rem = hw.o < 64 ? S.mask[hw.o] : 0ull;
-                }
-            }
-            // open partials: lanes whose range ended inside an owner's hits
-            if (__ballot(open) != 0ull) {
-                bool last;
-                const int lo = run_first(lane, open ? hw.o : 64 + lane, &last);
-                seg_scan_up(lane, lo, [&](auto ctl, auto rows, bool take) {
-                    constexpr int C = decltype(ctl)::value, RW = decltype(rows)::value;
-                    pP = dpp_take_add<C, RW>(pP, take);
-                    pM = dpp_take_max<C, RW>(pM, take);
-                    pNB |= int(dpp_u32<C, RW>(uint32_t(pNB))) & int(take);
-                });
-                if (open && last) {
-                    osP[hw.o] += double(pP);
-                    osM[hw.o] = osM[hw.o] > pM ? osM[hw.o] : pM;
-                    osNB[hw.o] |= pNB;
-                }
-            }
+            DmEval<Real, N, EXACT_G, RB, PAIRS> eval(a, G, S, SR, o_x, o_y, o_z, o_h, o_vx, o_vy, o_vz, o_dt, o_ph, ph, t,
+                                                     npairs, ncrit);
+            walk_group(S, lane, H, da, eval);
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -2084,12 +2241,15 @@ __global__ __launch_bounds__(64, sizeof(Real) == 4 ? 4 : 3) void k_pass_dm(DmPas
         const Real accM = osM[lane];
         const int accNB = osNB[lane];
         if (G.item_off[t + 1] - G.item_off[t] == 1u) {
-            if (ov) {
-                if (accNB) nnear++;
-                uint32_t f = dm_decide(o_id[lane], slot, accP, float(accM), step, a.box, a.k0, a.k1, a.psum_own,
-                                       a.psum, a.pmax, a.scount, a.slist);
-                nscat += f & 1u; npge1 += (f >> 1) & 1u; nnonf += (f >> 2) & 1u; nneard += (f >> 3) & 1u;
-            }
+            uint32_t f = 0u;
+            if (ov)
+                f = dm_decide(oid, slot, accP, float(accM), step, a.box, a.k0, a.k1, a.psum_own, a.psum, a.pmax,
+                              a.scount, a.slist);
+            nnear += __popcll(__ballot(ov && accNB));
+            nscat += __popcll(__ballot(f & 1u));
+            npge1 += __popcll(__ballot(f & 2u));
+            nnonf += __popcll(__ballot(f & 4u));
+            nneard += __popcll(__ballot(f & 8u));
         } else {
             a.part_p[it * kTile + lane] = accP;
             a.part_pm[it * kTile + lane] = float(accM);
@@ -2124,7 +2284,7 @@ struct GasCombineArgs {
     GasOutArgs out;
 };
 
-// One block per owner tile with several items; wave w sums the tile's items
+// One block per owner tile with several items (the closure: every tile with items); wave w sums the tile's items
 // w, w + kCombineWaves, ... (lane = owner slot) and the wave sums are added in
 // wave order, so the result does not depend on scheduling.
 constexpr int kCombineWaves = 8;
@@ -2136,7 +2296,7 @@ __global__ __launch_bounds__(64 * kCombineWaves) void k_combine_gas(GasCombineAr
     __shared__ double s_acc[kCombineWaves][64][NS];
     const int64_t t = blockIdx.x;
     const uint32_t i0 = a.item_off[t], i1 = a.item_off[t + 1];
-    if (i1 - i0 <= 1u) return;
+    if (i1 - i0 <= (RM == kRatesClosure ? 0u : 1u)) return;
     const int w = int(threadIdx.x) >> 6, l = lane_id();
     double acc[NS];
     for (int c = 0; c < NS; ++c) acc[c] = 0.0;
@@ -2471,15 +2631,13 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(ResolveArgs a)
                     if (d2 < hs * hs) {
                         const GasRec<Real> r = reinterpret_cast<const GasRec<Real>*>(a.grec)[k];
                         const uint32_t gid = r.perm;
+                        auto g = [&] { return pair_g<Real, EXACT_G>(a.gtab, d2, mh, G.th[k]); };
                         double P;
                         if constexpr (RB) {
-                            P = double(pair_Pbar<Real, N, EXACT_G>(d2, mh, G.th[k], mvx, mvy, mvz, r.Vx, r.Vy, r.Vz,
-                                                                   r.vs, r.K, mdt, a.gtab));
+                            P = double(pair_Pbar<Real, N>(g, mvx, mvy, mvz, r.Vx, r.Vy, r.Vz, r.vs, r.K, mdt));
                         } else {
-                            Real urel[3];
-                            P = double(pair_P<Real, N, EXACT_G>(d2, mh, G.th[k], mvx, mvy, mvz, r.Vx, r.Vy, r.Vz, r.vs,
-                                                                r.K, mdt, oid, gid, step, a.box, a.k0, a.k1, a.gtab,
-                                                                urel));
+                            const U4 rnd = philox_block(oid, gid, step, kTagGasVel, a.box, a.k0, a.k1);
+                            P = double(pair_P<Real, N>(g, mvx, mvy, mvz, r.Vx, r.Vy, r.Vz, r.vs, r.K, mdt, rnd));
                         }
                         fn(gid, P);
                     }

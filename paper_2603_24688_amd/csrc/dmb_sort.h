@@ -14,10 +14,14 @@ constexpr int kScanTile = kScanBlock * kScanItems;  // 1024
 // Block-local exclusive scan (inputs TI, sums and outputs TO: 64-bit outputs
 // for offsets that can pass 2^32); writes the block total to sums[blockIdx].
 // Inputs at or past n_in read as 0 (so that out[n_in] can hold the total).
+// Blocks of the grid's second row scan a second array.
 template <typename TI, typename TO>
 __global__ __launch_bounds__(kScanBlock) void k_scan_block(const TI* __restrict__ in, TO* __restrict__ out,
-                                                           TO* __restrict__ sums, int64_t n, int64_t n_in)
+                                                           TO* __restrict__ sums, int64_t n, int64_t n_in,
+                                                           const TI* __restrict__ in2, TO* __restrict__ out2,
+                                                           TO* __restrict__ sums2)
 {
+    if (blockIdx.y) { in = in2; out = out2; sums = sums2; }
     __shared__ TO wsum[kScanBlock / 64];
     int64_t base = int64_t(blockIdx.x) * kScanTile + int64_t(threadIdx.x) * kScanItems;
     TO v[kScanItems];
@@ -58,8 +62,10 @@ constexpr int64_t kScanOwnMax = 4096;
 
 template <typename TO>
 __global__ __launch_bounds__(kScanBlock) void k_scan_add_own(TO* __restrict__ out, const TO* __restrict__ sums,
-                                                             int64_t n)
+                                                             int64_t n, TO* __restrict__ out2,
+                                                             const TO* __restrict__ sums2)
 {
+    if (blockIdx.y) { out = out2; sums = sums2; }
     __shared__ TO part[kScanBlock / 64];
     const int b = int(blockIdx.x);
     if (b == 0) return;
@@ -79,8 +85,10 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_add_own(TO* __restrict__ ou
 }
 
 template <typename TO>
-__global__ __launch_bounds__(kScanBlock) void k_scan_add(TO* __restrict__ out, const TO* __restrict__ sums, int64_t n)
+__global__ __launch_bounds__(kScanBlock) void k_scan_add(TO* __restrict__ out, const TO* __restrict__ sums, int64_t n,
+                                                         TO* __restrict__ out2, const TO* __restrict__ sums2)
 {
+    if (blockIdx.y) { out = out2; sums = sums2; }
     TO add = sums[blockIdx.x];
     int64_t base = int64_t(blockIdx.x) * kScanTile + threadIdx.x;
 #pragma unroll
@@ -112,6 +120,7 @@ constexpr uint64_t kOsAgg = 1ull << 62;        // status: this tile's own count 
 constexpr uint64_t kOsInc = 2ull << 62;        // status: count of this and all earlier tiles
 constexpr uint64_t kOsCount = (1ull << 62) - 1;
 constexpr uint32_t kOsSpinMax = 1u << 24;
+constexpr int kOsWords = kOsMaxPasses * 256 + kOsMaxPasses;   // digit counts and tile counters
 
 struct OsArgs {
     int64_t n;
