@@ -77,7 +77,7 @@ struct Cells {
     Species gas, dm;
     Pairs gp, dp;                          // gas owners x DM tiles; DM owners x gas tiles
     DevBuf part_gas, part_p, part_pm, part_nb, psum_own;
-    DevBuf qctr, slist;
+    DevBuf qctr, slist, rwide;
     int64_t built_ngas = -1, built_ndm = -1;
     const double* built_gas_pos = nullptr;
     const double* built_dm_pos = nullptr;
@@ -701,6 +701,9 @@ dmb_status both(dmb_ctx* c, FA&& a, FB&& b)
     return sj;
 }
 
+// A DM can outgrow a block's cache only if the box has that many gas particles or sub-tiles.
+bool resolve_may_widen(const Cells& X) { return X.gas.n > kResolvePairs || X.gas.ntile > kResolveList; }
+
 // Per-step gathers into Morton order and the clearing of outputs, counters
 // and the box's queue counters (qctr: eight of the gas queue, eight of the DM
 // queue and the scatter count, kQueueStride words apart).  Buffers are sized first; with `overlap` the gas
@@ -727,6 +730,7 @@ dmb_status gather_and_fill(dmb_ctx* c, Cells& X, const dmb_particles* gas, const
         ENSURE(c, X.part_nb, size_t(X.dp.nitems) * kTile);
         ENSURE(c, X.psum_own, size_t(D.n_own) * 8);
         ENSURE(c, X.slist, size_t(D.n_own) * 4);
+        if (resolve_may_widen(X)) ENSURE(c, X.rwide, kResolveWide * sizeof(ResolveWide));
     }
     auto gas_gather = [&] {
         GasGatherArgs ga;
@@ -841,12 +845,8 @@ DmPassArgs dm_pass_args(dmb_ctx* c, Cells& X, const dmb_params* par, dmb_out* ou
     return a;
 }
 
-template <typename Real, int N, bool RB>
-void combine_dm_and_resolve(dmb_ctx* c, Cells& X, const DmPassArgs& a, const dmb_particles* gas,
-                            const dmb_params* par, dmb_out* out, uint64_t* counters)
+void combine_dm(dmb_ctx* c, Cells& X, const DmPassArgs& a, dmb_out* out, uint64_t* counters)
 {
-    constexpr bool kExact = sizeof(Real) == 8;
-    Species& G = X.gas;
     Species& D = X.dm;
     DmCombineArgs cb;
     cb.n_own = D.n_own; cb.own = D.own.as<const uint32_t>(); cb.perm = D.perm;
@@ -855,11 +855,14 @@ void combine_dm_and_resolve(dmb_ctx* c, Cells& X, const DmPassArgs& a, const dmb
     cb.k0 = a.k0; cb.k1 = a.k1; cb.step = a.step; cb.box = a.box; cb.step_off = a.step_off;
     cb.psum_own = X.psum_own.as<double>(); cb.psum = out->p_sum; cb.pmax = out->p_max;
     cb.scount = a.scount; cb.slist = X.slist.as<uint32_t>(); cb.counters = counters;
-    {
-        Phase ph(c, DMB_PH_COMBINE_DM);
-        hipLaunchKernelGGL(k_combine_dm, dim3(unsigned((D.n_own + kTile - 1) / kTile)), dim3(64 * kCombineWaves), 0,
-                           c->stream, cb);
-    }
+    Phase ph(c, DMB_PH_COMBINE_DM);
+    hipLaunchKernelGGL(k_combine_dm, dim3(unsigned((D.n_own + kTile - 1) / kTile)), dim3(64 * kCombineWaves), 0,
+                       c->stream, cb);
+}
+
+ResolveArgs resolve_args(dmb_ctx* c, Cells& X, const DmPassArgs& a, const dmb_particles* gas, const dmb_params* par,
+                         dmb_out* out, uint64_t* counters)
+{
     ResolveArgs r;
     r.g = a.g;
     r.cand_beg = X.dp.beg.as<const uint64_t>(); r.cand_cnt = X.dp.scnt.as<const uint32_t>();
@@ -869,15 +872,41 @@ void combine_dm_and_resolve(dmb_ctx* c, Cells& X, const DmPassArgs& a, const dmb
     r.gtab = a.gtab; r.k0 = a.k0; r.k1 = a.k1; r.step = a.step; r.box = a.box; r.step_off = a.step_off;
     r.aniso_g = par->aniso_g;
     r.tilt_gl = c->tilt_gl.as<const double>();
-    r.n_gas_bits = bits_for(std::max<int64_t>(G.n, 2));
-    r.n_gas = uint32_t(G.n);
+    r.n_gas_bits = bits_for(std::max<int64_t>(X.gas.n, 2));
+    r.n_gas = uint32_t(X.gas.n);
     r.scount = a.scount; r.slist = X.slist.as<const uint32_t>();
+    r.wide = resolve_may_widen(X) ? X.rwide.as<ResolveWide>() : nullptr;
+    r.wcount = const_cast<uint32_t*>(a.scount) + kQueueStride / 2;
+    r.err = c->os_err.as<uint32_t>();
     r.dv = out->dv_dm; r.partner = out->partner; r.counters = counters;
+    return r;
+}
+
+// The partner resolve of one box (dev: null) or of all boxes of a batch (args in device memory);
+// wide: some DM may outgrow a block.
+template <typename Real, int N, bool RB, bool BATCH>
+void launch_resolve(dmb_ctx* c, const ResolveArgs& r, const ResolveArgs* dev, int nbox, bool wide)
+{
+    constexpr bool kExact = sizeof(Real) == 8;
     Phase ph(c, DMB_PH_RESOLVE);
-    hipLaunchKernelGGL((k_resolve<Real, N, kExact, RB>), dim3(std::max(8, c->num_cu * 2)), dim3(kResolveThreads), 0,
-                       c->stream, r);
+    const dim3 grid(unsigned(std::max(8, c->num_cu * 2 / nbox)), unsigned(nbox));
+    hipLaunchKernelGGL((k_resolve<Real, N, kExact, RB, BATCH>), grid, dim3(kResolveThreads), 0, c->stream, r, dev);
+    if (wide)
+        hipLaunchKernelGGL((k_resolve_wide<Real, N, kExact, RB, BATCH>),
+                           dim3(unsigned(std::max(8, c->num_cu / nbox)), unsigned(nbox)), dim3(kResolveThreads), 0,
+                           c->stream, r, dev);
     if constexpr (RB)
-        hipLaunchKernelGGL((k_rb_kick<Real, N>), dim3(std::max(8, c->num_cu * 4)), dim3(64), 0, c->stream, r);
+        hipLaunchKernelGGL((k_rb_kick<Real, N, BATCH>), dim3(unsigned(std::max(8, c->num_cu * 4 / nbox)), unsigned(nbox)),
+                           dim3(64), 0, c->stream, r, dev);
+}
+
+template <typename Real, int N, bool RB>
+void combine_dm_and_resolve(dmb_ctx* c, Cells& X, const DmPassArgs& a, const dmb_particles* gas,
+                            const dmb_params* par, dmb_out* out, uint64_t* counters)
+{
+    combine_dm(c, X, a, out, counters);
+    const ResolveArgs r = resolve_args(c, X, a, gas, par, out, counters);
+    launch_resolve<Real, N, RB, false>(c, r, nullptr, 1, r.wide != nullptr);
 }
 
 // The DM pair pass of one step (RB: Rao-Blackwellised sampling, expected
@@ -973,6 +1002,8 @@ struct BatchPlan {
     int64_t gas_items = 0, dm_items = 0;
     std::vector<GasPassArgs> ga;
     std::vector<DmPassArgs> da;
+    std::vector<ResolveArgs> ra;
+    bool resolve_wide = false;             // some box may need k_resolve_wide
     int nb_gas = 0, nb_dm = 0;
     bool rb = false;                       // Rao-Blackwellised DM sampling
 };
@@ -986,6 +1017,8 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
     P.nbox = nbox;
     P.ga.resize(nbox);
     P.da.resize(nbox);
+    P.ra.resize(nbox);
+    P.resolve_wide = false;
     std::vector<int64_t> gi(nbox + 1, 0), di(nbox + 1, 0);
     // global queues (gas, DM), then the Philox step offset
     ENSURE(c, c->bstep, kQueueWords * sizeof(uint32_t));
@@ -1000,6 +1033,7 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
             ENSURE(c, X.part_nb, size_t(X.dp.nitems) * kTile);
             ENSURE(c, X.psum_own, size_t(X.dm.n_own) * 8);
             ENSURE(c, X.slist, size_t(X.dm.n_own) * 4);
+            if (resolve_may_widen(X)) ENSURE(c, X.rwide, kResolveWide * sizeof(ResolveWide));
         }
         ENSURE(c, X.qctr, kQueueWords * 4);
         const int rs = int(sizeof(Real));
@@ -1016,18 +1050,22 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
         uint64_t* counters = out[b].counters;
         P.ga[b] = gas_pass_args<Real, N, RM>(c, X, gas + b, par + b, out + b, counters);
         P.da[b] = dm_pass_args(c, X, par + b, out + b, counters, step_off);
+        P.ra[b] = resolve_args(c, X, P.da[b], gas + b, par + b, out + b, counters);
+        if (X.dp.nitems > 0 && P.ra[b].wide) P.resolve_wide = true;
         gi[b + 1] = gi[b] + X.gp.nitems;
         di[b + 1] = di[b] + X.dp.nitems;
     }
     P.gas_items = gi[nbox];
     P.dm_items = di[nbox];
-    const size_t argb = sizeof(GasPassArgs) + sizeof(DmPassArgs);
+    const size_t argb = sizeof(GasPassArgs) + sizeof(DmPassArgs) + sizeof(ResolveArgs);
     ENSURE(c, c->bgeom, size_t(nbox) * argb + 256);
     ENSURE(c, c->bitem, size_t(2 * (nbox + 1)) * sizeof(int64_t));
     char* gdev = c->bgeom.as<char>();
     HIPCHK(c, hipMemcpyAsync(gdev, P.ga.data(), nbox * sizeof(GasPassArgs), hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(gdev + size_t(nbox) * sizeof(GasPassArgs), P.da.data(), nbox * sizeof(DmPassArgs),
                              hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(gdev + size_t(nbox) * (sizeof(GasPassArgs) + sizeof(DmPassArgs)), P.ra.data(),
+                             nbox * sizeof(ResolveArgs), hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->bitem.p, gi.data(), (nbox + 1) * sizeof(int64_t), hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->bitem.as<int64_t>() + nbox + 1, di.data(), (nbox + 1) * sizeof(int64_t),
                              hipMemcpyHostToDevice, c->stream));
@@ -1043,11 +1081,10 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
     return DMB_OK;
 }
 
-// The DM side of a batched step: one pass over all boxes' items, then the
-// per-box combines and resolves.
+// The DM side of a batched step: one pass over all boxes' items, the per-box
+// combines, and one resolve over all boxes.
 template <typename Real, int N, bool RB>
-void batch_dm_side(dmb_ctx* c, const dmb_particles* gas, const dmb_params* par, dmb_out* out, const BatchPlan& P,
-                   const DmPassArgs* ddev, const int64_t* ditems)
+void batch_dm_side(dmb_ctx* c, dmb_out* out, const BatchPlan& P, const DmPassArgs* ddev, const int64_t* ditems)
 {
     constexpr bool kExact = sizeof(Real) == 8;
     DmPassArgs a0 = P.da[0];
@@ -1060,7 +1097,9 @@ void batch_dm_side(dmb_ctx* c, const dmb_particles* gas, const dmb_params* par, 
     }
     for (int b = 0; b < P.nbox; ++b)
         if (c->boxes[b]->dp.nitems > 0)
-            combine_dm_and_resolve<Real, N, RB>(c, *c->boxes[b], P.da[b], gas + b, par + b, out + b, out[b].counters);
+            combine_dm(c, *c->boxes[b], P.da[b], out + b, out[b].counters);
+    launch_resolve<Real, N, RB, true>(c, P.ra[0], reinterpret_cast<const ResolveArgs*>(ddev + P.nbox), P.nbox,
+                                      P.resolve_wide);
 }
 
 template <typename Real, int N, int RM>
@@ -1092,11 +1131,11 @@ dmb_status batch_enqueue(dmb_ctx* c, const dmb_particles* gas, const dmb_particl
         bool done = false;
         if constexpr (N > -4) {
             if (P.rb) {
-                batch_dm_side<Real, N, true>(c, gas, par, out, P, ddev, ditems);
+                batch_dm_side<Real, N, true>(c, out, P, ddev, ditems);
                 done = true;
             }
         }
-        if (!done) batch_dm_side<Real, N, false>(c, gas, par, out, P, ddev, ditems);
+        if (!done) batch_dm_side<Real, N, false>(c, out, P, ddev, ditems);
     }
     if (P.gas_items > 0) {
         OnSide on(c, side);
@@ -1326,7 +1365,8 @@ void free_cells(Cells& X)
                          &P->it_ord, &P->it_slice, &P->slices, &P->gbox, &P->gh, &P->gsup, &P->gq, &P->gcnt, &P->glist, &P->gmax};
         for (DevBuf* b : all) fr(*b);
     }
-    DevBuf* rest[] = {&X.part_gas, &X.part_p, &X.part_pm, &X.part_nb, &X.psum_own, &X.qctr, &X.slist};
+    DevBuf* rest[] = {&X.part_gas, &X.part_p, &X.part_pm, &X.part_nb, &X.psum_own, &X.qctr, &X.slist,
+                      &X.rwide};
     for (DevBuf* b : rest) fr(*b);
 }
 
@@ -1611,7 +1651,7 @@ dmb_status build_cells_impl(dmb_ctx* c, const dmb_particles* gas, const dmb_part
         if (v[4] != 0) {
             hipLaunchKernelGGL(k_os_clear, dim3(1), dim3(256), 0, c->stream, c->os_err.as<uint32_t>(), 1);
             c->X->built_ngas = c->X->built_ndm = -1;
-            return fail(c, DMB_EHIP, "radix sort: a look-back wait gave up");
+            return fail(c, DMB_EHIP, "a wait of the radix sort or the partner search gave up");
         }
         c->X->gas.n_own = int64_t(v[0]);
         c->X->gas.ntile = int64_t(v[1]);

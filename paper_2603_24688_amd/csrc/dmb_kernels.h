@@ -2373,13 +2373,28 @@ __global__ __launch_bounds__(64 * kCombineWaves) void k_combine_dm(DmCombineArgs
 // ---------------------------------------------------------------------------
 // Partner resolve for the DM that scatter (eq. dm-update-vels: one draw from
 // the mixture): the partner is the smallest gas index whose running sum of
-// P_ij exceeds U_i.  The DM's pairs are enumerated once (candidate sub-tiles
-// first filtered by a point-to-box test) with the same arithmetic as the DM
-// pass and cached in LDS as (gas index, P_ij); a radix select over the gas
-// index, 8 bits per pass, accumulates P_ij per digit as exact fixed-point
-// integers (P * 2^64 split into two u64 halves), so the running sums are exact
-// sums of the per-pair values and do not depend on accumulation order.  DM
-// with more pairs than the cache recompute their pairs in every pass.
+// P_ij exceeds U_i.  The DM's pairs are enumerated with the same arithmetic as
+// the DM pass; a radix select over the gas index, 8 bits per pass, accumulates
+// P_ij per digit as exact fixed-point integers (P * 2^64 split into two u64
+// halves), so the running sums are exact sums of the per-pair values and do not
+// depend on accumulation order or on how the pairs are split.
+//
+// k_resolve: one block per scattering DM, bound by the latency of its chain of
+// loads and barriers.  Wavefronts filter the candidate sub-tiles (point-to-box
+// test), then test their particles four sub-tiles at a time, so that four loads
+// are in flight; the pairs inside the support are packed in LDS and evaluated by
+// full wavefronts (a third of the tested particles are pairs, and the binary64
+// overlap is most of the work), and every radix pass reads the cached (gas index,
+// P_ij), its 256 bins summed by one wavefront without barriers.
+// A DM with more sub-tiles or pairs than the cache holds goes to a list, and
+// k_resolve_wide spreads the pairs of its few entries over the whole chip; in each
+// radix pass the last block of a DM to finish picks the digit.
+struct ResolveWide {              // state of one entry of that list
+    unsigned long long hi[256], lo[256];
+    uint32_t e;                   // index into the scatter list
+    uint32_t prefix, done, pass;  // digits picked so far, slices finished in this pass, passes finished
+    unsigned long long below[2];
+};
 struct ResolveArgs {
     PassGeom g;                   // owners = DM, others = gas sub-tiles (as in the DM pass)
     const uint64_t* cand_beg; const uint32_t* cand_cnt;   // each owner tile's candidate list
@@ -2395,6 +2410,8 @@ struct ResolveArgs {
     int n_gas_bits;
     uint32_t n_gas;
     const uint32_t* scount; const uint32_t* slist;
+    ResolveWide* wide; uint32_t* wcount;  // nullptr: no DM can outgrow the cache; entries, [1]: tickets
+    uint32_t* err;                // raised if a wait gave up
     double* dv; int32_t* partner;
     uint64_t* counters;
 };
@@ -2534,221 +2551,407 @@ __device__ void scatter_kick(const ResolveArgs& a, uint32_t oid, uint32_t j, uin
     a.partner[oid] = int32_t(j);
 }
 
-constexpr int kResolveThreads = 1024; // sixteen wavefronts per scattering DM (the first 256 threads own the histogram bins)
+constexpr int kResolveThreads = 512;  // eight wavefronts: the most that leaves the overlap its registers
+constexpr int kResolveWaves = kResolveThreads / 64;
 constexpr int kResolveList = 2048;    // candidate sub-tiles kept per scattering DM after the point test
-constexpr int kResolvePairs = 8192;   // pairs cached per scattering DM (LDS)
+constexpr int kResolvePairs = 8192;   // pairs cached per scattering DM (LDS; the registers allow one block per CU anyway)
+constexpr int kResolveWide = 256;     // DM spread over the chip (beyond these, enough blocks are busy anyway)
+constexpr int kResolveStreams = 4;    // sub-tiles a wavefront (candidates a thread) tests at a time
+constexpr uint32_t kResolveSpinMax = 1u << 24;
 
-template <typename Real, int N, bool EXACT_G, bool RB = false>
-__global__ __launch_bounds__(kResolveThreads) void k_resolve(ResolveArgs a)
+// The scattering DM of list entry e.
+template <typename Real>
+struct ResolveDm {
+    double x, y, z, h, vx, vy, vz;
+    Real dt;
+    uint32_t oid;
+    int64_t t;
+    uint64_t U;                   // U_i in units of 2^-64
+    __device__ __forceinline__ ResolveDm(const ResolveArgs& a, uint32_t e, uint32_t step)
+    {
+        const int64_t s = a.slist[e], sp = a.g.own[s];
+        t = s / kTile;
+        x = a.g.ox[sp]; y = a.g.oy[sp]; z = a.g.oz[sp]; h = a.g.oh[sp];
+        const DmRec<Real> r = reinterpret_cast<const DmRec<Real>*>(a.drec)[sp];
+        vx = r.vx; vy = r.vy; vz = r.vz; dt = r.dt;
+        oid = a.dm_perm[sp];
+        const U4 rd = philox_block(oid, 0xFFFFFFFFu, step, kTagDecision, a.box, a.k0, a.k1);
+        U = uint64_t(2ull * (rd.x >> 8) + 1ull) << 39;
+    }
+    __device__ __forceinline__ bool near(const ResolveArgs& a, uint32_t ot) const
+    {
+        const double P6[6] = {x, y, z, x, y, z};
+        return boxes_near(P6, h, a.g.tbox + 6 * int64_t(ot), a.g.thmax[ot], a.g.L);
+    }
+};
+
+// P_ij of the DM with gas particle k (sorted index) at squared distance d2.
+template <typename Real, int N, bool EXACT_G, bool RB>
+__device__ __forceinline__ double resolve_P(const ResolveArgs& a, const ResolveDm<Real>& m, uint32_t step, int64_t k,
+                                            double d2, double gh, uint32_t* gid)
+{
+    const GasRec<Real> r = reinterpret_cast<const GasRec<Real>*>(a.grec)[k];
+    *gid = r.perm;
+    auto g = [&] { return pair_g<Real, EXACT_G>(a.gtab, d2, m.h, gh); };
+    if constexpr (RB) {
+        return double(pair_Pbar<Real, N>(g, m.vx, m.vy, m.vz, r.Vx, r.Vy, r.Vz, r.vs, r.K, m.dt));
+    } else {
+        const U4 rnd = philox_block(m.oid, r.perm, step, kTagGasVel, a.box, a.k0, a.k1);
+        return double(pair_P<Real, N>(g, m.vx, m.vy, m.vz, r.Vx, r.Vy, r.Vz, r.vs, r.K, m.dt, rnd));
+    }
+}
+
+// One wavefront's share of the DM's pairs, straight from the candidate list: candidates
+// first, first + stride, ...; 64 are tested at a time, the reached ones walked in turn.
+template <typename Real, int N, bool EXACT_G, bool RB, typename Fn>
+__device__ __forceinline__ void resolve_walk(const ResolveArgs& a, const ResolveDm<Real>& m, uint32_t step, int lane,
+                                             uint64_t first, uint64_t stride, Fn&& fn)
+{
+    const PassGeom& G = a.g;
+    double A[6];
+    for (int k = 0; k < 6; ++k) A[k] = G.obox[6 * m.t + k];
+    const uint64_t cb = a.cand_beg[m.t], nc = a.cand_cnt[m.t];
+    for (uint64_t i0 = first; i0 < nc; i0 += 64 * stride) {
+        const uint64_t i = i0 + uint64_t(lane) * stride;
+        uint32_t ot = 0u;
+        bool near = false;
+        if (i < nc) {
+            ot = G.cand[cb + i];
+            near = m.near(a, ot);
+        }
+        for (uint64_t mk = __ballot(near); mk;) {
+            // the next four reached sub-tiles, a quarter of the wavefront each
+            int from = -1;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                if (mk && g == (lane >> 4)) from = int(__builtin_ctzll(mk));
+                mk &= mk - 1ull;
+            }
+            const uint32_t o = uint32_t(__shfl(int(ot), max(from, 0)));
+            double sh[3];
+            bool clean;
+            tile_pair_shift(A, G.tbox + 6 * int64_t(o), G.L, sh, &clean);
+            const int cnt = from >= 0 ? int(G.sub_cnt[o]) : 0;
+            for (int kk = lane & 15; kk < cnt; kk += 16) {
+                const int64_t k = int64_t(G.sub_start[o]) + kk;
+                const double gh = G.th[k], hs = m.h + gh;
+                const double d2 = pair_d2(m.x, m.y, m.z, G.tx[k] + sh[0], G.ty[k] + sh[1], G.tz[k] + sh[2], clean, G.L);
+                if (d2 < hs * hs) {
+                    uint32_t gid;
+                    const double P = resolve_P<Real, N, EXACT_G, RB>(a, m, step, k, d2, gh, &gid);
+                    fn(gid, P);
+                }
+            }
+        }
+    }
+}
+
+__device__ __forceinline__ void hist_add(unsigned long long* hi, unsigned long long* lo, int shft, uint32_t prefix,
+                                         uint32_t gid, double P)
+{
+    if ((uint64_t(gid) >> (shft + 8)) == uint64_t(prefix)) {
+        unsigned long long h, l;
+        fixed_split(P, &h, &l);
+        const int dg = (gid >> shft) & 255u;
+        atomicAdd(&hi[dg], h);
+        atomicAdd(&lo[dg], l);
+    }
+}
+
+__device__ __forceinline__ unsigned __int128 shfl128(unsigned __int128 v, int l)
+{
+    const uint64_t lo = __shfl((unsigned long long)v, l), hi = __shfl((unsigned long long)(v >> 64), l);
+    return ((unsigned __int128)hi << 64) | lo;
+}
+
+// The selected bin: the first whose running sum (from `below`) passes U.  One
+// wavefront, four bins per lane, v[k] the sum of bin 4 lane + k; every lane
+// returns the same digit and running sums before (*before) and after (*after) it.
+__device__ __forceinline__ uint32_t radix_pick(int lane, const unsigned __int128 v[4], unsigned __int128 below, uint64_t U,
+                                               unsigned __int128* before, unsigned __int128* after)
+{
+    unsigned __int128 own = v[0] + v[1] + v[2] + v[3], incl = own;
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned __int128 y = shfl128(incl, max(lane - d, 0));
+        if (lane >= d) incl += y;
+    }
+    unsigned __int128 run = below + incl - own, fb = 0, fa = 0;
+    int found = -1, nz = -1;
+    for (int k = 0; k < 4; ++k) {
+        const unsigned __int128 nx = run + v[k];
+        if (v[k] != 0) nz = 4 * lane + k;
+        if (run <= U && nx > U) {            // unique: running sums increase, empty bins cannot pass
+            found = 4 * lane + k;
+            fb = run; fa = nx;
+        }
+        run = nx;
+    }
+    const uint64_t mf = __ballot(found >= 0);
+    if (mf) {
+        const int l = int(__builtin_ctzll(mf));
+        *before = shfl128(fb, l);
+        *after = shfl128(fa, l);
+        return uint32_t(__shfl(found, l));
+    }
+    // rounding guard: keep the largest index with P > 0
+    const uint64_t mz = __ballot(nz >= 0);
+    *before = below;
+    *after = below + shfl128(incl, 63);
+    return mz ? uint32_t(__shfl(nz, 63 - int(__builtin_clzll(mz)))) : 0u;
+}
+
+// The chosen partner of one DM (one thread): near-boundary count, partner and, in
+// the pairwise scheme, the kick.
+template <typename Real, bool RB>
+__device__ __forceinline__ void resolve_finish(const ResolveArgs& a, const ResolveDm<Real>& m, uint32_t step, uint32_t prefix,
+                                               unsigned __int128 before, unsigned __int128 after)
+{
+    // running sums adjacent to U_i (relative 1e-6 band)
+    const double Ud = double(m.U) * 0x1p-64, Sb = double(before) * 0x1p-64, Sa = double(after) * 0x1p-64;
+    if (fabs(Sb - Ud) <= 1e-6 * Ud || fabs(Sa - Ud) <= 1e-6 * Ud)
+        atomicAdd((unsigned long long*)&a.counters[4], 1ull);
+    const uint32_t j = prefix < a.n_gas ? prefix : a.n_gas - 1u;
+    if constexpr (RB) {
+        a.partner[m.oid] = int32_t(j);   // the kick follows in k_rb_kick
+    } else {
+        // the partner's gas-velocity sample from the same uniforms as its P_ij (tag 0),
+        // and the kick, in binary64 in either precision: one thread per scattering DM
+        const double vs = sqrt(2.0 * a.gas_u[j] / 3.0);
+        U4 r = philox_block(m.oid, j, step, kTagGasVel, a.box, a.k0, a.k1);
+        double z[3];
+        normals3<double>(r, z);
+        const double ux = (m.vx - a.gas_vel[3 * int64_t(j)]) - vs * z[0];
+        const double uy = (m.vy - a.gas_vel[3 * int64_t(j) + 1]) - vs * z[1];
+        const double uz = (m.vz - a.gas_vel[3 * int64_t(j) + 2]) - vs * z[2];
+        scatter_kick<double>(a, m.oid, j, step, ux, uy, uz);
+    }
+}
+
+template <typename Real, int N, bool EXACT_G, bool RB = false, bool BATCH = false>
+__global__ __launch_bounds__(kResolveThreads) void k_resolve(ResolveArgs a0, const ResolveArgs* __restrict__ boxes)
 {
     __shared__ unsigned long long hhi[256], hlo[256];
-
-    __shared__ uint32_t s_list[kResolveList];
-    __shared__ uint32_t s_pre[kResolveList + 1];
-    __shared__ uint32_t s_gid[kResolvePairs];
+    // kept sub-tiles: first particle; image (8 bits per axis), particle count << 24, clean << 31
+    __shared__ uint32_t s_start[kResolveList], s_info[kResolveList];
+    __shared__ uint32_t s_gid[kResolvePairs];   // list position << 6 | particle, then the gas index
     __shared__ double s_P[kResolvePairs];
-    __shared__ uint32_t s_nrel, s_npairs, s_sel;
-    __shared__ int s_near, s_found, s_lastnz;
-    __shared__ unsigned __int128 s_cum[256], s_selb, s_sela;
-    __shared__ unsigned long long s_run[kResolveThreads];
-    static_assert(kResolveThreads >= 256 && kResolveThreads % 256 == 0, "thread t < 256 owns histogram bin t");
-    const bool bin_owner = threadIdx.x < 256;
+    __shared__ uint32_t s_nrel, s_npart, s_npairs, s_wide, s_prefix;
+    const ResolveArgs& a = BATCH ? boxes[blockIdx.y] : a0;
     const PassGeom& G = a.g;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t step = a.step + (a.step_off ? *a.step_off : 0u);
     const uint32_t nsc = *a.scount;
-    uint32_t nnearD = 0;
+    const int npass = (a.n_gas_bits + 7) / 8;
 
     for (uint32_t e = blockIdx.x; e < nsc; e += gridDim.x) {
-        const int64_t s = a.slist[e];
-        const int64_t sp = G.own[s];
-        const int64_t t = s / kTile;
-        const double mx = G.ox[sp], my = G.oy[sp], mz = G.oz[sp], mh = G.oh[sp];
-        const DmRec<Real> orc = reinterpret_cast<const DmRec<Real>*>(a.drec)[sp];
-        const double mvx = orc.vx, mvy = orc.vy, mvz = orc.vz;
-        const Real mdt = orc.dt;
-        const uint32_t oid = a.dm_perm[sp];
-        U4 rd = philox_block(oid, 0xFFFFFFFFu, step, kTagDecision, a.box, a.k0, a.k1);
-        const unsigned __int128 Ufix = (unsigned __int128)(2ull * (rd.x >> 8) + 1ull) << 39;
+        const ResolveDm<Real> m(a, e, step);
         double A[6];
-        for (int k = 0; k < 6; ++k) A[k] = G.obox[6 * t + k];
-        const uint64_t cb = a.cand_beg[t], ce = cb + a.cand_cnt[t];
-        if (tid == 0) { s_nrel = 0; s_npairs = 0; }
+        for (int k = 0; k < 6; ++k) A[k] = G.obox[6 * m.t + k];
+        const uint64_t cb = a.cand_beg[m.t], ce = cb + a.cand_cnt[m.t];
+        if (tid == 0) { s_nrel = 0u; s_npart = 0u; s_npairs = 0u; s_wide = 0u; }
         __syncthreads();
         // candidate sub-tiles this DM can reach (point-to-box gap < h_i + max h of the sub-tile)
-        const double P6[6] = {mx, my, mz, mx, my, mz};
-        for (uint64_t c = cb + tid; c < ce; c += kResolveThreads) {
-            const uint32_t ot = G.cand[c];
-            if (boxes_near(P6, mh, G.tbox + 6 * int64_t(ot), G.thmax[ot], G.L)) {
+        for (uint64_t c0 = cb + tid; c0 < ce; c0 += kResolveStreams * kResolveThreads) {
+            uint32_t ot[kResolveStreams];
+            bool near[kResolveStreams];
+#pragma unroll
+            for (int u = 0; u < kResolveStreams; ++u) ot[u] = G.cand[min(c0 + u * kResolveThreads, ce - 1)];
+#pragma unroll
+            for (int u = 0; u < kResolveStreams; ++u) near[u] = c0 + u * kResolveThreads < ce && m.near(a, ot[u]);
+#pragma unroll
+            for (int u = 0; u < kResolveStreams; ++u) {
+                if (!near[u]) continue;
                 const uint32_t pos = atomicAdd(&s_nrel, 1u);
-                if (pos < uint32_t(kResolveList)) s_list[pos] = ot;
+                if (pos >= uint32_t(kResolveList)) continue;
+                double sh[3];
+                bool clean;
+                tile_pair_shift(A, G.tbox + 6 * int64_t(ot[u]), G.L, sh, &clean);
+                const uint32_t sc = uint32_t(G.sub_cnt[ot[u]]);
+                atomicAdd(&s_npart, sc);
+                uint32_t pk = (sc << 24) | (clean ? 0x80000000u : 0u);
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    if (G.L[k] > 0.0) pk |= (uint32_t(int(rint(sh[k] / G.L[k]))) & 255u) << (8 * k);
+                s_start[pos] = uint32_t(G.sub_start[ot[u]]);
+                s_info[pos] = pk;
             }
         }
         __syncthreads();
         const uint32_t nrel = s_nrel;
-        const bool use_list = nrel <= uint32_t(kResolveList);
-        const uint32_t nl = use_list ? nrel : uint32_t(ce - cb);
-        // prefix sums of particle counts over the kept sub-tiles (nl <= kResolveList):
-        // counts loaded in parallel, each thread sums a contiguous run, the
-        // run totals are scanned in LDS
-        if (use_list) {
-            for (uint32_t q = tid; q < nl; q += kResolveThreads) s_pre[q] = G.sub_cnt[s_list[q]];
-            __syncthreads();
-            const uint32_t per = (nl + kResolveThreads - 1) / kResolveThreads;
-            const uint32_t q0 = min(nl, uint32_t(tid) * per), q1 = min(nl, q0 + per);
-            uint32_t run = 0;
-            for (uint32_t q = q0; q < q1; ++q) run += s_pre[q];
-            s_run[tid] = run;
-            __syncthreads();
-            for (int d = 1; d < kResolveThreads; d <<= 1) {
-                const unsigned long long y = tid >= d ? s_run[tid - d] : 0ull;
-                __syncthreads();
-                s_run[tid] += y;
-                __syncthreads();
-            }
-            uint32_t acc = uint32_t(s_run[tid]) - run;
-            for (uint32_t q = q0; q < q1; ++q) {
-                const uint32_t v = s_pre[q];
-                s_pre[q] = acc;
-                acc += v;
-            }
-            if (tid == kResolveThreads - 1) s_pre[nl] = uint32_t(s_run[tid]);
-        }
-        __syncthreads();
-        // Pairs of this DM, enumerated over the flattened particles of the kept
-        // sub-tiles (all wavefronts of the block in parallel).  Without a list (too many
-        // candidates) every candidate sub-tile is walked by one wavefront.
-        auto for_pairs = [&](auto&& fn) {
-            auto visit = [&](uint32_t ot, int kk) {
-                double sh[3];
-                bool clean;
-                tile_pair_shift(A, G.tbox + 6 * int64_t(ot), G.L, sh, &clean);
-                if (kk < int(G.sub_cnt[ot])) {
-                    const int64_t k = int64_t(G.sub_start[ot]) + kk;
-                    const double px = G.tx[k] + sh[0], py = G.ty[k] + sh[1], pz = G.tz[k] + sh[2];
-                    const double d2 = pair_d2(mx, my, mz, px, py, pz, clean, G.L);
-                    const double hs = mh + G.th[k];
-                    if (d2 < hs * hs) {
-                        const GasRec<Real> r = reinterpret_cast<const GasRec<Real>*>(a.grec)[k];
-                        const uint32_t gid = r.perm;
-                        auto g = [&] { return pair_g<Real, EXACT_G>(a.gtab, d2, mh, G.th[k]); };
-                        double P;
-                        if constexpr (RB) {
-                            P = double(pair_Pbar<Real, N>(g, mvx, mvy, mvz, r.Vx, r.Vy, r.Vz, r.vs, r.K, mdt));
-                        } else {
-                            const U4 rnd = philox_block(oid, gid, step, kTagGasVel, a.box, a.k0, a.k1);
-                            P = double(pair_P<Real, N>(g, mvx, mvy, mvz, r.Vx, r.Vy, r.Vz, r.vs, r.K, mdt, rnd));
-                        }
-                        fn(gid, P);
-                    }
-                }
-            };
-            if (use_list) {
-                const uint32_t np = s_pre[nl];
-                for (uint32_t pos = tid; pos < np; pos += kResolveThreads) {
-                    uint32_t lo = 0, hi = nl;  // largest q with s_pre[q] <= pos
-                    while (hi - lo > 1) {
-                        const uint32_t mid = (lo + hi) >> 1;
-                        if (s_pre[mid] <= pos) lo = mid; else hi = mid;
-                    }
-                    visit(s_list[lo], int(pos - s_pre[lo]));
-                }
-            } else {
-                const int w = tid >> 6, lane = tid & 63;
-                for (uint32_t q = w; q < nl; q += kResolveThreads / 64) visit(G.cand[cb + q], lane);
-            }
+        auto shifted = [&](uint32_t info, double X, double Y, double Z) {
+            const double px = X + double(int8_t(info)) * G.L[0], py = Y + double(int8_t(info >> 8)) * G.L[1],
+                         pz = Z + double(int8_t(info >> 16)) * G.L[2];
+            return pair_d2(m.x, m.y, m.z, px, py, pz, (info >> 31) != 0u, G.L);
         };
-        for_pairs([&](uint32_t gid, double P) {
-            const uint32_t pos = atomicAdd(&s_npairs, 1u);
-            if (pos < uint32_t(kResolvePairs)) { s_gid[pos] = gid; s_P[pos] = P; }
-        });
+        if (nrel <= uint32_t(kResolveList)) {
+            // 16 lanes per sub-tile, 32 where they are well filled (6 particles on average in a
+            // galaxy, 32 in a uniform box; whole wavefronts took 131 instead of 89 us for the
+            // search of 411 DM among 40k gas particles), kResolveStreams at a time
+            const uint32_t lw = s_npart > 12u * nrel ? 5u : 4u, ngrp = 64u >> lw;
+            const uint32_t sub = uint32_t(lane) >> lw, ll = uint32_t(lane) & ((1u << lw) - 1u);
+            const uint32_t per = ngrp * kResolveStreams;
+            for (uint32_t q0 = uint32_t(w) * per; q0 < nrel; q0 += per * kResolveWaves) {
+                uint32_t info[kResolveStreams], start[kResolveStreams], cnt[kResolveStreams];
+                uint32_t most = 0u;
+#pragma unroll
+                for (int u = 0; u < kResolveStreams; ++u) {
+                    const uint32_t q = q0 + ngrp * u + sub, qq = min(q, nrel - 1u);
+                    info[u] = s_info[qq];
+                    start[u] = s_start[qq];
+                    cnt[u] = q < nrel ? (info[u] >> 24) & 127u : 0u;
+                    most = max(most, cnt[u]);
+                }
+                for (uint32_t k0 = 0; __ballot(k0 < most); k0 += 1u << lw) {
+                    double X[kResolveStreams], Y[kResolveStreams], Z[kResolveStreams], H[kResolveStreams];
+                    const uint32_t kk = k0 + ll;
+#pragma unroll
+                    for (int u = 0; u < kResolveStreams; ++u) {
+                        const int64_t k = int64_t(start[u]) + (kk < cnt[u] ? kk : 0u);
+                        X[u] = G.tx[k]; Y[u] = G.ty[k]; Z[u] = G.tz[k]; H[u] = G.th[k];
+                    }
+#pragma unroll
+                    for (int u = 0; u < kResolveStreams; ++u) {
+                        const double hs = m.h + H[u];
+                        const bool hit = kk < cnt[u] && shifted(info[u], X[u], Y[u], Z[u]) < hs * hs;
+                        const uint64_t mk = __ballot(hit);
+                        if (!mk) continue;
+                        uint32_t base = 0u;
+                        if (lane == 0) base = atomicAdd(&s_npairs, uint32_t(__popcll(mk)));
+                        base = uint32_t(__builtin_amdgcn_readfirstlane(int(base)));
+                        const uint32_t pos = base + uint32_t(__popcll(mk & ((1ull << lane) - 1ull)));
+                        if (hit && pos < uint32_t(kResolvePairs)) s_gid[pos] = ((q0 + ngrp * u + sub) << 6) | kk;
+                    }
+                }
+            }
+        }
         __syncthreads();
         const uint32_t npairs = s_npairs;
-        const bool cached = npairs <= uint32_t(kResolvePairs);
-        const int npass = (a.n_gas_bits + 7) / 8;
-        uint32_t prefix = 0;
-        unsigned __int128 below = 0;
+        const bool cached = nrel <= uint32_t(kResolveList) && npairs <= uint32_t(kResolvePairs);
+        if (!cached && a.wide) {
+            if (tid == 0) s_wide = atomicAdd(a.wcount, 1u) + 1u;
+            __syncthreads();
+            const uint32_t ws = s_wide;
+            if (ws <= uint32_t(kResolveWide)) {
+                ResolveWide& W = a.wide[ws - 1u];
+                if (tid < 256) { W.hi[tid] = 0ull; W.lo[tid] = 0ull; }
+                if (tid == 0) { W.e = e; W.prefix = 0u; W.done = 0u; W.pass = 0u; W.below[0] = 0ull; W.below[1] = 0ull; }
+                __syncthreads();
+                continue;
+            }
+        }
+        if (cached) {
+            for (uint32_t p = tid; p < npairs; p += kResolveThreads) {
+                const uint32_t key = s_gid[p], info = s_info[key >> 6];
+                const int64_t k = int64_t(s_start[key >> 6]) + (key & 63u);
+                const double gh = G.th[k], d2 = shifted(info, G.tx[k], G.ty[k], G.tz[k]);
+                uint32_t gid;
+                s_P[p] = resolve_P<Real, N, EXACT_G, RB>(a, m, step, k, d2, gh, &gid);
+                s_gid[p] = gid;
+            }
+        }
+        uint32_t prefix = 0u;
+        unsigned __int128 below = 0, after = 0;    // wavefront 0
         for (int ps = 0; ps < npass; ++ps) {
             const int shft = 8 * (npass - 1 - ps);
-            hhi[tid & 255] = 0ull;
-            hlo[tid & 255] = 0ull;
+            if (tid < 256) { hhi[tid] = 0ull; hlo[tid] = 0ull; }
             __syncthreads();
-            auto add = [&](uint32_t gid, double P) {
-                if ((uint64_t(gid) >> (shft + 8)) == uint64_t(prefix)) {
-                    unsigned long long hi, lo;
-                    fixed_split(P, &hi, &lo);
-                    const int dg = (gid >> shft) & 255u;
-                    atomicAdd(&hhi[dg], hi);
-                    atomicAdd(&hlo[dg], lo);
-                }
-            };
             if (cached) {
-                for (uint32_t q = tid; q < npairs; q += kResolveThreads) add(s_gid[q], s_P[q]);
+                for (uint32_t p = tid; p < npairs; p += kResolveThreads)
+                    hist_add(hhi, hlo, shft, prefix, s_gid[p], s_P[p]);
             } else {
-                for_pairs(add);
-            }
-            // the selected bin: the first whose running sum (from `below`) passes
-            // U_i, by an inclusive scan over the 256 bins (thread = bin)
-            if (tid == 0) { s_found = 0; s_lastnz = -1; }
-            __syncthreads();
-            const int bt = tid & 255;
-            const unsigned __int128 v = ((unsigned __int128)hhi[bt] << 32) + (unsigned __int128)hlo[bt];
-            if (bin_owner) {
-                s_cum[tid] = v;
-                if (v != 0) atomicMax(&s_lastnz, tid);
+                resolve_walk<Real, N, EXACT_G, RB>(a, m, step, lane, uint64_t(w), uint64_t(kResolveWaves),
+                                                   [&](uint32_t gid, double P) { hist_add(hhi, hlo, shft, prefix, gid, P); });
             }
             __syncthreads();
-            for (int d = 1; d < 256; d <<= 1) {
-                const unsigned __int128 y = bin_owner && tid >= d ? s_cum[tid - d] : (unsigned __int128)0;
-                __syncthreads();
-                if (bin_owner) s_cum[tid] += y;
-                __syncthreads();
-            }
-            const unsigned __int128 incl = below + s_cum[bt], excl = incl - v;
-            if (bin_owner && excl <= Ufix && incl > Ufix) {      // unique: running sums increase, empty bins cannot pass
-                s_found = 1;
-                s_sel = uint32_t(tid);
-                s_selb = excl;
-                s_sela = incl;
+            if (w == 0) {
+                unsigned __int128 v[4], b4;
+                for (int k = 0; k < 4; ++k)
+                    v[k] = ((unsigned __int128)hhi[4 * lane + k] << 32) + (unsigned __int128)hlo[4 * lane + k];
+                const uint32_t sel = radix_pick(lane, v, below, m.U, &b4, &after);
+                below = b4;
+                if (lane == 0) s_prefix = (prefix << 8) | sel;
             }
             __syncthreads();
-            if (tid == 0 && !s_found) {   // rounding guard: keep the largest index with P > 0
-                s_sel = uint32_t(s_lastnz < 0 ? 0 : s_lastnz);
-                s_selb = below;
-                s_sela = below + s_cum[255];
-            }
-            __syncthreads();
-            below = s_selb;
-            if (tid == 0 && ps == npass - 1) {
-                // running sums adjacent to U_i (relative 1e-6 band)
-                double Ud = double(Ufix) * 0x1p-64, Sb = double(s_selb) * 0x1p-64, Sa = double(s_sela) * 0x1p-64;
-                s_near = (fabs(Sb - Ud) <= 1e-6 * Ud || fabs(Sa - Ud) <= 1e-6 * Ud) ? 1 : 0;
-            }
-            __syncthreads();
-            prefix = (prefix << 8) | s_sel;
-            __syncthreads();
+            prefix = s_prefix;
         }
+        if (tid == 0) resolve_finish<Real, RB>(a, m, step, prefix, below, after);
+    }
+}
+
+// The DM on the wide list.  Each radix pass of a DM is split into as many slices of
+// its candidates (strided, so that near and far ones mix) as the grid has blocks
+// for; a slice's histogram is summed in LDS and added to the DM's, and the last
+// slice to finish picks the digit and clears the histogram for the next pass.
+// Blocks take (pass, DM, slice) by tickets, pass by pass, so a block only ever waits
+// for the digit of a pass whose slices are all held by running blocks; the wait is
+// still bounded (kResolveSpinMax polls, then an error flag is raised).
+template <typename Real, int N, bool EXACT_G, bool RB = false, bool BATCH = false>
+__global__ __launch_bounds__(kResolveThreads) void k_resolve_wide(ResolveArgs a0, const ResolveArgs* __restrict__ boxes)
+{
+    __shared__ unsigned long long hhi[256], hlo[256];
+    __shared__ uint32_t s_last, s_ticket, s_prefix;
+    const ResolveArgs& a = BATCH ? boxes[blockIdx.y] : a0;
+    if (!a.wide) return;
+    const uint32_t nw = min(*a.wcount, uint32_t(kResolveWide));
+    if (nw == 0u) return;
+    const int npass = (a.n_gas_bits + 7) / 8;
+    const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t step = a.step + (a.step_off ? *a.step_off : 0u);
+    const uint32_t S = max(1u, gridDim.x / nw), per = nw * S;
+    for (;;) {
+        if (tid == 0) s_ticket = atomicAdd(a.wcount + 1, 1u);
+        __syncthreads();
+        const uint32_t tk = s_ticket;
+        if (tk >= uint32_t(npass) * per) return;
+        const uint32_t ps = tk / per, u = tk % per, slice = u % S;
+        ResolveWide& W = a.wide[u / S];
         if (tid == 0) {
-            const uint32_t j = prefix < a.n_gas ? prefix : a.n_gas - 1u;
-            nnearD += uint32_t(s_near);
-            if constexpr (RB) {
-                a.partner[oid] = int32_t(j);   // the kick follows in k_rb_kick
-            } else {
-                // the partner's gas-velocity sample from the same uniforms as its P_ij (tag 0),
-                // and the kick, in binary64 in either precision: one thread per scattering DM
-                const double vs = sqrt(2.0 * a.gas_u[j] / 3.0);
-                U4 r = philox_block(oid, j, step, kTagGasVel, a.box, a.k0, a.k1);
-                double z[3];
-                normals3<double>(r, z);
-                const double ux = (mvx - a.gas_vel[3 * int64_t(j)]) - vs * z[0];
-                const double uy = (mvy - a.gas_vel[3 * int64_t(j) + 1]) - vs * z[1];
-                const double uz = (mvz - a.gas_vel[3 * int64_t(j) + 2]) - vs * z[2];
-                scatter_kick<double>(a, oid, j, step, ux, uy, uz);
+            uint32_t polls = 0;
+            while (__hip_atomic_load(&W.pass, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < ps) {
+                if (++polls == kResolveSpinMax) { atomicOr(a.err, 1u); break; }
+                __builtin_amdgcn_s_sleep(1);
             }
+            s_prefix = __hip_atomic_load(&W.prefix, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (tid < 256) { hhi[tid] = 0ull; hlo[tid] = 0ull; }
+        __syncthreads();
+        const int shft = 8 * (npass - 1 - int(ps));
+        const uint32_t prefix = s_prefix;
+        const ResolveDm<Real> m(a, W.e, step);
+        resolve_walk<Real, N, EXACT_G, RB>(a, m, step, lane, uint64_t(slice) * kResolveWaves + w, uint64_t(S) * kResolveWaves,
+                                           [&](uint32_t gid, double P) { hist_add(hhi, hlo, shft, prefix, gid, P); });
+        __syncthreads();
+        if (tid < 256) {
+            if (hhi[tid]) atomicAdd(&W.hi[tid], hhi[tid]);
+            if (hlo[tid]) atomicAdd(&W.lo[tid], hlo[tid]);
+        }
+        __threadfence();
+        __syncthreads();
+        if (tid == 0) s_last = atomicAdd(&W.done, 1u) == S - 1u ? 1u : 0u;
+        __syncthreads();
+        if (s_last && w == 0) {
+            __threadfence();
+            unsigned __int128 v[4], below, before, after;
+            for (int k = 0; k < 4; ++k) {   // read and cleared where the adds were made
+                const uint64_t hi = atomicExch(&W.hi[4 * lane + k], 0ull), lo = atomicExch(&W.lo[4 * lane + k], 0ull);
+                v[k] = ((unsigned __int128)hi << 32) + (unsigned __int128)lo;
+            }
+            const uint64_t b0 = __hip_atomic_load(&W.below[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t b1 = __hip_atomic_load(&W.below[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            below = ((unsigned __int128)b1 << 64) | b0;
+            const uint32_t sel = radix_pick(lane, v, below, m.U, &before, &after), pf = (prefix << 8) | sel;
+            if (lane == 0) {
+                __hip_atomic_store(&W.prefix, pf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&W.below[0], (unsigned long long)before, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&W.below[1], (unsigned long long)(before >> 64), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&W.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (int(ps) == npass - 1) resolve_finish<Real, RB>(a, m, step, pf, before, after);
+            }
+            __threadfence();
+            if (lane == 0) __hip_atomic_store(&W.pass, ps + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         }
         __syncthreads();
     }
-    if (tid == 0 && nnearD) atomicAdd((unsigned long long*)&a.counters[4], (unsigned long long)nnearD);
 }
 
 // Kicks of the Rao-Blackwellised scheme, after k_resolve has chosen the
@@ -2756,9 +2959,10 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(ResolveArgs a)
 // its pair from the tilted law (tag 5: radius, cosine to w, azimuth),
 // u = vs r (c e + s (cos phi e1 + sin phi e2)), e = w/|w| (the z axis if
 // w = 0; cold gas: u = w), and applies the kick, all in binary64.
-template <typename Real, int N>
-__global__ __launch_bounds__(64) void k_rb_kick(ResolveArgs a)
+template <typename Real, int N, bool BATCH = false>
+__global__ __launch_bounds__(64) void k_rb_kick(ResolveArgs a0, const ResolveArgs* __restrict__ boxes)
 {
+    const ResolveArgs& a = BATCH ? boxes[blockIdx.y] : a0;
     __shared__ double s_cell[kTiltCells];
     __shared__ double s_gl[32];
     const int lane = int(threadIdx.x);
