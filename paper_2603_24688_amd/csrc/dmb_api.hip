@@ -2188,7 +2188,7 @@ dmb_status dmb_mlp_grad(dmb_ctx* c, int64_t n, const double* x, const double* y,
     MlpGradArgs g;
     g.ts = c->mlp_ts.as<const float4>(); g.n_total = n; g.batch = n; g.epoch = nullptr; g.shuffle = nullptr;
     g.step = 0; g.W = c->mlp_blob.as<const MlpBlob>(); g.part = c->mlp_part.as<float>();
-    hipLaunchKernelGGL(k_mlp_grad, dim3(unsigned(nblk)), dim3(64), 0, c->stream, g);
+    hipLaunchKernelGGL(k_mlp_grad, dim3(unsigned(nblk)), dim3(64 * kMlpGradWaves), 0, c->stream, g);
     hipLaunchKernelGGL(k_mlp_reduce, dim3(blocks_for(kMlpParams + 1, 256)), dim3(256), 0, c->stream,
                        c->mlp_part.as<const float>(), int(nblk), c->mlp_red.as<float>());
     HIPCHK(c, hipGetLastError());
@@ -2255,8 +2255,8 @@ dmb_status dmb_mlp_train(dmb_ctx* c, int64_t n, const double* x, const double* y
         for (int64_t k = 0; k < S; ++k) {
             g.step = k;
             a.step = k;
-            hipLaunchKernelGGL(k_mlp_grad, dim3(unsigned(nblk)), dim3(64), 0, ts, g);
-            hipLaunchKernelGGL(k_mlp_adam, dim3(blocks_for(kMlpParams + 1, 256)), dim3(256), 0, ts, a);
+            hipLaunchKernelGGL(k_mlp_grad, dim3(unsigned(nblk)), dim3(64 * kMlpGradWaves), 0, ts, g);
+            hipLaunchKernelGGL(k_mlp_adam, dim3(blocks_for(kMlpParams + 1, 64)), dim3(64), 0, ts, a);
         }
         hipLaunchKernelGGL(k_mlp_tick, dim3(1), dim3(1), 0, ts, c->mlp_epoch.as<uint32_t>());
     };

@@ -152,13 +152,11 @@ __device__ __forceinline__ float mlp_input(float u) { return 2.f * u / (u + kMlp
 // network outputs of the lane's own column.  All 64 lanes must be active.
 // The four column blocks go through the layers NB at a time (NB = 4 loads
 // each weight fragment once; NB = 2 halves the live accumulators).
-// If `act` is non-null the bfloat16 activations of layers 1..3 are kept
-// there: act[layer][block][step] (B-operand layout of the lane).
 // NBLK < 4 evaluates only the first NBLK column blocks (lanes 0 .. 16 NBLK - 1);
 // the other lanes return 0.
 template <int NB = 4, int NBLK = 4>
 __device__ __forceinline__ void mlp_forward64(const MlpBlob* __restrict__ W, float s_in, int nidx, float* yA,
-                                              float* yB, uint4 (*act)[4][2] = nullptr)
+                                              float* yB)
 {
     static_assert(NB == 1 || NB == 2 || NB == 4, "column blocks per round");
     const int l = threadIdx.x & 63, h = l >> 4, c = l & 15;
@@ -184,7 +182,6 @@ __device__ __forceinline__ void mlp_forward64(const MlpBlob* __restrict__ W, flo
         for (int b = 0; b < NB; ++b) {
             Bx[b][0] = act_frag(D[b][0], D[b][1]);
             Bx[b][1] = act_frag(D[b][2], D[b][3]);
-            if (act) { act[0][NB * r + b][0] = Bx[b][0]; act[0][NB * r + b][1] = Bx[b][1]; }
         }
         // layers 2 and 3 (16x16x32)
 #pragma unroll
@@ -205,7 +202,6 @@ __device__ __forceinline__ void mlp_forward64(const MlpBlob* __restrict__ W, flo
             for (int b = 0; b < NB; ++b) {
                 Bx[b][0] = act_frag(D[b][0], D[b][1]);
                 Bx[b][1] = act_frag(D[b][2], D[b][3]);
-                if (act) { act[layer + 1][NB * r + b][0] = Bx[b][0]; act[layer + 1][NB * r + b][1] = Bx[b][1]; }
             }
         }
         // output layer: rows 0 and 1 of a 16-row block, read back by the
@@ -222,6 +218,43 @@ __device__ __forceinline__ void mlp_forward64(const MlpBlob* __restrict__ W, flo
     }
     *yA = oA;
     *yB = oB;
+}
+
+// One column block (16 of the wave's 64 samples: 16 blk + lane % 16) for the training,
+// with the bfloat16 activations of layers 1..3 kept: act[layer][step] (B-operand layout
+// of the lane).  Every lane returns the outputs of its column.
+__device__ __forceinline__ void mlp_forward16(const MlpBlob* __restrict__ W, float s_in, int nidx, int blk, float* yA,
+                                              float* yB, uint4 (*act)[2])
+{
+    const int l = threadIdx.x & 63, h = l >> 4, c = l & 15;
+    f32x4 D[4];
+    const uint2 B1 = input_frag(__shfl(s_in, 16 * blk + c), __shfl(nidx, 16 * blk + c), h);
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb)
+        D[mb] = mfma16(*reinterpret_cast<const uint2*>(&W->w1[16 * mb + c][4 * h]), B1,
+                       *reinterpret_cast<const f32x4*>(&W->b1[16 * mb + 4 * h]));
+    act[0][0] = act_frag(D[0], D[1]);
+    act[0][1] = act_frag(D[2], D[3]);
+#pragma unroll
+    for (int layer = 0; layer < 2; ++layer) {
+        const uint16_t(*w)[kMlpH] = layer == 0 ? W->w2 : W->w3;
+        const float* bias = layer == 0 ? W->b2 : W->b3;
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb) {
+            const f32x4 C = *reinterpret_cast<const f32x4*>(&bias[16 * mb + 4 * h]);
+            const uint4 A0 = *reinterpret_cast<const uint4*>(&w[16 * mb + c][8 * h]);
+            const uint4 A1 = *reinterpret_cast<const uint4*>(&w[16 * mb + c][32 + 8 * h]);
+            D[mb] = mfma32(A1, act[layer][1], mfma32(A0, act[layer][0], C));
+        }
+        act[layer + 1][0] = act_frag(D[0], D[1]);
+        act[layer + 1][1] = act_frag(D[2], D[3]);
+    }
+    const f32x4 C4 = *reinterpret_cast<const f32x4*>(&W->b4[4 * h]);
+    const uint4 A0 = *reinterpret_cast<const uint4*>(&W->w4[c][8 * h]);
+    const uint4 A1 = *reinterpret_cast<const uint4*>(&W->w4[c][32 + 8 * h]);
+    const f32x4 O = mfma32(A1, act[2][1], mfma32(A0, act[2][0], C4));
+    *yA = __shfl(O[0], c);
+    *yB = __shfl(O[1], c);
 }
 
 // q^{K/4} for the odd K the base functions need.
@@ -405,6 +438,10 @@ __global__ __launch_bounds__(64) void k_mlp_eval(int64_t n, const double* x, con
 // Writes this block's gradient and loss terms to part[block][0..kMlpParams].
 // Sample g of the batch is training sample (mul * (step * batch + g) + add) mod n;
 // mul, add come from shuffle[epoch] (identity when shuffle is null).
+// Bound by latency: a batch of 4096 is 64 blocks.  Four wavefronts share a slice, a
+// column block of samples each in the forward pass, a row block of units in the
+// products of the backward pass, one of the sums over samples each in between; every
+// sum keeps its order, so the result is that of one wavefront.
 struct MlpGradArgs {
     const float4* ts; int64_t n_total;
     int64_t batch;              // samples in the minibatch (loss normalisation)
@@ -417,13 +454,15 @@ struct MlpGradArgs {
 
 constexpr int kMlpLd = kMlpH + 1;   // padded LDS row
 
-__global__ __launch_bounds__(64) void k_mlp_grad(MlpGradArgs a)
+constexpr int kMlpGradWaves = 4;
+
+__global__ __launch_bounds__(64 * kMlpGradWaves) void k_mlp_grad(MlpGradArgs a)
 {
     __shared__ float F[3][kMlpWave][kMlpLd];    // activations a1..a3, [sample][unit]
     __shared__ float G[2][kMlpWave][kMlpLd];    // error signals, [sample][unit]
-    __shared__ float E[kMlpWave][2], S[kMlpWave];
+    __shared__ float E[kMlpWave][2], S[kMlpWave], Ls[kMlpWave];
     __shared__ int NI[kMlpWave];
-    const int l = threadIdx.x, h = l >> 4, c = l & 15;
+    const int l = threadIdx.x & 63, w = int(threadIdx.x) >> 6, h = l >> 4, c = l & 15;
     float* out = a.part + int64_t(blockIdx.x) * (kMlpParams + 1);
     const int64_t g = int64_t(blockIdx.x) * kMlpWave + l;
     const bool ok = g < a.batch;
@@ -440,18 +479,16 @@ __global__ __launch_bounds__(64) void k_mlp_grad(MlpGradArgs a)
         smp = a.ts[idx];
     }
     const int nidx = int(smp.y);
-    uint4 act[3][4][2];
+    uint4 act[3][2];
     float oA, oB;
-    mlp_forward64(a.W, smp.x, nidx, &oA, &oB, act);
-    // loss terms and output error
+    mlp_forward16(a.W, smp.x, nidx, w, &oA, &oB, act);
     const float ls2 = kMlpLossScale * kMlpLossScale;
-    const float rA = ok ? oA - smp.z : 0.f, rB = ok ? oB - smp.w : 0.f;
-    float lsum = 0.5f * ls2 * (rA * rA + rB * rB) / float(a.batch);
-    for (int d = 32; d >= 1; d >>= 1) lsum += __shfl_xor(lsum, d);
-    if (l == 0) out[kMlpParams] = lsum;
-    E[l][0] = ls2 * rA / float(a.batch);
-    E[l][1] = ls2 * rB / float(a.batch);
-    {
+    if (h == w) {
+        // loss terms and output error of this wavefront's samples
+        const float rA = ok ? oA - smp.z : 0.f, rB = ok ? oB - smp.w : 0.f;
+        Ls[l] = 0.5f * ls2 * (rA * rA + rB * rB) / float(a.batch);
+        E[l][0] = ls2 * rA / float(a.batch);
+        E[l][1] = ls2 * rB / float(a.batch);
         const uint32_t hi16 = bf16_bits(smp.x);
         S[l] = bf16_float(hi16) + bf16_round(smp.x - bf16_float(hi16));
         NI[l] = nidx;
@@ -460,40 +497,48 @@ __global__ __launch_bounds__(64) void k_mlp_grad(MlpGradArgs a)
 #pragma unroll
     for (int ly = 0; ly < 3; ++ly)
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+        for (int st = 0; st < 2; ++st) {
+            const uint4 v = act[ly][st];
+            const uint32_t u[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-            for (int st = 0; st < 2; ++st) {
-                const uint4 v = act[ly][b][st];
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    F[ly][16 * b + c][mlp_nu(32 * st + 8 * h + j)] = bf16_float((w[j >> 1] >> (16 * (j & 1))) & 0xFFFFu);
-            }
+            for (int j = 0; j < 8; ++j)
+                F[ly][16 * w + c][mlp_nu(32 * st + 8 * h + j)] = bf16_float((u[j >> 1] >> (16 * (j & 1))) & 0xFFFFu);
+        }
     __syncthreads();
     // output layer (lane = unit): dW4, db4, and the layer-3 error
     {
-        float g0 = 0.f, g1 = 0.f, db = 0.f;
         const float w0 = a.W->w4f[0][l], w1 = a.W->w4f[1][l];
-        for (int b = 0; b < kMlpWave; ++b) {
+        auto err3 = [&](int b) {
             const float e0 = E[b][0], e1 = E[b][1], x = F[2][b][l];
-            g0 += e0 * x;
-            g1 += e1 * x;
-            const float d = x > 0.f ? e0 * w0 + e1 * w1 : 0.f;
-            G[0][b][l] = d;
-            db += d;
-        }
-        out[kOffW4 + l] = g0;
-        out[kOffW4 + kMlpH + l] = g1;
-        out[kOffB3 + l] = db;
-        if (l < 2) {
-            float s = 0.f;
-            for (int b = 0; b < kMlpWave; ++b) s += E[b][l];
-            out[kOffB4 + l] = s;
+            return x > 0.f ? e0 * w0 + e1 * w1 : 0.f;
+        };
+#pragma unroll
+        for (int b = 16 * w; b < 16 * w + 16; ++b) G[0][b][l] = err3(b);
+        if (w < 2) {
+            float g0 = 0.f;
+#pragma unroll 16
+            for (int b = 0; b < kMlpWave; ++b) g0 += E[b][w] * F[2][b][l];
+            out[kOffW4 + w * kMlpH + l] = g0;
+        } else if (w == 2) {
+            float db = 0.f;
+#pragma unroll 16
+            for (int b = 0; b < kMlpWave; ++b) db += err3(b);
+            out[kOffB3 + l] = db;
+        } else {
+            float lsum = Ls[l];
+            for (int d = 32; d >= 1; d >>= 1) lsum += __shfl_xor(lsum, d);
+            if (l == 0) out[kMlpParams] = lsum;
+            if (l < 2) {
+                float s = 0.f;
+#pragma unroll 16
+                for (int b = 0; b < kMlpWave; ++b) s += E[b][l];
+                out[kOffB4 + l] = s;
+            }
         }
     }
     __syncthreads();
     // layers 3 and 2: weight gradient (MFMA over samples), then the error of
-    // the layer below (MFMA over units)
+    // the layer below (MFMA over units); this wavefront's rows are 16 w ... 16 w + 15
 #pragma unroll 1
     for (int ly = 1; ly >= 0; --ly) {
         const float(*Gi)[kMlpLd] = G[(1 - ly) & 1];     // error of layer ly+2: ly=1 -> G[0], ly=0 -> G[1]
@@ -501,92 +546,73 @@ __global__ __launch_bounds__(64) void k_mlp_grad(MlpGradArgs a)
         const float(*Fin)[kMlpLd] = F[ly];               // input activations of layer ly+2
         const int offW = ly == 1 ? kOffW3 : kOffW2;
         const uint16_t(*wt)[kMlpH] = ly == 1 ? a.W->w3t : a.W->w2t;
+        auto pack8 = [](const float* v) {
+            return make_uint4(bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3]), bf16_pack2(v[4], v[5]),
+                              bf16_pack2(v[6], v[7]));
+        };
         // dW[out][in] = sum_samples q(err[s][out]) act[s][in]
-        f32x4 D[4][4];
+        f32x4 D[4];
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < 4; ++nb) D[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int nb = 0; nb < 4; ++nb) D[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int st = 0; st < 2; ++st) {
-            uint4 Af[4], Bf[4];
+            float v[8];
 #pragma unroll
-            for (int mb = 0; mb < 4; ++mb) {
-                float v[8];
+            for (int j = 0; j < 8; ++j) v[j] = Gi[32 * st + 8 * h + j][16 * w + c];
+            const uint4 Af = pack8(v);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) v[j] = Gi[32 * st + 8 * h + j][16 * mb + c];
-                Af[mb] = make_uint4(bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3]), bf16_pack2(v[4], v[5]),
-                                    bf16_pack2(v[6], v[7]));
+            for (int nb = 0; nb < 4; ++nb) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) v[j] = Fin[32 * st + 8 * h + j][16 * mb + c];
-                Bf[mb] = make_uint4(bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3]), bf16_pack2(v[4], v[5]),
-                                    bf16_pack2(v[6], v[7]));
+                for (int j = 0; j < 8; ++j) v[j] = Fin[32 * st + 8 * h + j][16 * nb + c];
+                D[nb] = mfma32(Af, pack8(v), D[nb]);
             }
-#pragma unroll
-            for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-                for (int nb = 0; nb < 4; ++nb) D[mb][nb] = mfma32(Af[mb], Bf[nb], D[mb][nb]);
         }
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
+        for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) out[offW + (16 * mb + 4 * h + i) * kMlpH + 16 * nb + c] = D[mb][nb][i];
+            for (int i = 0; i < 4; ++i) out[offW + (16 * w + 4 * h + i) * kMlpH + 16 * nb + c] = D[nb][i];
         // err_below[s][unit] = (sum_k q(W)[k][unit] q(err[s][k])) * [act[s][unit] > 0]
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < 4; ++nb) D[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int nb = 0; nb < 4; ++nb) D[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int st = 0; st < 2; ++st) {
-            uint4 Bf[4];
+            const uint4 A = *reinterpret_cast<const uint4*>(&wt[16 * w + c][32 * st + 8 * h]);
 #pragma unroll
             for (int nb = 0; nb < 4; ++nb) {
                 float v[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) v[j] = Gi[16 * nb + c][mlp_nu(32 * st + 8 * h + j)];
-                Bf[nb] = make_uint4(bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3]), bf16_pack2(v[4], v[5]),
-                                    bf16_pack2(v[6], v[7]));
-            }
-#pragma unroll
-            for (int mb = 0; mb < 4; ++mb) {
-                const uint4 A = *reinterpret_cast<const uint4*>(&wt[16 * mb + c][32 * st + 8 * h]);
-#pragma unroll
-                for (int nb = 0; nb < 4; ++nb) D[mb][nb] = mfma32(A, Bf[nb], D[mb][nb]);
+                D[nb] = mfma32(A, pack8(v), D[nb]);
             }
         }
-        __syncthreads();
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
+        for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int u = 16 * mb + 4 * h + i, smp_i = 16 * nb + c;
-                    Go[smp_i][u] = Fin[smp_i][u] > 0.f ? D[mb][nb][i] : 0.f;
-                }
+            for (int i = 0; i < 4; ++i) {
+                const int u = 16 * w + 4 * h + i, smp_i = 16 * nb + c;
+                Go[smp_i][u] = Fin[smp_i][u] > 0.f ? D[nb][i] : 0.f;
+            }
         __syncthreads();
         // bias gradient of layer ly+1 (lane = unit)
-        float db = 0.f;
-        for (int b = 0; b < kMlpWave; ++b) db += Go[b][l];
-        out[(ly == 1 ? kOffB2 : kOffB1) + l] = db;
-        __syncthreads();
+        if (w == ly) {
+            float db = 0.f;
+#pragma unroll 16
+            for (int b = 0; b < kMlpWave; ++b) db += Go[b][l];
+            out[(ly == 1 ? kOffB2 : kOffB1) + l] = db;
+        }
     }
     // layer 1 weights (lane = unit): inputs (s, one-hot n)
     {
-        float gs = 0.f, gn[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int b = 0; b < kMlpWave; ++b) {
-            const float d = G[0][b][l];
-            gs += d * S[b];
-            const int k = NI[b];
-            gn[0] += k == 0 ? d : 0.f;
-            gn[1] += k == 1 ? d : 0.f;
-            gn[2] += k == 2 ? d : 0.f;
-            gn[3] += k == 3 ? d : 0.f;
+        float gn = 0.f;
+#pragma unroll 16
+        for (int b = 0; b < kMlpWave; ++b) gn += NI[b] == w ? G[0][b][l] : 0.f;
+        out[kOffW1 + l * kMlpIn + 1 + w] = gn;
+        if (w == 3) {
+            float gs = 0.f;
+#pragma unroll 16
+            for (int b = 0; b < kMlpWave; ++b) gs += G[0][b][l] * S[b];
+            out[kOffW1 + l * kMlpIn] = gs;
         }
-        out[kOffW1 + l * kMlpIn] = gs;
-        for (int k = 0; k < 4; ++k) out[kOffW1 + l * kMlpIn + 1 + k] = gn[k];
     }
 }
 
@@ -602,7 +628,10 @@ __global__ __launch_bounds__(256) void k_mlp_reduce(const float* part, int nblk,
 
 // Adam (Kingma & Ba 2015) on the binary32 master weights with a cosine
 // learning rate, then repacking of the bfloat16 weights.  The global step is
-// t = epoch * steps_per_epoch + step + 1.
+// t = epoch * steps_per_epoch + step + 1.  Bound by the latency of the partials
+// (64 rows for a batch of 4096): one wavefront per block spreads the 8834
+// parameters over 139 compute units, and 16 rows are loaded at a time and
+// added in order.
 struct MlpAdamArgs {
     float* p; float* m; float* v;
     const float* part; int nblk;
@@ -612,19 +641,33 @@ struct MlpAdamArgs {
     float* loss;                // [total_steps]
 };
 
-__global__ __launch_bounds__(256) void k_mlp_adam(MlpAdamArgs a)
+// part[0][i] + part[1][i] + ... in this order
+__device__ __forceinline__ float mlp_part_sum(const float* __restrict__ part, int nblk, int i)
 {
-    const int i = int(blockIdx.x) * 256 + int(threadIdx.x);
+    constexpr int kRows = 16;
+    float s = 0.f;
+    int b = 0;
+    for (; b + kRows <= nblk; b += kRows) {
+        float x[kRows];
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) x[k] = part[int64_t(b + k) * (kMlpParams + 1) + i];
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) s += x[k];
+    }
+    for (; b < nblk; ++b) s += part[int64_t(b) * (kMlpParams + 1) + i];
+    return s;
+}
+
+__global__ __launch_bounds__(64) void k_mlp_adam(MlpAdamArgs a)
+{
+    const int i = int(blockIdx.x) * 64 + int(threadIdx.x);
+    if (i > kMlpParams) return;
+    const float g = mlp_part_sum(a.part, a.nblk, i);
     const int64_t t = int64_t(a.epoch ? *a.epoch : 0u) * a.steps_per_epoch + a.step + 1;
     if (i == kMlpParams) {
-        float s = 0.f;
-        for (int b = 0; b < a.nblk; ++b) s += a.part[int64_t(b) * (kMlpParams + 1) + kMlpParams];
-        a.loss[t - 1] = s;
+        a.loss[t - 1] = g;
         return;
     }
-    if (i > kMlpParams) return;
-    float g = 0.f;
-    for (int b = 0; b < a.nblk; ++b) g += a.part[int64_t(b) * (kMlpParams + 1) + i];
     const float lr = a.lr_min + 0.5f * (a.lr0 - a.lr_min) *
                                     (1.f + cosf(3.14159265358979f * float(t - 1) / float(a.total_steps)));
     const float m = a.beta1 * a.m[i] + (1.f - a.beta1) * g;
