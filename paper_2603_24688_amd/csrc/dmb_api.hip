@@ -77,7 +77,7 @@ struct Cells {
     Species gas, dm;
     Pairs gp, dp;                          // gas owners x DM tiles; DM owners x gas tiles
     DevBuf part_gas, part_p, part_pm, part_nb, psum_own;
-    DevBuf qctr, slist, rwide;
+    DevBuf qctr, slist, mlist, rwide;
     int64_t built_ngas = -1, built_ndm = -1;
     const double* built_gas_pos = nullptr;
     const double* built_dm_pos = nullptr;
@@ -729,7 +729,7 @@ dmb_status gather_and_fill(dmb_ctx* c, Cells& X, const dmb_particles* gas, const
         ENSURE(c, X.part_pm, size_t(X.dp.nitems) * kTile * 4);
         ENSURE(c, X.part_nb, size_t(X.dp.nitems) * kTile);
         ENSURE(c, X.psum_own, size_t(D.n_own) * 8);
-        ENSURE(c, X.slist, size_t(D.n_own) * 4);
+        ENSURE(c, X.slist, size_t(D.n_own) * 4); ENSURE(c, X.mlist, size_t(D.n_own) * 4);
         if (resolve_may_widen(X)) ENSURE(c, X.rwide, kResolveWide * sizeof(ResolveWide));
     }
     auto gas_gather = [&] {
@@ -877,27 +877,31 @@ ResolveArgs resolve_args(dmb_ctx* c, Cells& X, const DmPassArgs& a, const dmb_pa
     r.scount = a.scount; r.slist = X.slist.as<const uint32_t>();
     r.wide = resolve_may_widen(X) ? X.rwide.as<ResolveWide>() : nullptr;
     r.wcount = const_cast<uint32_t*>(a.scount) + kQueueStride / 2;
+    r.mcount = r.wcount + 2; r.mlist = X.mlist.as<uint32_t>();
     r.err = c->os_err.as<uint32_t>();
     r.dv = out->dv_dm; r.partner = out->partner; r.counters = counters;
     return r;
 }
 
 // The partner resolve of one box (dev: null) or of all boxes of a batch (args in device memory);
-// wide: some DM may outgrow a block.
+// n_dm: the most DM that can scatter; wide: some DM may outgrow a block.
 template <typename Real, int N, bool RB, bool BATCH>
-void launch_resolve(dmb_ctx* c, const ResolveArgs& r, const ResolveArgs* dev, int nbox, bool wide)
+void launch_resolve(dmb_ctx* c, const ResolveArgs& r, const ResolveArgs* dev, int nbox, int64_t n_dm, bool wide)
 {
     constexpr bool kExact = sizeof(Real) == 8;
     Phase ph(c, DMB_PH_RESOLVE);
-    const dim3 grid(unsigned(std::max(8, c->num_cu * 2 / nbox)), unsigned(nbox));
-    hipLaunchKernelGGL((k_resolve<Real, N, kExact, RB, BATCH>), grid, dim3(kResolveThreads), 0, c->stream, r, dev);
+    auto grid = [&](int per_cu) { return dim3(unsigned(c->num_cu * per_cu)); };
+    if (n_dm > int64_t(kResolveMany))
+        hipLaunchKernelGGL((k_resolve<Real, N, kExact, RB, BATCH, true>), grid(8), dim3(64), 0, c->stream, r, dev,
+                           nbox);
+    hipLaunchKernelGGL((k_resolve<Real, N, kExact, RB, BATCH, false>), grid(2), dim3(kResolveThreads), 0, c->stream, r,
+                       dev, nbox);
     if (wide)
         hipLaunchKernelGGL((k_resolve_wide<Real, N, kExact, RB, BATCH>),
                            dim3(unsigned(std::max(8, c->num_cu / nbox)), unsigned(nbox)), dim3(kResolveThreads), 0,
                            c->stream, r, dev);
     if constexpr (RB)
-        hipLaunchKernelGGL((k_rb_kick<Real, N, BATCH>), dim3(unsigned(std::max(8, c->num_cu * 4 / nbox)), unsigned(nbox)),
-                           dim3(64), 0, c->stream, r, dev);
+        hipLaunchKernelGGL((k_rb_kick<Real, N, BATCH>), grid(4), dim3(64), 0, c->stream, r, dev, nbox);
 }
 
 template <typename Real, int N, bool RB>
@@ -906,7 +910,7 @@ void combine_dm_and_resolve(dmb_ctx* c, Cells& X, const DmPassArgs& a, const dmb
 {
     combine_dm(c, X, a, out, counters);
     const ResolveArgs r = resolve_args(c, X, a, gas, par, out, counters);
-    launch_resolve<Real, N, RB, false>(c, r, nullptr, 1, r.wide != nullptr);
+    launch_resolve<Real, N, RB, false>(c, r, nullptr, 1, X.dm.n_own, r.wide != nullptr);
 }
 
 // The DM pair pass of one step (RB: Rao-Blackwellised sampling, expected
@@ -1003,6 +1007,7 @@ struct BatchPlan {
     std::vector<GasPassArgs> ga;
     std::vector<DmPassArgs> da;
     std::vector<ResolveArgs> ra;
+    int64_t most_dm = 0;                   // active DM of the largest box
     bool resolve_wide = false;             // some box may need k_resolve_wide
     int nb_gas = 0, nb_dm = 0;
     bool rb = false;                       // Rao-Blackwellised DM sampling
@@ -1019,6 +1024,7 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
     P.da.resize(nbox);
     P.ra.resize(nbox);
     P.resolve_wide = false;
+    P.most_dm = 0;
     std::vector<int64_t> gi(nbox + 1, 0), di(nbox + 1, 0);
     // global queues (gas, DM), then the Philox step offset
     ENSURE(c, c->bstep, kQueueWords * sizeof(uint32_t));
@@ -1032,7 +1038,7 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
             ENSURE(c, X.part_pm, size_t(X.dp.nitems) * kTile * 4);
             ENSURE(c, X.part_nb, size_t(X.dp.nitems) * kTile);
             ENSURE(c, X.psum_own, size_t(X.dm.n_own) * 8);
-            ENSURE(c, X.slist, size_t(X.dm.n_own) * 4);
+            ENSURE(c, X.slist, size_t(X.dm.n_own) * 4); ENSURE(c, X.mlist, size_t(X.dm.n_own) * 4);
             if (resolve_may_widen(X)) ENSURE(c, X.rwide, kResolveWide * sizeof(ResolveWide));
         }
         ENSURE(c, X.qctr, kQueueWords * 4);
@@ -1052,6 +1058,7 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
         P.da[b] = dm_pass_args(c, X, par + b, out + b, counters, step_off);
         P.ra[b] = resolve_args(c, X, P.da[b], gas + b, par + b, out + b, counters);
         if (X.dp.nitems > 0 && P.ra[b].wide) P.resolve_wide = true;
+        P.most_dm = std::max(P.most_dm, X.dm.n_own);
         gi[b + 1] = gi[b] + X.gp.nitems;
         di[b + 1] = di[b] + X.dp.nitems;
     }
@@ -1099,7 +1106,7 @@ void batch_dm_side(dmb_ctx* c, dmb_out* out, const BatchPlan& P, const DmPassArg
         if (c->boxes[b]->dp.nitems > 0)
             combine_dm(c, *c->boxes[b], P.da[b], out + b, out[b].counters);
     launch_resolve<Real, N, RB, true>(c, P.ra[0], reinterpret_cast<const ResolveArgs*>(ddev + P.nbox), P.nbox,
-                                      P.resolve_wide);
+                                      P.most_dm * P.nbox, P.resolve_wide);
 }
 
 template <typename Real, int N, int RM>
@@ -1366,7 +1373,7 @@ void free_cells(Cells& X)
         for (DevBuf* b : all) fr(*b);
     }
     DevBuf* rest[] = {&X.part_gas, &X.part_p, &X.part_pm, &X.part_nb, &X.psum_own, &X.qctr, &X.slist,
-                      &X.rwide};
+                      &X.mlist, &X.rwide};
     for (DevBuf* b : rest) fr(*b);
 }
 

@@ -2391,7 +2391,7 @@ __global__ __launch_bounds__(64 * kCombineWaves) void k_combine_dm(DmCombineArgs
 // radix pass the last block of a DM to finish picks the digit.
 struct ResolveWide {              // state of one entry of that list
     unsigned long long hi[256], lo[256];
-    uint32_t e;                   // index into the scatter list
+    uint32_t s;                   // the DM's owner slot
     uint32_t prefix, done, pass;  // digits picked so far, slices finished in this pass, passes finished
     unsigned long long below[2];
 };
@@ -2410,6 +2410,7 @@ struct ResolveArgs {
     int n_gas_bits;
     uint32_t n_gas;
     const uint32_t* scount; const uint32_t* slist;
+    uint32_t* mcount; uint32_t* mlist;    // DM that the one-wavefront search passed on
     ResolveWide* wide; uint32_t* wcount;  // nullptr: no DM can outgrow the cache; entries, [1]: tickets
     uint32_t* err;                // raised if a wait gave up
     double* dv; int32_t* partner;
@@ -2555,11 +2556,17 @@ constexpr int kResolveThreads = 512;  // eight wavefronts: the most that leaves 
 constexpr int kResolveWaves = kResolveThreads / 64;
 constexpr int kResolveList = 2048;    // candidate sub-tiles kept per scattering DM after the point test
 constexpr int kResolvePairs = 8192;   // pairs cached per scattering DM (LDS; the registers allow one block per CU anyway)
+// Where more than kResolveMany DM scatter (two rounds of blocks), one wavefront per DM
+// comes first, eight to a CU, with a cache of kResolveFewPairs; it passes the larger
+// ones on; blocks share the DM of all boxes of a batch.  A step of eight boxes whose
+// sigma0 spans four decades: 3.1 -> 2.5 ms.
+constexpr uint32_t kResolveMany = 512;
+constexpr int kResolveFewList = 256, kResolveFewPairs = 1024;
 constexpr int kResolveWide = 256;     // DM spread over the chip (beyond these, enough blocks are busy anyway)
 constexpr int kResolveStreams = 4;    // sub-tiles a wavefront (candidates a thread) tests at a time
 constexpr uint32_t kResolveSpinMax = 1u << 24;
 
-// The scattering DM of list entry e.
+// The scattering DM of owner slot s.
 template <typename Real>
 struct ResolveDm {
     double x, y, z, h, vx, vy, vz;
@@ -2567,9 +2574,9 @@ struct ResolveDm {
     uint32_t oid;
     int64_t t;
     uint64_t U;                   // U_i in units of 2^-64
-    __device__ __forceinline__ ResolveDm(const ResolveArgs& a, uint32_t e, uint32_t step)
+    __device__ __forceinline__ ResolveDm(const ResolveArgs& a, int64_t s, uint32_t step)
     {
-        const int64_t s = a.slist[e], sp = a.g.own[s];
+        const int64_t sp = a.g.own[s];
         t = s / kTile;
         x = a.g.ox[sp]; y = a.g.oy[sp]; z = a.g.oz[sp]; h = a.g.oh[sp];
         const DmRec<Real> r = reinterpret_cast<const DmRec<Real>*>(a.drec)[sp];
@@ -2727,42 +2734,76 @@ __device__ __forceinline__ void resolve_finish(const ResolveArgs& a, const Resol
     }
 }
 
-template <typename Real, int N, bool EXACT_G, bool RB = false, bool BATCH = false>
-__global__ __launch_bounds__(kResolveThreads) void k_resolve(ResolveArgs a0, const ResolveArgs* __restrict__ boxes)
+// Box and position of entry e of the boxes' lists laid end to end (count(b) entries of
+// box b; the block's wavefronts all call); -1 past the end, when *pos is the total.
+template <typename Count>
+__device__ __forceinline__ int box_of_entry(int nbox, int lane, uint32_t e, Count&& count, uint32_t* pos)
 {
+    uint32_t before = 0u;
+    for (int b0 = 0; b0 < nbox; b0 += 64) {
+        const uint32_t n = b0 + lane < nbox ? count(b0 + lane) : 0u;
+        const uint32_t incl = before + uint32_t(wave_incl_scan(int(n)));
+        const uint64_t past = __ballot(incl > e);
+        if (past) {
+            const int l = int(__builtin_ctzll(past));
+            *pos = e - uint32_t(__builtin_amdgcn_readlane(int(incl - n), l));
+            return b0 + l;
+        }
+        before = uint32_t(__builtin_amdgcn_readlane(int(incl), 63));
+    }
+    *pos = before;
+    return -1;
+}
+
+template <typename Real, int N, bool EXACT_G, bool RB, bool BATCH, bool FEW>
+__global__ __launch_bounds__(FEW ? 64 : kResolveThreads) void k_resolve(ResolveArgs a0, const ResolveArgs* __restrict__ boxes, int nbox)
+{
+    constexpr int TH = FEW ? 64 : kResolveThreads, WV = TH / 64;
+    constexpr int LIST = FEW ? kResolveFewList : kResolveList, CAP = FEW ? kResolveFewPairs : kResolvePairs;
     __shared__ unsigned long long hhi[256], hlo[256];
     // kept sub-tiles: first particle; image (8 bits per axis), particle count << 24, clean << 31
-    __shared__ uint32_t s_start[kResolveList], s_info[kResolveList];
-    __shared__ uint32_t s_gid[kResolvePairs];   // list position << 6 | particle, then the gas index
-    __shared__ double s_P[kResolvePairs];
+    __shared__ uint32_t s_start[LIST], s_info[LIST];
+    __shared__ uint32_t s_gid[CAP];   // list position << 6 | particle, then the gas index
+    __shared__ double s_P[CAP];
     __shared__ uint32_t s_nrel, s_npart, s_npairs, s_wide, s_prefix;
-    const ResolveArgs& a = BATCH ? boxes[blockIdx.y] : a0;
-    const PassGeom& G = a.g;
     const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t step = a.step + (a.step_off ? *a.step_off : 0u);
-    const uint32_t nsc = *a.scount;
-    const int npass = (a.n_gas_bits + 7) / 8;
-
-    for (uint32_t e = blockIdx.x; e < nsc; e += gridDim.x) {
-        const ResolveDm<Real> m(a, e, step);
+    // many scattering DM: the one-wavefront search took them all and left the larger ones on mlist
+    auto scattering = [&](int b) { return *(BATCH ? boxes[b] : a0).scount; };
+    uint32_t total = 0u;
+    box_of_entry(nbox, lane, ~0u, scattering, &total);
+    const bool many = total > kResolveMany;
+    if (FEW && !many) return;
+    const bool rest = !FEW && many;
+    auto count = [&](int b) { return rest ? *(BATCH ? boxes[b] : a0).mcount : scattering(b); };
+    for (uint32_t eg = blockIdx.x;; eg += gridDim.x) {
+        uint32_t e = eg;
+        const int b = box_of_entry(nbox, lane, eg, count, &e);
+        if (b < 0) return;
+        const ResolveArgs& a = BATCH ? boxes[b] : a0;
+        const PassGeom& G = a.g;
+        const uint32_t step = a.step + (a.step_off ? *a.step_off : 0u);
+        const int npass = (a.n_gas_bits + 7) / 8;
+        const uint32_t* list = rest ? a.mlist : a.slist;
+        const int64_t s = list[e];
+        const ResolveDm<Real> m(a, s, step);
         double A[6];
         for (int k = 0; k < 6; ++k) A[k] = G.obox[6 * m.t + k];
         const uint64_t cb = a.cand_beg[m.t], ce = cb + a.cand_cnt[m.t];
         if (tid == 0) { s_nrel = 0u; s_npart = 0u; s_npairs = 0u; s_wide = 0u; }
         __syncthreads();
         // candidate sub-tiles this DM can reach (point-to-box gap < h_i + max h of the sub-tile)
-        for (uint64_t c0 = cb + tid; c0 < ce; c0 += kResolveStreams * kResolveThreads) {
+        for (uint64_t c0 = cb + tid; c0 < ce; c0 += kResolveStreams * TH) {
             uint32_t ot[kResolveStreams];
             bool near[kResolveStreams];
 #pragma unroll
-            for (int u = 0; u < kResolveStreams; ++u) ot[u] = G.cand[min(c0 + u * kResolveThreads, ce - 1)];
+            for (int u = 0; u < kResolveStreams; ++u) ot[u] = G.cand[min(c0 + u * TH, ce - 1)];
 #pragma unroll
-            for (int u = 0; u < kResolveStreams; ++u) near[u] = c0 + u * kResolveThreads < ce && m.near(a, ot[u]);
+            for (int u = 0; u < kResolveStreams; ++u) near[u] = c0 + u * TH < ce && m.near(a, ot[u]);
 #pragma unroll
             for (int u = 0; u < kResolveStreams; ++u) {
                 if (!near[u]) continue;
                 const uint32_t pos = atomicAdd(&s_nrel, 1u);
-                if (pos >= uint32_t(kResolveList)) continue;
+                if (pos >= uint32_t(LIST)) continue;
                 double sh[3];
                 bool clean;
                 tile_pair_shift(A, G.tbox + 6 * int64_t(ot[u]), G.L, sh, &clean);
@@ -2783,14 +2824,14 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(ResolveArgs a0, con
                          pz = Z + double(int8_t(info >> 16)) * G.L[2];
             return pair_d2(m.x, m.y, m.z, px, py, pz, (info >> 31) != 0u, G.L);
         };
-        if (nrel <= uint32_t(kResolveList)) {
+        if (nrel <= uint32_t(LIST)) {
             // 16 lanes per sub-tile, 32 where they are well filled (6 particles on average in a
             // galaxy, 32 in a uniform box; whole wavefronts took 131 instead of 89 us for the
             // search of 411 DM among 40k gas particles), kResolveStreams at a time
             const uint32_t lw = s_npart > 12u * nrel ? 5u : 4u, ngrp = 64u >> lw;
             const uint32_t sub = uint32_t(lane) >> lw, ll = uint32_t(lane) & ((1u << lw) - 1u);
             const uint32_t per = ngrp * kResolveStreams;
-            for (uint32_t q0 = uint32_t(w) * per; q0 < nrel; q0 += per * kResolveWaves) {
+            for (uint32_t q0 = uint32_t(w) * per; q0 < nrel; q0 += per * WV) {
                 uint32_t info[kResolveStreams], start[kResolveStreams], cnt[kResolveStreams];
                 uint32_t most = 0u;
 #pragma unroll
@@ -2819,14 +2860,18 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(ResolveArgs a0, con
                         if (lane == 0) base = atomicAdd(&s_npairs, uint32_t(__popcll(mk)));
                         base = uint32_t(__builtin_amdgcn_readfirstlane(int(base)));
                         const uint32_t pos = base + uint32_t(__popcll(mk & ((1ull << lane) - 1ull)));
-                        if (hit && pos < uint32_t(kResolvePairs)) s_gid[pos] = ((q0 + ngrp * u + sub) << 6) | kk;
+                        if (hit && pos < uint32_t(CAP)) s_gid[pos] = ((q0 + ngrp * u + sub) << 6) | kk;
                     }
                 }
             }
         }
         __syncthreads();
         const uint32_t npairs = s_npairs;
-        const bool cached = nrel <= uint32_t(kResolveList) && npairs <= uint32_t(kResolvePairs);
+        const bool cached = nrel <= uint32_t(LIST) && npairs <= uint32_t(CAP);
+        if (FEW && !cached) {
+            if (tid == 0) a.mlist[atomicAdd(a.mcount, 1u)] = uint32_t(s);
+            continue;
+        }
         if (!cached && a.wide) {
             if (tid == 0) s_wide = atomicAdd(a.wcount, 1u) + 1u;
             __syncthreads();
@@ -2834,13 +2879,13 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(ResolveArgs a0, con
             if (ws <= uint32_t(kResolveWide)) {
                 ResolveWide& W = a.wide[ws - 1u];
                 if (tid < 256) { W.hi[tid] = 0ull; W.lo[tid] = 0ull; }
-                if (tid == 0) { W.e = e; W.prefix = 0u; W.done = 0u; W.pass = 0u; W.below[0] = 0ull; W.below[1] = 0ull; }
+                if (tid == 0) { W.s = uint32_t(s); W.prefix = 0u; W.done = 0u; W.pass = 0u; W.below[0] = 0ull; W.below[1] = 0ull; }
                 __syncthreads();
                 continue;
             }
         }
         if (cached) {
-            for (uint32_t p = tid; p < npairs; p += kResolveThreads) {
+            for (uint32_t p = tid; p < npairs; p += TH) {
                 const uint32_t key = s_gid[p], info = s_info[key >> 6];
                 const int64_t k = int64_t(s_start[key >> 6]) + (key & 63u);
                 const double gh = G.th[k], d2 = shifted(info, G.tx[k], G.ty[k], G.tz[k]);
@@ -2853,13 +2898,13 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(ResolveArgs a0, con
         unsigned __int128 below = 0, after = 0;    // wavefront 0
         for (int ps = 0; ps < npass; ++ps) {
             const int shft = 8 * (npass - 1 - ps);
-            if (tid < 256) { hhi[tid] = 0ull; hlo[tid] = 0ull; }
+            for (int k = tid; k < 256; k += TH) { hhi[k] = 0ull; hlo[k] = 0ull; }
             __syncthreads();
             if (cached) {
-                for (uint32_t p = tid; p < npairs; p += kResolveThreads)
+                for (uint32_t p = tid; p < npairs; p += TH)
                     hist_add(hhi, hlo, shft, prefix, s_gid[p], s_P[p]);
             } else {
-                resolve_walk<Real, N, EXACT_G, RB>(a, m, step, lane, uint64_t(w), uint64_t(kResolveWaves),
+                resolve_walk<Real, N, EXACT_G, RB>(a, m, step, lane, uint64_t(w), uint64_t(WV),
                                                    [&](uint32_t gid, double P) { hist_add(hhi, hlo, shft, prefix, gid, P); });
             }
             __syncthreads();
@@ -2917,7 +2962,7 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve_wide(ResolveArgs a0
         __syncthreads();
         const int shft = 8 * (npass - 1 - int(ps));
         const uint32_t prefix = s_prefix;
-        const ResolveDm<Real> m(a, W.e, step);
+        const ResolveDm<Real> m(a, int64_t(W.s), step);
         resolve_walk<Real, N, EXACT_G, RB>(a, m, step, lane, uint64_t(slice) * kResolveWaves + w, uint64_t(S) * kResolveWaves,
                                            [&](uint32_t gid, double P) { hist_add(hhi, hlo, shft, prefix, gid, P); });
         __syncthreads();
@@ -2960,17 +3005,19 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve_wide(ResolveArgs a0
 // u = vs r (c e + s (cos phi e1 + sin phi e2)), e = w/|w| (the z axis if
 // w = 0; cold gas: u = w), and applies the kick, all in binary64.
 template <typename Real, int N, bool BATCH = false>
-__global__ __launch_bounds__(64) void k_rb_kick(ResolveArgs a0, const ResolveArgs* __restrict__ boxes)
+__global__ __launch_bounds__(64) void k_rb_kick(ResolveArgs a0, const ResolveArgs* __restrict__ boxes, int nbox)
 {
-    const ResolveArgs& a = BATCH ? boxes[blockIdx.y] : a0;
     __shared__ double s_cell[kTiltCells];
     __shared__ double s_gl[32];
     const int lane = int(threadIdx.x);
-    if (lane < 32) s_gl[lane] = a.tilt_gl[lane];
+    if (lane < 32) s_gl[lane] = (BATCH ? boxes[0] : a0).tilt_gl[lane];
     __syncthreads();
-    const uint32_t step = a.step + (a.step_off ? *a.step_off : 0u);
-    const uint32_t nsc = *a.scount;
-    for (uint32_t e = blockIdx.x; e < nsc; e += gridDim.x) {
+    for (uint32_t eg = blockIdx.x;; eg += gridDim.x) {
+        uint32_t e = eg;
+        const int b = box_of_entry(nbox, lane, eg, [&](int q) { return *(BATCH ? boxes[q] : a0).scount; }, &e);
+        if (b < 0) return;
+        const ResolveArgs& a = BATCH ? boxes[b] : a0;
+        const uint32_t step = a.step + (a.step_off ? *a.step_off : 0u);
         const int64_t sp = a.g.own[a.slist[e]];
         const DmRec<Real> orc = reinterpret_cast<const DmRec<Real>*>(a.drec)[sp];
         const uint32_t oid = a.dm_perm[sp];
