@@ -704,6 +704,36 @@ dmb_status both(dmb_ctx* c, FA&& a, FB&& b)
 // A DM can outgrow a block's cache only if the box has that many gas particles or sub-tiles.
 bool resolve_may_widen(const Cells& X) { return X.gas.n > kResolvePairs || X.gas.ntile > kResolveList; }
 
+GasGatherArgs gas_gather_args(Species& G, const dmb_particles* gas, const dmb_params* par)
+{
+    GasGatherArgs ga;
+    ga.n = G.n; ga.perm = G.perm; ga.vel = gas->vel; ga.mass = gas->mass; ga.u = gas->u; ga.mu = gas->mu;
+    ga.m_chi = par->m_chi_g; ga.sig_kpc2_cn = sig_kpc2_cn_of(par); ga.alpha_n = alpha_n(par->n_pow);
+    ga.n_pow = par->n_pow;
+    ga.rb = par->dm_sampling == DMB_SAMPLE_RB;
+    ga.alpha_rb = ga.rb ? alpha_n(par->n_pow - 2) : 0.0;
+    ga.Vx = G.v0.as<double>(); ga.Vy = G.v1.as<double>(); ga.Vz = G.v2.as<double>();
+    ga.flag = G.flag.as<const uint32_t>(); ga.flag_off = G.flag_off.as<const uint32_t>();
+    ga.orate = G.orate.p;
+    ga.rec = G.rec.p;
+    return ga;
+}
+
+DmGatherArgs dm_gather_args(Species& D, const dmb_particles* dm, const dmb_params* par)
+{
+    DmGatherArgs da;
+    da.n = D.n; da.perm = D.perm; da.vel = dm->vel; da.mass = dm->mass; da.dt = dm->dt;
+    da.dt_default = par->dt;
+    da.rec = D.rec.p;
+    return da;
+}
+
+FillArgs fill_args(int64_t n_gas, int64_t n_dm, const dmb_out* out, uint64_t* counters, uint32_t* queues, int nqueues)
+{
+    return FillArgs{n_gas, n_dm, out->dp_gas, out->de_gas, out->dv_dm, out->partner, out->p_sum, out->p_max, counters,
+                    queues, nqueues};
+}
+
 // Per-step gathers into Morton order and the clearing of outputs, counters
 // and the box's queue counters (qctr: eight of the gas queue, eight of the DM
 // queue and the scatter count, kQueueStride words apart).  Buffers are sized first; with `overlap` the gas
@@ -733,17 +763,8 @@ dmb_status gather_and_fill(dmb_ctx* c, Cells& X, const dmb_particles* gas, const
         if (resolve_may_widen(X)) ENSURE(c, X.rwide, kResolveWide * sizeof(ResolveWide));
     }
     auto gas_gather = [&] {
-        GasGatherArgs ga;
-        ga.n = G.n; ga.perm = G.perm; ga.vel = gas->vel; ga.mass = gas->mass; ga.u = gas->u; ga.mu = gas->mu;
-        ga.m_chi = par->m_chi_g; ga.sig_kpc2_cn = sig_kpc2_cn_of(par); ga.alpha_n = alpha_n(par->n_pow);
-        ga.n_pow = par->n_pow;
-        ga.rb = par->dm_sampling == DMB_SAMPLE_RB;
-        ga.alpha_rb = ga.rb ? alpha_n(par->n_pow - 2) : 0.0;
-        ga.Vx = G.v0.as<double>(); ga.Vy = G.v1.as<double>(); ga.Vz = G.v2.as<double>();
-        ga.flag = G.flag.as<const uint32_t>(); ga.flag_off = G.flag_off.as<const uint32_t>();
-        ga.orate = G.orate.p;
-        ga.rec = G.rec.p;
-        hipLaunchKernelGGL(k_gather_gas<Real>, dim3(blocks_for(G.n, 256)), dim3(256), 0, c->stream, ga);
+        hipLaunchKernelGGL(k_gather_gas<Real>, dim3(blocks_for(G.n, 256)), dim3(256), 0, c->stream,
+                           gas_gather_args(G, gas, par), (const GasGatherArgs*)nullptr);
     };
     const bool side = overlap && G.n > 0 && D.n > 0;
     if (side) {
@@ -755,16 +776,12 @@ dmb_status gather_and_fill(dmb_ctx* c, Cells& X, const dmb_particles* gas, const
         gas_gather();
     }
     if (D.n > 0) {
-        DmGatherArgs da;
-        da.n = D.n; da.perm = D.perm; da.vel = dm->vel; da.mass = dm->mass; da.dt = dm->dt;
-        da.dt_default = par->dt;
-        da.rec = D.rec.p;
-        hipLaunchKernelGGL(k_gather_dm<Real>, dim3(blocks_for(D.n, 256)), dim3(256), 0, c->stream, da);
+        hipLaunchKernelGGL(k_gather_dm<Real>, dim3(blocks_for(D.n, 256)), dim3(256), 0, c->stream,
+                           dm_gather_args(D, dm, par), (const DmGatherArgs*)nullptr);
     }
     int64_t nfill = std::max<int64_t>(std::max<int64_t>(G.n, D.n), kQueueWords);
-    hipLaunchKernelGGL(k_fill_out, dim3(blocks_for(nfill, 256)), dim3(256), 0, c->stream, G.n, D.n, out->dp_gas,
-                       out->de_gas, out->dv_dm, out->partner, out->p_sum, out->p_max, counters,
-                       X.qctr.as<uint32_t>(), kQueueWords);
+    hipLaunchKernelGGL(k_fill_out, dim3(blocks_for(nfill, 256)), dim3(256), 0, c->stream,
+                       fill_args(G.n, D.n, out, counters, X.qctr.as<uint32_t>(), kQueueWords), (const FillArgs*)nullptr);
     if (side) {
         dmb_status s = join(c);
         if (s != DMB_OK) return s;
@@ -812,8 +829,7 @@ GasPassArgs gas_pass_args(dmb_ctx* c, Cells& X, const dmb_particles* gas, const 
     return a;
 }
 
-template <int N, int RM>
-void combine_gas(dmb_ctx* c, Cells& X, const dmb_particles* gas, const dmb_params* par, dmb_out* out)
+GasCombineArgs gas_combine_args(Cells& X, const dmb_particles* gas, const dmb_params* par, dmb_out* out)
 {
     Species& G = X.gas;
     GasCombineArgs cb;
@@ -821,8 +837,15 @@ void combine_gas(dmb_ctx* c, Cells& X, const dmb_particles* gas, const dmb_param
     cb.item_off = X.gp.ioff.as<const uint32_t>(); cb.part = X.part_gas.as<const double>();
     cb.out = GasOutArgs{gas->mass, gas->mu, gas->dt, gas->u, par->dt, par->m_chi_g,
                         sig_kpc2_cn_of(par) * (1.0 - par->aniso_g), alpha_n(par->n_pow), out->dp_gas, out->de_gas};
-    hipLaunchKernelGGL((k_combine_gas<N, RM>), dim3(unsigned((G.n_own + kTile - 1) / kTile)),
-                       dim3(64 * kCombineWaves), 0, c->stream, cb);
+    return cb;
+}
+
+template <int N, int RM>
+void combine_gas(dmb_ctx* c, Cells& X, const dmb_particles* gas, const dmb_params* par, dmb_out* out)
+{
+    hipLaunchKernelGGL((k_combine_gas<N, RM, false>), dim3(unsigned((X.gas.n_own + kTile - 1) / kTile)),
+                       dim3(64 * kCombineWaves), 0, c->stream, gas_combine_args(X, gas, par, out),
+                       (const GasCombineArgs*)nullptr);
 }
 
 DmPassArgs dm_pass_args(dmb_ctx* c, Cells& X, const dmb_params* par, dmb_out* out, uint64_t* counters,
@@ -845,7 +868,7 @@ DmPassArgs dm_pass_args(dmb_ctx* c, Cells& X, const dmb_params* par, dmb_out* ou
     return a;
 }
 
-void combine_dm(dmb_ctx* c, Cells& X, const DmPassArgs& a, dmb_out* out, uint64_t* counters)
+DmCombineArgs dm_combine_args(Cells& X, const DmPassArgs& a, dmb_out* out, uint64_t* counters)
 {
     Species& D = X.dm;
     DmCombineArgs cb;
@@ -855,9 +878,7 @@ void combine_dm(dmb_ctx* c, Cells& X, const DmPassArgs& a, dmb_out* out, uint64_
     cb.k0 = a.k0; cb.k1 = a.k1; cb.step = a.step; cb.box = a.box; cb.step_off = a.step_off;
     cb.psum_own = X.psum_own.as<double>(); cb.psum = out->p_sum; cb.pmax = out->p_max;
     cb.scount = a.scount; cb.slist = X.slist.as<uint32_t>(); cb.counters = counters;
-    Phase ph(c, DMB_PH_COMBINE_DM);
-    hipLaunchKernelGGL(k_combine_dm, dim3(unsigned((D.n_own + kTile - 1) / kTile)), dim3(64 * kCombineWaves), 0,
-                       c->stream, cb);
+    return cb;
 }
 
 ResolveArgs resolve_args(dmb_ctx* c, Cells& X, const DmPassArgs& a, const dmb_particles* gas, const dmb_params* par,
@@ -908,7 +929,11 @@ template <typename Real, int N, bool RB>
 void combine_dm_and_resolve(dmb_ctx* c, Cells& X, const DmPassArgs& a, const dmb_particles* gas,
                             const dmb_params* par, dmb_out* out, uint64_t* counters)
 {
-    combine_dm(c, X, a, out, counters);
+    {
+        Phase ph(c, DMB_PH_COMBINE_DM);
+        hipLaunchKernelGGL(k_combine_dm<false>, dim3(unsigned((X.dm.n_own + kTile - 1) / kTile)), dim3(64 * kCombineWaves), 0,
+                           c->stream, dm_combine_args(X, a, out, counters), (const DmCombineArgs*)nullptr);
+    }
     const ResolveArgs r = resolve_args(c, X, a, gas, par, out, counters);
     launch_resolve<Real, N, RB, false>(c, r, nullptr, 1, X.dm.n_own, r.wide != nullptr);
 }
@@ -1007,6 +1032,13 @@ struct BatchPlan {
     std::vector<GasPassArgs> ga;
     std::vector<DmPassArgs> da;
     std::vector<ResolveArgs> ra;
+    std::vector<GasGatherArgs> gg;
+    std::vector<DmGatherArgs> dg;
+    std::vector<FillArgs> fa;              // one per box, then the queues of the passes
+    std::vector<GasCombineArgs> gc;
+    std::vector<DmCombineArgs> dc;
+    size_t at_da = 0, at_ra = 0, at_gg = 0, at_dg = 0, at_fa = 0, at_gc = 0, at_dc = 0;   // offsets in bgeom (ga at 0)
+    int64_t most_gas = 0, most_n = 0;      // active gas, particles of either species of the largest box
     int64_t most_dm = 0;                   // active DM of the largest box
     bool resolve_wide = false;             // some box may need k_resolve_wide
     int nb_gas = 0, nb_dm = 0;
@@ -1023,6 +1055,8 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
     P.ga.resize(nbox);
     P.da.resize(nbox);
     P.ra.resize(nbox);
+    P.gg.clear(); P.dg.clear(); P.fa.clear(); P.gc.clear(); P.dc.clear();
+    P.most_gas = P.most_n = 0;
     P.resolve_wide = false;
     P.most_dm = 0;
     std::vector<int64_t> gi(nbox + 1, 0), di(nbox + 1, 0);
@@ -1059,20 +1093,37 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
         P.ra[b] = resolve_args(c, X, P.da[b], gas + b, par + b, out + b, counters);
         if (X.dp.nitems > 0 && P.ra[b].wide) P.resolve_wide = true;
         P.most_dm = std::max(P.most_dm, X.dm.n_own);
+        P.most_gas = std::max(P.most_gas, X.gas.n_own);
+        P.most_n = std::max({P.most_n, G.n, D.n});
+        P.gg.push_back(gas_gather_args(G, gas + b, par + b));
+        P.dg.push_back(dm_gather_args(D, dm + b, par + b));
+        P.fa.push_back(fill_args(G.n, D.n, out + b, counters, X.qctr.as<uint32_t>(), kQueueWords));
+        P.gc.push_back(gas_combine_args(X, gas + b, par + b, out + b));
+        P.dc.push_back(dm_combine_args(X, P.da[b], out + b, counters));
         gi[b + 1] = gi[b] + X.gp.nitems;
         di[b + 1] = di[b] + X.dp.nitems;
     }
     P.gas_items = gi[nbox];
     P.dm_items = di[nbox];
-    const size_t argb = sizeof(GasPassArgs) + sizeof(DmPassArgs) + sizeof(ResolveArgs);
-    ENSURE(c, c->bgeom, size_t(nbox) * argb + 256);
+    const dmb_out none{};
+    P.fa.push_back(fill_args(0, 0, &none, nullptr, c->bstep.as<uint32_t>(), 2 * kXcd * kQueueStride));
+    size_t bytes = 0;
+    auto place = [&](const auto& v) {
+        const size_t at = bytes;
+        bytes += (v.size() * sizeof(v[0]) + 15) / 16 * 16;
+        return at;
+    };
+    (void)place(P.ga);
+    P.at_da = place(P.da); P.at_ra = place(P.ra); P.at_gg = place(P.gg); P.at_dg = place(P.dg); P.at_fa = place(P.fa);
+    P.at_gc = place(P.gc); P.at_dc = place(P.dc);
+    ENSURE(c, c->bgeom, bytes);
     ENSURE(c, c->bitem, size_t(2 * (nbox + 1)) * sizeof(int64_t));
-    char* gdev = c->bgeom.as<char>();
-    HIPCHK(c, hipMemcpyAsync(gdev, P.ga.data(), nbox * sizeof(GasPassArgs), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(gdev + size_t(nbox) * sizeof(GasPassArgs), P.da.data(), nbox * sizeof(DmPassArgs),
-                             hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(gdev + size_t(nbox) * (sizeof(GasPassArgs) + sizeof(DmPassArgs)), P.ra.data(),
-                             nbox * sizeof(ResolveArgs), hipMemcpyHostToDevice, c->stream));
+    auto upload = [&](const auto& v, size_t at) {
+        return hipMemcpyAsync(c->bgeom.as<char>() + at, v.data(), v.size() * sizeof(v[0]), hipMemcpyHostToDevice, c->stream);
+    };
+    HIPCHK(c, upload(P.ga, 0)); HIPCHK(c, upload(P.da, P.at_da)); HIPCHK(c, upload(P.ra, P.at_ra));
+    HIPCHK(c, upload(P.gg, P.at_gg)); HIPCHK(c, upload(P.dg, P.at_dg)); HIPCHK(c, upload(P.fa, P.at_fa));
+    HIPCHK(c, upload(P.gc, P.at_gc)); HIPCHK(c, upload(P.dc, P.at_dc));
     HIPCHK(c, hipMemcpyAsync(c->bitem.p, gi.data(), (nbox + 1) * sizeof(int64_t), hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->bitem.as<int64_t>() + nbox + 1, di.data(), (nbox + 1) * sizeof(int64_t),
                              hipMemcpyHostToDevice, c->stream));
@@ -1088,10 +1139,9 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
     return DMB_OK;
 }
 
-// The DM side of a batched step: one pass over all boxes' items, the per-box
-// combines, and one resolve over all boxes.
+// The DM side of a batched step: pass, combine and resolve, each over all boxes.
 template <typename Real, int N, bool RB>
-void batch_dm_side(dmb_ctx* c, dmb_out* out, const BatchPlan& P, const DmPassArgs* ddev, const int64_t* ditems)
+void batch_dm_side(dmb_ctx* c, const BatchPlan& P, const DmPassArgs* ddev, const int64_t* ditems)
 {
     constexpr bool kExact = sizeof(Real) == 8;
     DmPassArgs a0 = P.da[0];
@@ -1102,10 +1152,13 @@ void batch_dm_side(dmb_ctx* c, dmb_out* out, const BatchPlan& P, const DmPassArg
         hipLaunchKernelGGL((k_pass_dm<Real, N, kExact, true, false, RB>), dim3(P.nb_dm), dim3(64), 0, c->stream, a0,
                            ddev, ditems, P.nbox);
     }
-    for (int b = 0; b < P.nbox; ++b)
-        if (c->boxes[b]->dp.nitems > 0)
-            combine_dm(c, *c->boxes[b], P.da[b], out + b, out[b].counters);
-    launch_resolve<Real, N, RB, true>(c, P.ra[0], reinterpret_cast<const ResolveArgs*>(ddev + P.nbox), P.nbox,
+    const char* const base = c->bgeom.as<const char>();
+    {
+        Phase ph(c, DMB_PH_COMBINE_DM);
+        hipLaunchKernelGGL(k_combine_dm<true>, dim3(blocks_for(P.most_dm, kTile), unsigned(P.nbox)), dim3(64 * kCombineWaves), 0,
+                           c->stream, P.dc[0], reinterpret_cast<const DmCombineArgs*>(base + P.at_dc));
+    }
+    launch_resolve<Real, N, RB, true>(c, P.ra[0], reinterpret_cast<const ResolveArgs*>(base + P.at_ra), P.nbox,
                                       P.most_dm * P.nbox, P.resolve_wide);
 }
 
@@ -1117,16 +1170,17 @@ dmb_status batch_enqueue(dmb_ctx* c, const dmb_particles* gas, const dmb_particl
     constexpr int kW = RM == kRatesMlp ? kMlpPassWaves : 1;
     const int nbox = P.nbox;
     const GasPassArgs* gdev = reinterpret_cast<const GasPassArgs*>(c->bgeom.p);
-    const DmPassArgs* ddev = reinterpret_cast<const DmPassArgs*>(c->bgeom.as<char>() + size_t(nbox) * sizeof(GasPassArgs));
+    const char* const base = c->bgeom.as<const char>();
+    const DmPassArgs* ddev = reinterpret_cast<const DmPassArgs*>(base + P.at_da);
     const int64_t* gitems = c->bitem.as<const int64_t>();
     const int64_t* ditems = gitems + nbox + 1;
-    for (int b = 0; b < nbox; ++b) {
-        dmb_status s = gather_and_fill<Real, RM>(c, *c->boxes[b], gas + b, dm + b, par + b, out + b, out[b].counters);
-        if (s != DMB_OK) return s;
-    }
-    hipLaunchKernelGGL(k_fill_out, dim3(blocks_for(2 * kXcd * kQueueStride, 256)), dim3(256), 0, c->stream, int64_t(0), int64_t(0), (double*)nullptr,
-                       (double*)nullptr, (double*)nullptr, (int32_t*)nullptr, (double*)nullptr, (double*)nullptr,
-                       (uint64_t*)nullptr, c->bstep.as<uint32_t>(), 2 * kXcd * kQueueStride);
+    const dim3 rows(blocks_for(std::max<int64_t>(P.most_n, kQueueWords), 256), unsigned(nbox));
+    hipLaunchKernelGGL(k_gather_gas<Real>, rows, dim3(256), 0, c->stream, P.gg[0],
+                       reinterpret_cast<const GasGatherArgs*>(base + P.at_gg));
+    hipLaunchKernelGGL(k_gather_dm<Real>, rows, dim3(256), 0, c->stream, P.dg[0],
+                       reinterpret_cast<const DmGatherArgs*>(base + P.at_dg));
+    hipLaunchKernelGGL(k_fill_out, dim3(rows.x, unsigned(nbox + 1)), dim3(256), 0, c->stream, P.fa[0],
+                       reinterpret_cast<const FillArgs*>(base + P.at_fa));
     // as in the single-box step, the DM side (enqueued first) and the gas side run on two
     // streams, forked after the gathers and joined at the end (also inside a captured graph)
     const bool side = c->pass_overlap && P.gas_items > 0 && P.dm_items > 0;
@@ -1138,11 +1192,11 @@ dmb_status batch_enqueue(dmb_ctx* c, const dmb_particles* gas, const dmb_particl
         bool done = false;
         if constexpr (N > -4) {
             if (P.rb) {
-                batch_dm_side<Real, N, true>(c, out, P, ddev, ditems);
+                batch_dm_side<Real, N, true>(c, P, ddev, ditems);
                 done = true;
             }
         }
-        if (!done) batch_dm_side<Real, N, false>(c, out, P, ddev, ditems);
+        if (!done) batch_dm_side<Real, N, false>(c, P, ddev, ditems);
     }
     if (P.gas_items > 0) {
         OnSide on(c, side);
@@ -1155,8 +1209,9 @@ dmb_status batch_enqueue(dmb_ctx* c, const dmb_particles* gas, const dmb_particl
                                a0, gdev, gitems, nbox);
         }
         Phase ph(c, DMB_PH_COMBINE_GAS);
-        for (int b = 0; b < nbox; ++b)
-            if (c->boxes[b]->gp.nitems > 0) combine_gas<N, RM>(c, *c->boxes[b], gas + b, par + b, out + b);
+        hipLaunchKernelGGL((k_combine_gas<N, RM, true>), dim3(blocks_for(P.most_gas, kTile), unsigned(nbox)),
+                           dim3(64 * kCombineWaves), 0, c->stream, P.gc[0],
+                           reinterpret_cast<const GasCombineArgs*>(base + P.at_gc));
     }
     if (side) {
         dmb_status s = join(c);

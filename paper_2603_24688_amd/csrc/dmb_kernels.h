@@ -853,7 +853,8 @@ __global__ __launch_bounds__(256) void k_item_write(const uint64_t* __restrict__
 }
 
 // ---------------------------------------------------------------------------
-// Per-step gathers into sorted order.
+// Per-step gathers into sorted order.  These kernels and the combines below take one
+// box (boxes null) or, in a batch, row blockIdx.y of the boxes' arguments.
 // Per-pair data of the other species of a pass, one 16-byte-aligned record
 // per sorted particle, so that a pair's reads are a few wide loads from one
 // base pointer.
@@ -903,8 +904,9 @@ __device__ __forceinline__ void gas_derived(double u, double mu, double m_chi, d
 }
 
 template <typename Real>
-__global__ __launch_bounds__(256) void k_gather_gas(GasGatherArgs a)
+__global__ __launch_bounds__(256) void k_gather_gas(GasGatherArgs a0, const GasGatherArgs* __restrict__ boxes)
 {
+    const GasGatherArgs a = boxes ? boxes[blockIdx.y] : a0;
     int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (k >= a.n) return;
     uint32_t o = a.perm[k];
@@ -940,8 +942,9 @@ struct DmGatherArgs {
 };
 
 template <typename Real>
-__global__ __launch_bounds__(256) void k_gather_dm(DmGatherArgs a)
+__global__ __launch_bounds__(256) void k_gather_dm(DmGatherArgs a0, const DmGatherArgs* __restrict__ boxes)
 {
+    const DmGatherArgs a = boxes ? boxes[blockIdx.y] : a0;
     int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (k >= a.n) return;
     uint32_t o = a.perm[k];
@@ -952,23 +955,31 @@ __global__ __launch_bounds__(256) void k_gather_dm(DmGatherArgs a)
     reinterpret_cast<DmRec<Real>*>(a.rec)[k] = r;
 }
 
-__global__ __launch_bounds__(256) void k_fill_out(int64_t n_gas, int64_t n_dm, double* dp, double* de, double* dv,
-                                                  int32_t* partner, double* psum, double* pmax, uint64_t* counters,
-                                                  uint32_t* queues, int nqueues)
+struct FillArgs {
+    int64_t n_gas, n_dm;
+    double* dp; double* de; double* dv;
+    int32_t* partner;
+    double* psum; double* pmax;
+    uint64_t* counters;
+    uint32_t* queues; int nqueues;
+};
+
+__global__ __launch_bounds__(256) void k_fill_out(FillArgs a0, const FillArgs* __restrict__ boxes)
 {
+    const FillArgs a = boxes ? boxes[blockIdx.y] : a0;
     int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n_gas) {
-        dp[3 * i] = 0.0; dp[3 * i + 1] = 0.0; dp[3 * i + 2] = 0.0;
-        de[i] = 0.0;
+    if (i < a.n_gas) {
+        a.dp[3 * i] = 0.0; a.dp[3 * i + 1] = 0.0; a.dp[3 * i + 2] = 0.0;
+        a.de[i] = 0.0;
     }
-    if (i < n_dm) {
-        dv[3 * i] = 0.0; dv[3 * i + 1] = 0.0; dv[3 * i + 2] = 0.0;
-        partner[i] = -1;
-        if (psum) psum[i] = 0.0;
-        if (pmax) pmax[i] = 0.0;
+    if (i < a.n_dm) {
+        a.dv[3 * i] = 0.0; a.dv[3 * i + 1] = 0.0; a.dv[3 * i + 2] = 0.0;
+        a.partner[i] = -1;
+        if (a.psum) a.psum[i] = 0.0;
+        if (a.pmax) a.pmax[i] = 0.0;
     }
-    if (i < 8 && counters) counters[i] = 0ull;
-    if (i < nqueues) queues[i] = 0u;
+    if (i < 8 && a.counters) a.counters[i] = 0ull;
+    if (i < a.nqueues) a.queues[i] = 0u;
 }
 
 // ---------------------------------------------------------------------------
@@ -2289,9 +2300,11 @@ struct GasCombineArgs {
 // wave order, so the result does not depend on scheduling.
 constexpr int kCombineWaves = 8;
 
-template <int N, int RM>
-__global__ __launch_bounds__(64 * kCombineWaves) void k_combine_gas(GasCombineArgs a)
+template <int N, int RM, bool BATCH>
+__global__ __launch_bounds__(64 * kCombineWaves) void k_combine_gas(GasCombineArgs a0, const GasCombineArgs* __restrict__ boxes)
 {
+    const GasCombineArgs& a = BATCH ? boxes[blockIdx.y] : a0;
+    if (int64_t(blockIdx.x) * kTile >= a.n_own) return;
     constexpr int NS = gas_sums<RM>();
     __shared__ double s_acc[kCombineWaves][64][NS];
     const int64_t t = blockIdx.x;
@@ -2327,8 +2340,11 @@ struct DmCombineArgs {
     uint64_t* counters;
 };
 
-__global__ __launch_bounds__(64 * kCombineWaves) void k_combine_dm(DmCombineArgs a)
+template <bool BATCH>
+__global__ __launch_bounds__(64 * kCombineWaves) void k_combine_dm(DmCombineArgs a0, const DmCombineArgs* __restrict__ boxes)
 {
+    const DmCombineArgs& a = BATCH ? boxes[blockIdx.y] : a0;
+    if (int64_t(blockIdx.x) * kTile >= a.n_own) return;
     __shared__ double s_p[kCombineWaves][64];
     __shared__ float s_m[kCombineWaves][64];
     __shared__ uint32_t s_nb[kCombineWaves][64];
