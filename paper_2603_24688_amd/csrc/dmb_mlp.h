@@ -456,23 +456,70 @@ constexpr int kMlpLd = kMlpH + 1;   // padded LDS row
 
 constexpr int kMlpGradWaves = 4;
 
+// x(0) + x(1) + ... over a slice's samples in this order (with e: of x(b) e(b)); 32 at a time are
+// read before they are added, which otherwise waits for LDS at every term.
+template <typename X>
+__device__ __forceinline__ float ordered_sum(X&& x)
+{
+    float s = 0.f;
+#pragma unroll
+    for (int b0 = 0; b0 < kMlpWave; b0 += 32) {
+        float v[32];
+#pragma unroll
+        for (int k = 0; k < 32; ++k) v[k] = x(b0 + k);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < 32; ++k) s += v[k];
+    }
+    return s;
+}
+template <typename X, typename Y>
+__device__ __forceinline__ float ordered_sum(X&& x, Y&& e)
+{
+    float s = 0.f;
+#pragma unroll
+    for (int b0 = 0; b0 < kMlpWave; b0 += 32) {
+        float v[32], u[32];
+#pragma unroll
+        for (int k = 0; k < 32; ++k) { v[k] = x(b0 + k); u[k] = e(b0 + k); }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < 32; ++k) s += u[k] * v[k];
+    }
+    return s;
+}
+
 __global__ __launch_bounds__(64 * kMlpGradWaves) void k_mlp_grad(MlpGradArgs a)
 {
     __shared__ float F[3][kMlpWave][kMlpLd];    // activations a1..a3, [sample][unit]
     __shared__ float G[2][kMlpWave][kMlpLd];    // error signals, [sample][unit]
     __shared__ float E[kMlpWave][2], S[kMlpWave], Ls[kMlpWave];
     __shared__ int NI[kMlpWave];
-    const int l = threadIdx.x & 63, w = int(threadIdx.x) >> 6, h = l >> 4, c = l & 15;
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    const int h = l >> 4, c = l & 15;
     float* out = a.part + int64_t(blockIdx.x) * (kMlpParams + 1);
     const int64_t g = int64_t(blockIdx.x) * kMlpWave + l;
     const bool ok = g < a.batch;
+    // the backward pass's weights, asked for at once: the update that wrote them has just
+    // ended, and a load behind each barrier would wait out the memory's latency again
+    uint4 wt[2][2];
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+        wt[0][st] = *reinterpret_cast<const uint4*>(&a.W->w2t[16 * w + c][32 * st + 8 * h]);
+        wt[1][st] = *reinterpret_cast<const uint4*>(&a.W->w3t[16 * w + c][32 * st + 8 * h]);
+    }
+    const float w0 = a.W->w4f[0][l], w1 = a.W->w4f[1][l];
     float4 smp = make_float4(0.f, 0.f, 0.f, 0.f);
     if (ok) {
         int64_t idx = a.step * a.batch + g;
         if (a.shuffle) {
             const uint64_t* sh = a.shuffle + 2 * (a.epoch ? *a.epoch : 0u);
-            idx = int64_t((unsigned __int128)(uint64_t(idx) % uint64_t(a.n_total)) * sh[0] % uint64_t(a.n_total));
-            idx = int64_t((uint64_t(idx) + sh[1]) % uint64_t(a.n_total));
+            const uint64_t n = uint64_t(a.n_total), q = uint64_t(idx) < n ? uint64_t(idx) : uint64_t(idx) % n;
+            uint64_t v;
+            if (n <= 0xFFFFFFFFull) v = q * sh[0] % n;       // the product fits 64 bits
+            else v = uint64_t((unsigned __int128)q * sh[0] % n);
+            v += sh[1];
+            idx = int64_t(v < n ? v : v - n);
         } else {
             idx %= a.n_total;
         }
@@ -507,7 +554,6 @@ __global__ __launch_bounds__(64 * kMlpGradWaves) void k_mlp_grad(MlpGradArgs a)
     __syncthreads();
     // output layer (lane = unit): dW4, db4, and the layer-3 error
     {
-        const float w0 = a.W->w4f[0][l], w1 = a.W->w4f[1][l];
         auto err3 = [&](int b) {
             const float e0 = E[b][0], e1 = E[b][1], x = F[2][b][l];
             return x > 0.f ? e0 * w0 + e1 * w1 : 0.f;
@@ -515,37 +561,26 @@ __global__ __launch_bounds__(64 * kMlpGradWaves) void k_mlp_grad(MlpGradArgs a)
 #pragma unroll
         for (int b = 16 * w; b < 16 * w + 16; ++b) G[0][b][l] = err3(b);
         if (w < 2) {
-            float g0 = 0.f;
-#pragma unroll 16
-            for (int b = 0; b < kMlpWave; ++b) g0 += E[b][w] * F[2][b][l];
-            out[kOffW4 + w * kMlpH + l] = g0;
+            out[kOffW4 + w * kMlpH + l] = ordered_sum([&](int b) { return F[2][b][l]; }, [&](int b) { return E[b][w]; });
         } else if (w == 2) {
-            float db = 0.f;
-#pragma unroll 16
-            for (int b = 0; b < kMlpWave; ++b) db += err3(b);
-            out[kOffB3 + l] = db;
+            out[kOffB3 + l] = ordered_sum([&](int b) { return err3(b); });
         } else {
             float lsum = Ls[l];
             for (int d = 32; d >= 1; d >>= 1) lsum += __shfl_xor(lsum, d);
             if (l == 0) out[kMlpParams] = lsum;
-            if (l < 2) {
-                float s = 0.f;
-#pragma unroll 16
-                for (int b = 0; b < kMlpWave; ++b) s += E[b][l];
-                out[kOffB4 + l] = s;
-            }
+            const float s = ordered_sum([&](int b) { return E[b][l & 1]; });
+            if (l < 2) out[kOffB4 + l] = s;
         }
     }
     __syncthreads();
     // layers 3 and 2: weight gradient (MFMA over samples), then the error of
     // the layer below (MFMA over units); this wavefront's rows are 16 w ... 16 w + 15
-#pragma unroll 1
+#pragma unroll
     for (int ly = 1; ly >= 0; --ly) {
         const float(*Gi)[kMlpLd] = G[(1 - ly) & 1];     // error of layer ly+2: ly=1 -> G[0], ly=0 -> G[1]
         float(*Go)[kMlpLd] = G[ly & 1];                 // error of layer ly+1
         const float(*Fin)[kMlpLd] = F[ly];               // input activations of layer ly+2
         const int offW = ly == 1 ? kOffW3 : kOffW2;
-        const uint16_t(*wt)[kMlpH] = ly == 1 ? a.W->w3t : a.W->w2t;
         auto pack8 = [](const float* v) {
             return make_uint4(bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3]), bf16_pack2(v[4], v[5]),
                               bf16_pack2(v[6], v[7]));
@@ -576,13 +611,12 @@ __global__ __launch_bounds__(64 * kMlpGradWaves) void k_mlp_grad(MlpGradArgs a)
         for (int nb = 0; nb < 4; ++nb) D[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int st = 0; st < 2; ++st) {
-            const uint4 A = *reinterpret_cast<const uint4*>(&wt[16 * w + c][32 * st + 8 * h]);
 #pragma unroll
             for (int nb = 0; nb < 4; ++nb) {
                 float v[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) v[j] = Gi[16 * nb + c][mlp_nu(32 * st + 8 * h + j)];
-                D[nb] = mfma32(A, pack8(v), D[nb]);
+                D[nb] = mfma32(wt[ly][st], pack8(v), D[nb]);
             }
         }
 #pragma unroll
@@ -594,25 +628,13 @@ __global__ __launch_bounds__(64 * kMlpGradWaves) void k_mlp_grad(MlpGradArgs a)
             }
         __syncthreads();
         // bias gradient of layer ly+1 (lane = unit)
-        if (w == ly) {
-            float db = 0.f;
-#pragma unroll 16
-            for (int b = 0; b < kMlpWave; ++b) db += Go[b][l];
-            out[(ly == 1 ? kOffB2 : kOffB1) + l] = db;
-        }
+        if (w == ly) out[(ly == 1 ? kOffB2 : kOffB1) + l] = ordered_sum([&](int b) { return Go[b][l]; });
     }
     // layer 1 weights (lane = unit): inputs (s, one-hot n)
     {
-        float gn = 0.f;
-#pragma unroll 16
-        for (int b = 0; b < kMlpWave; ++b) gn += NI[b] == w ? G[0][b][l] : 0.f;
-        out[kOffW1 + l * kMlpIn + 1 + w] = gn;
-        if (w == 3) {
-            float gs = 0.f;
-#pragma unroll 16
-            for (int b = 0; b < kMlpWave; ++b) gs += G[0][b][l] * S[b];
-            out[kOffW1 + l * kMlpIn] = gs;
-        }
+        out[kOffW1 + l * kMlpIn + 1 + w] = ordered_sum([&](int b) { return NI[b] == w ? G[0][b][l] : 0.f; });
+        if (w == 3)
+            out[kOffW1 + l * kMlpIn] = ordered_sum([&](int b) { return G[0][b][l]; }, [&](int b) { return S[b]; });
     }
 }
 
