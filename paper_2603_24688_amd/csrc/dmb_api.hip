@@ -701,6 +701,14 @@ dmb_status both(dmb_ctx* c, FA&& a, FB&& b)
     return sj;
 }
 
+// launch(first box, boxes) over the boxes of a batch, a grid row each.
+constexpr int kGridRows = 32768;
+template <typename F>
+void by_rows(int nbox, F&& launch)
+{
+    for (int b = 0; b < nbox; b += kGridRows) launch(b, unsigned(std::min(kGridRows, nbox - b)));
+}
+
 // A DM can outgrow a block's cache only if the box has that many gas particles or sub-tiles.
 bool resolve_may_widen(const Cells& X) { return X.gas.n > kResolvePairs || X.gas.ntile > kResolveList; }
 
@@ -918,9 +926,11 @@ void launch_resolve(dmb_ctx* c, const ResolveArgs& r, const ResolveArgs* dev, in
     hipLaunchKernelGGL((k_resolve<Real, N, kExact, RB, BATCH, false>), grid(2), dim3(kResolveThreads), 0, c->stream, r,
                        dev, nbox);
     if (wide)
-        hipLaunchKernelGGL((k_resolve_wide<Real, N, kExact, RB, BATCH>),
-                           dim3(unsigned(std::max(8, c->num_cu / nbox)), unsigned(nbox)), dim3(kResolveThreads), 0,
-                           c->stream, r, dev);
+        by_rows(nbox, [&](int b, unsigned rows) {
+            hipLaunchKernelGGL((k_resolve_wide<Real, N, kExact, RB, BATCH>),
+                               dim3(unsigned(std::max(8, c->num_cu / nbox)), rows), dim3(kResolveThreads), 0, c->stream, r,
+                               dev ? dev + b : nullptr);
+        });
     if constexpr (RB)
         hipLaunchKernelGGL((k_rb_kick<Real, N, BATCH>), grid(4), dim3(64), 0, c->stream, r, dev, nbox);
 }
@@ -1155,8 +1165,10 @@ void batch_dm_side(dmb_ctx* c, const BatchPlan& P, const DmPassArgs* ddev, const
     const char* const base = c->bgeom.as<const char>();
     {
         Phase ph(c, DMB_PH_COMBINE_DM);
-        hipLaunchKernelGGL(k_combine_dm<true>, dim3(blocks_for(P.most_dm, kTile), unsigned(P.nbox)), dim3(64 * kCombineWaves), 0,
-                           c->stream, P.dc[0], reinterpret_cast<const DmCombineArgs*>(base + P.at_dc));
+        by_rows(P.nbox, [&](int b, unsigned rows) {
+            hipLaunchKernelGGL(k_combine_dm<true>, dim3(blocks_for(P.most_dm, kTile), rows), dim3(64 * kCombineWaves), 0,
+                               c->stream, P.dc[0], reinterpret_cast<const DmCombineArgs*>(base + P.at_dc) + b);
+        });
     }
     launch_resolve<Real, N, RB, true>(c, P.ra[0], reinterpret_cast<const ResolveArgs*>(base + P.at_ra), P.nbox,
                                       P.most_dm * P.nbox, P.resolve_wide);
@@ -1174,13 +1186,17 @@ dmb_status batch_enqueue(dmb_ctx* c, const dmb_particles* gas, const dmb_particl
     const DmPassArgs* ddev = reinterpret_cast<const DmPassArgs*>(base + P.at_da);
     const int64_t* gitems = c->bitem.as<const int64_t>();
     const int64_t* ditems = gitems + nbox + 1;
-    const dim3 rows(blocks_for(std::max<int64_t>(P.most_n, kQueueWords), 256), unsigned(nbox));
-    hipLaunchKernelGGL(k_gather_gas<Real>, rows, dim3(256), 0, c->stream, P.gg[0],
-                       reinterpret_cast<const GasGatherArgs*>(base + P.at_gg));
-    hipLaunchKernelGGL(k_gather_dm<Real>, rows, dim3(256), 0, c->stream, P.dg[0],
-                       reinterpret_cast<const DmGatherArgs*>(base + P.at_dg));
-    hipLaunchKernelGGL(k_fill_out, dim3(rows.x, unsigned(nbox + 1)), dim3(256), 0, c->stream, P.fa[0],
-                       reinterpret_cast<const FillArgs*>(base + P.at_fa));
+    const unsigned blocks = blocks_for(std::max<int64_t>(P.most_n, kQueueWords), 256);
+    by_rows(nbox, [&](int b, unsigned rows) {
+        hipLaunchKernelGGL(k_gather_gas<Real>, dim3(blocks, rows), dim3(256), 0, c->stream, P.gg[0],
+                           reinterpret_cast<const GasGatherArgs*>(base + P.at_gg) + b);
+        hipLaunchKernelGGL(k_gather_dm<Real>, dim3(blocks, rows), dim3(256), 0, c->stream, P.dg[0],
+                           reinterpret_cast<const DmGatherArgs*>(base + P.at_dg) + b);
+    });
+    by_rows(nbox + 1, [&](int b, unsigned rows) {
+        hipLaunchKernelGGL(k_fill_out, dim3(blocks, rows), dim3(256), 0, c->stream, P.fa[0],
+                           reinterpret_cast<const FillArgs*>(base + P.at_fa) + b);
+    });
     // as in the single-box step, the DM side (enqueued first) and the gas side run on two
     // streams, forked after the gathers and joined at the end (also inside a captured graph)
     const bool side = c->pass_overlap && P.gas_items > 0 && P.dm_items > 0;
@@ -1209,9 +1225,11 @@ dmb_status batch_enqueue(dmb_ctx* c, const dmb_particles* gas, const dmb_particl
                                a0, gdev, gitems, nbox);
         }
         Phase ph(c, DMB_PH_COMBINE_GAS);
-        hipLaunchKernelGGL((k_combine_gas<N, RM, true>), dim3(blocks_for(P.most_gas, kTile), unsigned(nbox)),
-                           dim3(64 * kCombineWaves), 0, c->stream, P.gc[0],
-                           reinterpret_cast<const GasCombineArgs*>(base + P.at_gc));
+        by_rows(nbox, [&](int b, unsigned rows) {
+            hipLaunchKernelGGL((k_combine_gas<N, RM, true>), dim3(blocks_for(P.most_gas, kTile), rows),
+                               dim3(64 * kCombineWaves), 0, c->stream, P.gc[0],
+                               reinterpret_cast<const GasCombineArgs*>(base + P.at_gc) + b);
+        });
     }
     if (side) {
         dmb_status s = join(c);
