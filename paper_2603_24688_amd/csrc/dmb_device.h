@@ -222,10 +222,10 @@ struct Overlap32 {
     __device__ __forceinline__ void begin(const float4* __restrict__ tab, double d2, double h1, double h2)
     {
         const double hbd = h1 > h2 ? h1 : h2, hsd = h1 > h2 ? h2 : h1;
-        // binary32 root (x times its reciprocal root), then one Newton step in binary64
-        const float d2f = float(d2), ir = __builtin_amdgcn_rsqf(d2f);
-        const double d0 = double(d2f * ir);
-        const double d = masked(fma(fma(-d0, d0, d2), double(0.5f * ir), d0), bits(d2f > 0.f));
+        // binary32 root, then one Newton step in binary64
+        const float d0f = __builtin_amdgcn_sqrtf(float(d2));
+        const double d0 = double(d0f);
+        const double d = masked(fma(fma(-d0, d0, d2), double(0.5f * __builtin_amdgcn_rcpf(d0f)), d0), bits(d0f > 0.f));
         const double innerd = hbd - d;
         const bool shell = innerd < hsd;
         const uint32_t ms = bits(shell);
