@@ -77,7 +77,7 @@ struct Cells {
     Species gas, dm;
     Pairs gp, dp;                          // gas owners x DM tiles; DM owners x gas tiles
     DevBuf part_gas, part_p, part_pm, part_nb, psum_own;
-    DevBuf qctr, slist, mlist, rwide;
+    DevBuf qctr, slist, rwide;
     int64_t built_ngas = -1, built_ndm = -1;
     const double* built_gas_pos = nullptr;
     const double* built_dm_pos = nullptr;
@@ -521,8 +521,9 @@ dmb_status cand_subs(dmb_ctx* c, Species& A, Species& B, Pairs& P)
     const uint32_t target = uint32_t(int64_t(c->item_target_per_cu) * c->num_cu / std::max(1, c->item_share));
     const bool gas_pass = &P == &c->X->gp;
     const uint32_t split = uint32_t(gas_pass ? 2 * c->split : c->split);
-    const ItemCut cut = gas_pass || c->fp64_sums ? ItemCut{split, 1u, 4u * target, 0u}
-                                                 : ItemCut{split, 4u, target, 4u * target};
+    const uint32_t fine = 4u * target;
+    const ItemCut cut = gas_pass || c->fp64_sums ? ItemCut{split, 1u, fine, 0u, (gas_pass ? 16u : 24u) * fine, target}
+                                                 : ItemCut{split, 4u, target, fine, ~0u, target};
     ENSURE(c, P.slices, 4);
     hipLaunchKernelGGL(k_tile_items, dim3(blocks_for(nt + 1, 256)), dim3(256), 0, c->stream, nt,
                        P.off.as<const uint64_t>(), P.soff.as<const uint64_t>(), P.woff.as<const uint64_t>(),
@@ -767,7 +768,7 @@ dmb_status gather_and_fill(dmb_ctx* c, Cells& X, const dmb_particles* gas, const
         ENSURE(c, X.part_pm, size_t(X.dp.nitems) * kTile * 4);
         ENSURE(c, X.part_nb, size_t(X.dp.nitems) * kTile);
         ENSURE(c, X.psum_own, size_t(D.n_own) * 8);
-        ENSURE(c, X.slist, size_t(D.n_own) * 4); ENSURE(c, X.mlist, size_t(D.n_own) * 4);
+        ENSURE(c, X.slist, size_t(D.n_own) * 4);
         if (resolve_may_widen(X)) ENSURE(c, X.rwide, kResolveWide * sizeof(ResolveWide));
     }
     auto gas_gather = [&] {
@@ -906,7 +907,7 @@ ResolveArgs resolve_args(dmb_ctx* c, Cells& X, const DmPassArgs& a, const dmb_pa
     r.scount = a.scount; r.slist = X.slist.as<const uint32_t>();
     r.wide = resolve_may_widen(X) ? X.rwide.as<ResolveWide>() : nullptr;
     r.wcount = const_cast<uint32_t*>(a.scount) + kQueueStride / 2;
-    r.mcount = r.wcount + 2; r.mlist = X.mlist.as<uint32_t>();
+    r.mcount = r.wcount + 2; r.mlist = X.dm.keys2.as<uint32_t>();   // sort scratch, free after the build
     r.err = c->os_err.as<uint32_t>();
     r.dv = out->dv_dm; r.partner = out->partner; r.counters = counters;
     return r;
@@ -1082,7 +1083,7 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
             ENSURE(c, X.part_pm, size_t(X.dp.nitems) * kTile * 4);
             ENSURE(c, X.part_nb, size_t(X.dp.nitems) * kTile);
             ENSURE(c, X.psum_own, size_t(X.dm.n_own) * 8);
-            ENSURE(c, X.slist, size_t(X.dm.n_own) * 4); ENSURE(c, X.mlist, size_t(X.dm.n_own) * 4);
+            ENSURE(c, X.slist, size_t(X.dm.n_own) * 4);
             if (resolve_may_widen(X)) ENSURE(c, X.rwide, kResolveWide * sizeof(ResolveWide));
         }
         ENSURE(c, X.qctr, kQueueWords * 4);
@@ -1446,7 +1447,7 @@ void free_cells(Cells& X)
         for (DevBuf* b : all) fr(*b);
     }
     DevBuf* rest[] = {&X.part_gas, &X.part_p, &X.part_pm, &X.part_nb, &X.psum_own, &X.qctr, &X.slist,
-                      &X.mlist, &X.rwide};
+                      &X.rwide};
     for (DevBuf* b : rest) fr(*b);
 }
 

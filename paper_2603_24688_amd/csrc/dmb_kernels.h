@@ -787,7 +787,9 @@ __global__ __launch_bounds__(256) void k_expand(int64_t npairs, const uint32_t* 
 // coarse as that order was laid down (32 per compute unit, at least 4 sub-tiles), and
 // slices, which begin no group anew, give the rest: 0.33 instead of 0.59 ms for the DM
 // pass of a galaxy of 12k + 48k.
-struct ItemCut { uint32_t split, min_split, target, items; };
+// Beyond `most` candidate sub-tiles the finer pieces would add partial sums (2 KB per gas
+// item) and no speed: `coarse` pieces of at least 4 sub-tiles there.
+struct ItemCut { uint32_t split, min_split, target, items, most, coarse; };
 constexpr uint32_t kMaxSlices = 4;
 
 // Per owner tile: its candidate sub-tile count, where its list starts and
@@ -803,9 +805,11 @@ __global__ __launch_bounds__(256) void k_tile_items(int64_t nt, const uint64_t* 
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (t > nt) return;
     const uint64_t total = soff[poff[nt]];
+    const bool fine = total <= cut.most;
+    const uint32_t target = fine ? cut.target : cut.coarse, least = fine ? cut.min_split : 4u;
     uint32_t s = cut.split;
-    if (cut.target > 0 && s > cut.min_split)
-        s = uint32_t(max<uint64_t>(cut.min_split, min<uint64_t>(s, (total + cut.target - 1) / cut.target)));
+    if (target > 0 && s > least)
+        s = uint32_t(max<uint64_t>(least, min<uint64_t>(s, (total + target - 1) / target)));
     const uint32_t ns = uint32_t(max<uint64_t>(1, min<uint64_t>(kMaxSlices, uint64_t(cut.items) * s / max<uint64_t>(total, 1))));
     if (t == nt) { scnt[t] = 0u; icnt[t] = 0u; *slices = ns; return; }
     const uint64_t b = soff[poff[t]], e = soff[poff[t + 1]];
