@@ -129,13 +129,6 @@ __device__ __forceinline__ double overlap_integral(double delta, double eta, dou
 
 constexpr double kOverlapScale = 128.0 / kPi;    // 2 pi (8/pi)^2
 
-__device__ double overlap_H_exact(double delta, double eta)
-{
-    if (delta >= 1.0 + eta) return 0.0;
-    const double ie = 1.0 / eta;
-    return kOverlapScale * overlap_integral(delta, eta, ie, delta > 0.0 ? eta * eta / delta : 0.0) * (ie * ie * ie);
-}
-
 // ---------------------------------------------------------------------------
 // Overlap for the binary32 path (Appendix D tabulates the overlap; here the
 // table keeps RELATIVE accuracy over the whole support, down to pairs that

@@ -3275,8 +3275,103 @@ __global__ __launch_bounds__(64) void k_run_diag_final(RunDiagArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// Overlap table (Appendix D), built on the device from the exact overlap (the
-// regions and envelopes are described above overlap_g_table).
+// Overlap table (Appendix D), built on the device once per context from the exact
+// overlap (the regions and envelopes are described above overlap_g_table).
+//
+// The nodes keep a rule of their own, nine pieces of [0, 1] with five nodes each:
+// the differences below amplify the rounding of H, so the coefficients, and with
+// them every binary32 result, are those of this rule's rounding.  With
+// overlap_integral, which is exact to rounding too, 101 387 of the 524 288
+// coefficients moved, by up to 2.4e-8, and with them a rare pair (8 of 2e8 in a galaxy of 1M + 4M,
+// a unit or two in the last place of g).
+
+// psi(Q) = int_0^Q q w(q) dq differences on one polynomial branch, factored so
+// that a small b - a keeps relative accuracy (Appendix D inner integral).
+__device__ __forceinline__ double psi_piece(int br, double a, double b, double bma)
+{
+    const double c = 8.0 / kPi;
+    if (br == 0) {
+        double a2 = a * a, b2 = b * b;
+        double s1 = a + b;
+        double s3 = (a2 + b2) * s1;
+        double s4 = b2 * b2 + b2 * b * a + b2 * a2 + b * a2 * a + a2 * a2;
+        return c * bma * (0.5 * s1 - 1.5 * s3 + 1.2 * s4);
+    }
+    if (br == 1) {
+        double pa = 1.0 - a, pb = 1.0 - b;
+        double pa2 = pa * pa, pb2 = pb * pb;
+        double t3 = (pa2 + pb2) * (pa + pb);
+        double t4 = pa2 * pa2 + pa2 * pa * pb + pa2 * pb2 + pa * pb2 * pb + pb2 * pb2;
+        return c * bma * (0.5 * t3 - 0.4 * t4);
+    }
+    return 0.0;
+}
+
+// psi(b) - psi(a) for 0 <= a <= b (bma = b - a, formed by the caller without
+// cancellation): the part of [a, b] on each polynomial branch ([0, 1/2],
+// (1/2, 1]; psi is flat past 1), each by its factored difference.
+__device__ __forceinline__ double psi_range(double a, double b, double bma)
+{
+    const bool a0 = a <= 0.5, a1 = a <= 1.0, b0 = b <= 0.5, b1 = b <= 1.0;
+    // branch 0 holds [a, min(b, 1/2)] when a <= 1/2
+    const double hi0 = b0 ? b : 0.5;
+    const double p0 = psi_piece(0, a, hi0, b0 ? bma : 0.5 - a);
+    // branch 1 holds [max(a, 1/2), min(b, 1)] when a <= 1 and b > 1/2
+    const double lo1 = a0 ? 0.5 : a, hi1 = b1 ? b : 1.0;
+    const double p1 = psi_piece(1, lo1, hi1, (!a0 && b1) ? bma : hi1 - lo1);
+    return (a0 ? p0 : 0.0) + ((a1 && !b0) ? p1 : 0.0);
+}
+
+// H(delta, eta) = h_b^3 g (see overlap_integral); between consecutive breakpoints the
+// integrand s w(s) (eta^2/delta) [psi(b) - psi(a)] is one polynomial of degree 9 in s (8
+// for delta = 0), so 5-point Gauss-Legendre on each piece is exact up to rounding.
+__device__ double gtab_H(double delta, double eta)
+{
+    if (delta >= 1.0 + eta) return 0.0;
+    // 5-point Gauss-Legendre: nodes 0, +-gx[1], +-gx[2] with weights gw[0..2]
+    const double gx[3] = {0.0, 0.5384693101056830910, 0.9061798459386639928};
+    const double gw[3] = {0.5688888888888888889, 0.4786286704993664680, 0.2369268850561890875};
+    // breakpoints of the integrand inside (0, 1), clamped to [0, 1] (those outside give
+    // empty pieces), sorted by Batcher's odd-even merge network in registers
+    double bp[10] = {0.0, 0.5, delta, delta - 0.5 * eta, delta + 0.5 * eta, delta - eta, delta + eta,
+                     0.5 * eta - delta, eta - delta, 1.0};
+#pragma unroll
+    for (int k = 1; k < 9; ++k) bp[k] = fmin(fmax(bp[k], 0.0), 1.0);
+    constexpr int kNet[19][2] = {{1, 2}, {3, 4}, {5, 6}, {7, 8}, {1, 3}, {2, 4}, {5, 7}, {6, 8}, {2, 3}, {6, 7},
+                                 {1, 5}, {2, 6}, {3, 7}, {4, 8}, {3, 5}, {4, 6}, {2, 3}, {4, 5}, {6, 7}};
+#pragma unroll
+    for (int k = 0; k < 19; ++k) {
+        const double x = bp[kNet[k][0]], y = bp[kNet[k][1]];
+        bp[kNet[k][0]] = fmin(x, y);
+        bp[kNet[k][1]] = fmax(x, y);
+    }
+    // s^2 w(s) F(s) = s w(s) (eta^2/delta) [psi(b) - psi(a)]: one factor s cancels, and the
+    // two quotients are formed once per pair, so the nodes take no division
+    const double ie = 1.0 / eta, c_ed = delta > 0.0 ? eta * eta / delta : 0.0;
+    double acc = 0.0;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        const double lo = bp[k], hi = bp[k + 1];
+        if (!(hi > lo)) continue;
+        double half = 0.5 * (hi - lo), mid = 0.5 * (hi + lo), piece = 0.0;
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            const double s = mid + half * (q < 2 ? -gx[2 - q] : gx[q - 2]);
+            const double wq = q < 2 ? gw[2 - q] : gw[q - 2];
+            double sF;
+            if (delta == 0.0) {
+                sF = 2.0 * s * kernel_w(s * ie);
+            } else {
+                const double a = fabs(s - delta) * ie, b = (s + delta) * ie, bma = 2.0 * fmin(s, delta) * ie;
+                sF = c_ed * psi_range(a, b, bma);
+            }
+            piece += wq * s * kernel_w(s) * sF;
+        }
+        acc += half * piece;
+    }
+    return 2.0 * kPi * acc / (eta * eta * eta);
+}
+
 // Shell ratio QA(rho, eta) = H(1 + eta - eta rho, eta) / (eta^3 rho^8).
 __device__ double gtab_qa(double rho, double eta)
 {
@@ -3286,7 +3381,7 @@ __device__ double gtab_qa(double rho, double eta)
     }
     auto q = [rho](double e) {
         const double r2 = rho * rho, r4 = r2 * r2;
-        return overlap_H_exact(1.0 + e - e * rho, e) / (e * e * e * r4 * r4);
+        return gtab_H(1.0 + e - e * rho, e) / (e * e * e * r4 * r4);
     };
     if (eta > 0.0) return q(eta);
     // eta -> 0: quadratic extrapolation from eta = 1e-3, 2e-3, 3e-3 (QA is smooth in eta; much
@@ -3299,7 +3394,7 @@ __device__ double gtab_qb(double delta, double kappa)
 {
     auto q = [kappa](double dl) {
         const double e = kappa * (1.0 - dl), t = 1.0 - dl;
-        const double H = e > 0.0 ? overlap_H_exact(dl, e) : kernel_w(dl);
+        const double H = e > 0.0 ? gtab_H(dl, e) : kernel_w(dl);
         return H / (t * t * t);
     };
     if (delta < 1.0 - 1e-9) return q(delta);
