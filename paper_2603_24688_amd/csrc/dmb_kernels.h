@@ -3,6 +3,7 @@
 // and the partner resolve.  See dmb.h for the operation each entry computes.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 #include <type_traits>
 
@@ -1134,8 +1135,9 @@ __device__ __forceinline__ int select_bit(uint64_t m, int r)
     return base;
 }
 
-// Per-wave LDS of the test phase.
-struct TestLds {
+// Per-wave LDS of the test phase.  A chunk's test reads px, py and pz, ph as two rows of
+// float4, so both start on 16 bytes in every wave's copy.
+struct alignas(16) TestLds {
     uint32_t dsh[64];             // periodic image of each chunk sub-tile: shift / L per axis, a signed byte each
     int dbase[64];                // first sorted index of each chunk sub-tile; bit 31: every pair of the
                                   // sub-tile is at its tile-level image (clean)
@@ -1146,6 +1148,8 @@ struct TestLds {
     uint64_t mask[64];            // per owner lane: hit mask over the group's slots
     int offs[65];                 // owner-major offsets of the group's hits
 };
+static_assert(sizeof(TestLds) % 16 == 0 && offsetof(TestLds, px) % 16 == 0 && offsetof(TestLds, pz) % 16 == 0,
+              "float4 rows");
 
 // Test-phase state of one wave (owner lane values and the chunk/group cursor).
 struct PairTest {
