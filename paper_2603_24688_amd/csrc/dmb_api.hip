@@ -50,7 +50,8 @@ struct Species {
 struct Pairs {                             // candidate lists: owner tiles of A x sub-tiles of B
     // (owner tile, candidate super-tile) pairs: per-tile counts and offsets, the pairs, their sub-tile masks
     DevBuf cnt, off, psup, ptile, mask, pcnt, soff, pw, woff;
-    DevBuf pad, maxcnt;                    // count-pass copy of the first pad_cap super-tiles per tile; largest count
+    DevBuf pad, maxcnt;                    // count-pass copy of the first pad_cap super-tiles per tile; largest count,
+                                           // then (DM owners) whether a DM may outgrow a block of the partner search
     // groups of 64 owner tiles: bounds (box, h, support, nodes), candidate counts and lists, a spare max
     DevBuf gbox, gh, gsup, gq, gcnt, glist, gmax;
     // candidate sub-tiles: per-tile counts and starts, the lists, work items
@@ -78,6 +79,7 @@ struct Cells {
     Pairs gp, dp;                          // gas owners x DM tiles; DM owners x gas tiles
     DevBuf part_gas, part_p, part_pm, part_nb, psum_own;
     DevBuf qctr, slist, rwide;
+    bool resolve_wide = false;             // some DM may outgrow a block of the partner search (k_resolve_wide)
     int64_t built_ngas = -1, built_ndm = -1;
     const double* built_gas_pos = nullptr;
     const double* built_dm_pos = nullptr;
@@ -393,7 +395,7 @@ dmb_status build_species(dmb_ctx* c, Species& S, const dmb_particles* p)
 }
 
 // Sub-tile ranges and bounds, super- and mega-tiles (needs the sub-tile count), and the
-// bounds of the owner tiles; clears the word *maxcnt.
+// bounds of the owner tiles; clears both words of maxcnt.
 dmb_status build_subtiles(dmb_ctx* c, Species& S, uint32_t* maxcnt)
 {
     S.nown_tile = (S.n_own + kTile - 1) / kTile;
@@ -467,7 +469,7 @@ dmb_status cand_count(dmb_ctx* c, Species& A, Species& B, Pairs& P)
     if (use_groups(c, B)) {
         const int64_t ng = (nt + kTile - 1) / kTile;
         ENSURE(c, P.gbox, ng * 48); ENSURE(c, P.gh, ng * 8); ENSURE(c, P.gsup, ng * 48); ENSURE(c, P.gq, ng * 64);
-        ENSURE(c, P.gcnt, ng * 4); ENSURE(c, P.glist, ng * c->group_cap * 4); ENSURE(c, P.gmax, 4);
+        ENSURE(c, P.gcnt, ng * 4); ENSURE(c, P.glist, ng * c->group_cap * 4); ENSURE(c, P.gmax, 8);
         hipLaunchKernelGGL(k_super_bounds, dim3(unsigned(ng)), dim3(64), 0, c->stream, nt,
                            A.obox.as<const double>(), A.oh.as<const double>(), A.obox.as<const double>(),
                            P.gbox.as<double>(), P.gh.as<double>(), P.gsup.as<double>(), P.gq.as<float4>(),
@@ -528,7 +530,7 @@ dmb_status cand_subs(dmb_ctx* c, Species& A, Species& B, Pairs& P)
     hipLaunchKernelGGL(k_tile_items, dim3(blocks_for(nt + 1, 256)), dim3(256), 0, c->stream, nt,
                        P.off.as<const uint64_t>(), P.soff.as<const uint64_t>(), P.woff.as<const uint64_t>(),
                        P.scnt.as<uint32_t>(), P.beg.as<uint64_t>(), P.swt.as<uint32_t>(),
-                       cut, P.icnt.as<uint32_t>(), P.slices.as<uint32_t>());
+                       cut, P.icnt.as<uint32_t>(), P.slices.as<uint32_t>(), P.maxcnt.as<uint32_t>() + 1);
     s = scan_excl(c, P.icnt.as<const uint32_t>(), P.ioff.as<uint32_t>(), nt + 1);
     if (s != DMB_OK) return s;
     HIPCHK(c, hipGetLastError());
@@ -710,9 +712,6 @@ void by_rows(int nbox, F&& launch)
     for (int b = 0; b < nbox; b += kGridRows) launch(b, unsigned(std::min(kGridRows, nbox - b)));
 }
 
-// A DM can outgrow a block's cache only if the box has that many gas particles or sub-tiles.
-bool resolve_may_widen(const Cells& X) { return X.gas.n > kResolvePairs || X.gas.ntile > kResolveList; }
-
 GasGatherArgs gas_gather_args(Species& G, const dmb_particles* gas, const dmb_params* par)
 {
     GasGatherArgs ga;
@@ -769,7 +768,7 @@ dmb_status gather_and_fill(dmb_ctx* c, Cells& X, const dmb_particles* gas, const
         ENSURE(c, X.part_nb, size_t(X.dp.nitems) * kTile);
         ENSURE(c, X.psum_own, size_t(D.n_own) * 8);
         ENSURE(c, X.slist, size_t(D.n_own) * 4);
-        if (resolve_may_widen(X)) ENSURE(c, X.rwide, kResolveWide * sizeof(ResolveWide));
+        if (X.resolve_wide) ENSURE(c, X.rwide, kResolveWide * sizeof(ResolveWide));
     }
     auto gas_gather = [&] {
         hipLaunchKernelGGL(k_gather_gas<Real>, dim3(blocks_for(G.n, 256)), dim3(256), 0, c->stream,
@@ -905,18 +904,19 @@ ResolveArgs resolve_args(dmb_ctx* c, Cells& X, const DmPassArgs& a, const dmb_pa
     r.n_gas_bits = bits_for(std::max<int64_t>(X.gas.n, 2));
     r.n_gas = uint32_t(X.gas.n);
     r.scount = a.scount; r.slist = X.slist.as<const uint32_t>();
-    r.wide = resolve_may_widen(X) ? X.rwide.as<ResolveWide>() : nullptr;
+    r.wide = X.resolve_wide ? X.rwide.as<ResolveWide>() : nullptr;
     r.wcount = const_cast<uint32_t*>(a.scount) + kQueueStride / 2;
     r.mcount = r.wcount + 2; r.mlist = X.dm.keys2.as<uint32_t>();   // sort scratch, free after the build
-    r.err = c->os_err.as<uint32_t>();
     r.dv = out->dv_dm; r.partner = out->partner; r.counters = counters;
     return r;
 }
 
+int wide_passes(const ResolveArgs& r) { return r.wide ? (r.n_gas_bits + 7) / 8 : 0; }
+
 // The partner resolve of one box (dev: null) or of all boxes of a batch (args in device memory);
-// n_dm: the most DM that can scatter; wide: some DM may outgrow a block.
+// n_dm: the most DM that can scatter; wide: radix passes of the DM that may outgrow a block (0: none may).
 template <typename Real, int N, bool RB, bool BATCH>
-void launch_resolve(dmb_ctx* c, const ResolveArgs& r, const ResolveArgs* dev, int nbox, int64_t n_dm, bool wide)
+void launch_resolve(dmb_ctx* c, const ResolveArgs& r, const ResolveArgs* dev, int nbox, int64_t n_dm, int wide)
 {
     constexpr bool kExact = sizeof(Real) == 8;
     Phase ph(c, DMB_PH_RESOLVE);
@@ -926,11 +926,11 @@ void launch_resolve(dmb_ctx* c, const ResolveArgs& r, const ResolveArgs* dev, in
                            nbox);
     hipLaunchKernelGGL((k_resolve<Real, N, kExact, RB, BATCH, false>), grid(2), dim3(kResolveThreads), 0, c->stream, r,
                        dev, nbox);
-    if (wide)
+    for (int ps = 0; ps < wide; ++ps)
         by_rows(nbox, [&](int b, unsigned rows) {
             hipLaunchKernelGGL((k_resolve_wide<Real, N, kExact, RB, BATCH>),
                                dim3(unsigned(std::max(8, c->num_cu / nbox)), rows), dim3(kResolveThreads), 0, c->stream, r,
-                               dev ? dev + b : nullptr);
+                               dev ? dev + b : nullptr, ps);
         });
     if constexpr (RB)
         hipLaunchKernelGGL((k_rb_kick<Real, N, BATCH>), grid(4), dim3(64), 0, c->stream, r, dev, nbox);
@@ -946,7 +946,7 @@ void combine_dm_and_resolve(dmb_ctx* c, Cells& X, const DmPassArgs& a, const dmb
                            c->stream, dm_combine_args(X, a, out, counters), (const DmCombineArgs*)nullptr);
     }
     const ResolveArgs r = resolve_args(c, X, a, gas, par, out, counters);
-    launch_resolve<Real, N, RB, false>(c, r, nullptr, 1, X.dm.n_own, r.wide != nullptr);
+    launch_resolve<Real, N, RB, false>(c, r, nullptr, 1, X.dm.n_own, wide_passes(r));
 }
 
 // The DM pair pass of one step (RB: Rao-Blackwellised sampling, expected
@@ -1051,7 +1051,7 @@ struct BatchPlan {
     size_t at_da = 0, at_ra = 0, at_gg = 0, at_dg = 0, at_fa = 0, at_gc = 0, at_dc = 0;   // offsets in bgeom (ga at 0)
     int64_t most_gas = 0, most_n = 0;      // active gas, particles of either species of the largest box
     int64_t most_dm = 0;                   // active DM of the largest box
-    bool resolve_wide = false;             // some box may need k_resolve_wide
+    int wide = 0;                          // most radix passes of k_resolve_wide that a box may need
     int nb_gas = 0, nb_dm = 0;
     bool rb = false;                       // Rao-Blackwellised DM sampling
 };
@@ -1068,7 +1068,7 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
     P.ra.resize(nbox);
     P.gg.clear(); P.dg.clear(); P.fa.clear(); P.gc.clear(); P.dc.clear();
     P.most_gas = P.most_n = 0;
-    P.resolve_wide = false;
+    P.wide = 0;
     P.most_dm = 0;
     std::vector<int64_t> gi(nbox + 1, 0), di(nbox + 1, 0);
     // global queues (gas, DM), then the Philox step offset
@@ -1084,7 +1084,7 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
             ENSURE(c, X.part_nb, size_t(X.dp.nitems) * kTile);
             ENSURE(c, X.psum_own, size_t(X.dm.n_own) * 8);
             ENSURE(c, X.slist, size_t(X.dm.n_own) * 4);
-            if (resolve_may_widen(X)) ENSURE(c, X.rwide, kResolveWide * sizeof(ResolveWide));
+            if (X.resolve_wide) ENSURE(c, X.rwide, kResolveWide * sizeof(ResolveWide));
         }
         ENSURE(c, X.qctr, kQueueWords * 4);
         const int rs = int(sizeof(Real));
@@ -1102,7 +1102,7 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
         P.ga[b] = gas_pass_args<Real, N, RM>(c, X, gas + b, par + b, out + b, counters);
         P.da[b] = dm_pass_args(c, X, par + b, out + b, counters, step_off);
         P.ra[b] = resolve_args(c, X, P.da[b], gas + b, par + b, out + b, counters);
-        if (X.dp.nitems > 0 && P.ra[b].wide) P.resolve_wide = true;
+        if (X.dp.nitems > 0) P.wide = std::max(P.wide, wide_passes(P.ra[b]));
         P.most_dm = std::max(P.most_dm, X.dm.n_own);
         P.most_gas = std::max(P.most_gas, X.gas.n_own);
         P.most_n = std::max({P.most_n, G.n, D.n});
@@ -1172,7 +1172,7 @@ void batch_dm_side(dmb_ctx* c, const BatchPlan& P, const DmPassArgs* ddev, const
         });
     }
     launch_resolve<Real, N, RB, true>(c, P.ra[0], reinterpret_cast<const ResolveArgs*>(base + P.at_ra), P.nbox,
-                                      P.most_dm * P.nbox, P.resolve_wide);
+                                      P.most_dm * P.nbox, P.wide);
 }
 
 template <typename Real, int N, int RM>
@@ -1732,14 +1732,14 @@ dmb_status build_cells_impl(dmb_ctx* c, const dmb_particles* gas, const dmb_part
         if (v[4] != 0) {
             hipLaunchKernelGGL(k_os_clear, dim3(1), dim3(256), 0, c->stream, c->os_err.as<uint32_t>(), 1);
             c->X->built_ngas = c->X->built_ndm = -1;
-            return fail(c, DMB_EHIP, "a wait of the radix sort or the partner search gave up");
+            return fail(c, DMB_EHIP, "radix sort: a look-back wait gave up");
         }
         c->X->gas.n_own = int64_t(v[0]);
         c->X->gas.ntile = int64_t(v[1]);
         c->X->dm.n_own = int64_t(v[2]);
         c->X->dm.ntile = int64_t(v[3]);
     }
-    ENSURE(c, X.gp.maxcnt, 4); ENSURE(c, X.dp.maxcnt, 4);
+    ENSURE(c, X.gp.maxcnt, 8); ENSURE(c, X.dp.maxcnt, 8);
     s = both(c, [&] { return build_subtiles(c, X.gas, X.gp.maxcnt.as<uint32_t>()); },
              [&] { return build_subtiles(c, X.dm, X.dp.maxcnt.as<uint32_t>()); });
     if (s != DMB_OK) return s;
@@ -1791,8 +1791,10 @@ dmb_status build_cells_impl(dmb_ctx* c, const dmb_particles* gas, const dmb_part
             r.u64(A.nown_tile > 0 && P.npairs > 0 ? P.soff.as<uint64_t>() + P.npairs : nullptr);
             r.u32(A.nown_tile > 0 ? P.ioff.as<uint32_t>() + A.nown_tile : nullptr);
         }
-        uint64_t v[4];
+        r.u32(X.dm.nown_tile > 0 && X.dp.npairs > 0 ? X.dp.maxcnt.as<uint32_t>() + 1 : nullptr);
+        uint64_t v[5];
         if ((s = readback(c, r, v)) != DMB_OK) return s;
+        X.resolve_wide = v[4] != 0;
         for (int k = 0; k < 2; ++k) {
             tot[k] = v[2 * k];
             nit[k] = uint32_t(v[2 * k + 1]);

@@ -352,7 +352,7 @@ __device__ __forceinline__ void write_node_q(float4* q, const double b[6], doubl
     q[3] = make_float4(__double2float_ru(u[3]), __double2float_ru(u[4]), __double2float_ru(u[5]), 0.f);
 }
 
-// Super-tile bounds over 64 consecutive tiles: box, max h, support box; clears *word.
+// Super-tile bounds over 64 consecutive tiles: box, max h, support box; clears word[0], word[1].
 __global__ __launch_bounds__(64) void k_super_bounds(int64_t ntile, const double* __restrict__ tbox,
                                                      const double* __restrict__ th, const double* __restrict__ tsup,
                                                      double* __restrict__ box, double* __restrict__ hmax,
@@ -362,7 +362,7 @@ __global__ __launch_bounds__(64) void k_super_bounds(int64_t ntile, const double
     int64_t s = blockIdx.x;
     int64_t t = s * kTile + lane_id();
     bool v = t < ntile;
-    if (t == 0) *word = 0u;
+    if (t < 2) word[t] = 0u;
     double b[6], u[6];
     for (int a = 0; a < 3; ++a) {
         b[a] = v ? tbox[6 * t + a] : 1e300;
@@ -793,15 +793,21 @@ __global__ __launch_bounds__(256) void k_expand(int64_t npairs, const uint32_t* 
 struct ItemCut { uint32_t split, min_split, target, items, most, coarse; };
 constexpr uint32_t kMaxSlices = 4;
 
+// What a block of the partner search holds of one scattering DM in LDS (k_resolve).
+constexpr int kResolveList = 2048;    // candidate sub-tiles kept after the point test
+constexpr int kResolvePairs = 8192;   // pairs cached (the registers allow one block per CU anyway)
+
 // Per owner tile: its candidate sub-tile count, where its list starts and
 // the particles of its candidates (poff: pair offsets per tile, soff and
 // woff: sub-tile and particle offsets per pair), and its work items; also the
-// number of slices.
+// number of slices, and whether some tile's candidates are more than a block of the
+// partner search can hold (*wide, cleared before).
 __global__ __launch_bounds__(256) void k_tile_items(int64_t nt, const uint64_t* __restrict__ poff,
                                                     const uint64_t* __restrict__ soff, const uint64_t* __restrict__ woff,
                                                     uint32_t* __restrict__ scnt, uint64_t* __restrict__ sbeg,
                                                     uint32_t* __restrict__ swt, ItemCut cut,
-                                                    uint32_t* __restrict__ icnt, uint32_t* __restrict__ slices)
+                                                    uint32_t* __restrict__ icnt, uint32_t* __restrict__ slices,
+                                                    uint32_t* __restrict__ wide)
 {
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (t > nt) return;
@@ -818,6 +824,7 @@ __global__ __launch_bounds__(256) void k_tile_items(int64_t nt, const uint64_t* 
     scnt[t] = uint32_t(e - b);
     swt[t] = uint32_t(min<uint64_t>(woff[poff[t + 1]] - woff[poff[t]], 0xFFFFFFFFull));
     icnt[t] = (uint32_t(e - b) + s - 1) / s * ns;
+    if (e - b > uint64_t(kResolveList) || swt[t] > uint32_t(kResolvePairs)) *wide = 1u;
 }
 
 // Item it: its tile t (binary search over item_off), the piece of t's
@@ -2411,12 +2418,12 @@ __global__ __launch_bounds__(64 * kCombineWaves) void k_combine_dm(DmCombineArgs
 // overlap is most of the work), and every radix pass reads the cached (gas index,
 // P_ij), its 256 bins summed by one wavefront without barriers.
 // A DM with more sub-tiles or pairs than the cache holds goes to a list, and
-// k_resolve_wide spreads the pairs of its few entries over the whole chip; in each
-// radix pass the last block of a DM to finish picks the digit.
+// k_resolve_wide spreads the pairs of its few entries over the whole chip, one launch
+// per radix pass; the last block of a DM to finish picks the digit.
 struct ResolveWide {              // state of one entry of that list
     unsigned long long hi[256], lo[256];
     uint32_t s;                   // the DM's owner slot
-    uint32_t prefix, done, pass;  // digits picked so far, slices finished in this pass, passes finished
+    uint32_t prefix, done;        // digits picked so far, slices finished in this pass
     unsigned long long below[2];
 };
 struct ResolveArgs {
@@ -2435,8 +2442,7 @@ struct ResolveArgs {
     uint32_t n_gas;
     const uint32_t* scount; const uint32_t* slist;
     uint32_t* mcount; uint32_t* mlist;    // DM that the one-wavefront search passed on
-    ResolveWide* wide; uint32_t* wcount;  // nullptr: no DM can outgrow the cache; entries, [1]: tickets
-    uint32_t* err;                // raised if a wait gave up
+    ResolveWide* wide; uint32_t* wcount;  // the wide list (nullptr: no DM can outgrow a block) and its entries
     double* dv; int32_t* partner;
     uint64_t* counters;
 };
@@ -2578,8 +2584,6 @@ __device__ void scatter_kick(const ResolveArgs& a, uint32_t oid, uint32_t j, uin
 
 constexpr int kResolveThreads = 512;  // eight wavefronts: the most that leaves the overlap its registers
 constexpr int kResolveWaves = kResolveThreads / 64;
-constexpr int kResolveList = 2048;    // candidate sub-tiles kept per scattering DM after the point test
-constexpr int kResolvePairs = 8192;   // pairs cached per scattering DM (LDS; the registers allow one block per CU anyway)
 // Where more than kResolveMany DM scatter (two rounds of blocks), one wavefront per DM
 // comes first, eight to a CU, with a cache of kResolveFewPairs; it passes the larger
 // ones on; blocks share the DM of all boxes of a batch.  A step of eight boxes whose
@@ -2588,7 +2592,6 @@ constexpr uint32_t kResolveMany = 512;
 constexpr int kResolveFewList = 256, kResolveFewPairs = 1024;
 constexpr int kResolveWide = 256;     // DM spread over the chip (beyond these, enough blocks are busy anyway)
 constexpr int kResolveStreams = 4;    // sub-tiles a wavefront (candidates a thread) tests at a time
-constexpr uint32_t kResolveSpinMax = 1u << 24;
 
 // The scattering DM of owner slot s.
 template <typename Real>
@@ -2903,7 +2906,7 @@ __global__ __launch_bounds__(FEW ? 64 : kResolveThreads) void k_resolve(ResolveA
             if (ws <= uint32_t(kResolveWide)) {
                 ResolveWide& W = a.wide[ws - 1u];
                 if (tid < 256) { W.hi[tid] = 0ull; W.lo[tid] = 0ull; }
-                if (tid == 0) { W.s = uint32_t(s); W.prefix = 0u; W.done = 0u; W.pass = 0u; W.below[0] = 0ull; W.below[1] = 0ull; }
+                if (tid == 0) { W.s = uint32_t(s); W.prefix = 0u; W.done = 0u; W.below[0] = 0ull; W.below[1] = 0ull; }
                 __syncthreads();
                 continue;
             }
@@ -2947,47 +2950,35 @@ __global__ __launch_bounds__(FEW ? 64 : kResolveThreads) void k_resolve(ResolveA
     }
 }
 
-// The DM on the wide list.  Each radix pass of a DM is split into as many slices of
-// its candidates (strided, so that near and far ones mix) as the grid has blocks
-// for; a slice's histogram is summed in LDS and added to the DM's, and the last
-// slice to finish picks the digit and clears the histogram for the next pass.
-// Blocks take (pass, DM, slice) by tickets, pass by pass, so a block only ever waits
-// for the digit of a pass whose slices are all held by running blocks; the wait is
-// still bounded (kResolveSpinMax polls, then an error flag is raised).
+// One radix pass (ps) of the DM on the wide list.  A DM's candidates are split into as
+// many slices (strided, so that near and far ones mix) as the grid has blocks for; a
+// slice's histogram is summed in LDS and added to the DM's, and the last slice to
+// finish picks the digit and clears the histogram for the next pass.  The next pass
+// needs that digit, so it is a launch of its own: no block waits for another.  An empty
+// launch still costs about 5 us beside the gas pass, so none is made where no owner
+// tile's candidates could fill the list (k_tile_items).
 template <typename Real, int N, bool EXACT_G, bool RB = false, bool BATCH = false>
-__global__ __launch_bounds__(kResolveThreads) void k_resolve_wide(ResolveArgs a0, const ResolveArgs* __restrict__ boxes)
+__global__ __launch_bounds__(kResolveThreads) void k_resolve_wide(ResolveArgs a0, const ResolveArgs* __restrict__ boxes,
+                                                                 int ps)
 {
     __shared__ unsigned long long hhi[256], hlo[256];
-    __shared__ uint32_t s_last, s_ticket, s_prefix;
+    __shared__ uint32_t s_last;
     const ResolveArgs& a = BATCH ? boxes[blockIdx.y] : a0;
-    if (!a.wide) return;
+    const int npass = (a.n_gas_bits + 7) / 8;
+    if (!a.wide || ps >= npass) return;
     const uint32_t nw = min(*a.wcount, uint32_t(kResolveWide));
     if (nw == 0u) return;
-    const int npass = (a.n_gas_bits + 7) / 8;
     const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t step = a.step + (a.step_off ? *a.step_off : 0u);
-    const uint32_t S = max(1u, gridDim.x / nw), per = nw * S;
-    for (;;) {
-        if (tid == 0) s_ticket = atomicAdd(a.wcount + 1, 1u);
-        __syncthreads();
-        const uint32_t tk = s_ticket;
-        if (tk >= uint32_t(npass) * per) return;
-        const uint32_t ps = tk / per, u = tk % per, slice = u % S;
+    const int shft = 8 * (npass - 1 - ps);
+    const uint32_t S = max(1u, gridDim.x / nw);
+    for (uint32_t u = blockIdx.x; u < nw * S; u += gridDim.x) {
         ResolveWide& W = a.wide[u / S];
-        if (tid == 0) {
-            uint32_t polls = 0;
-            while (__hip_atomic_load(&W.pass, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < ps) {
-                if (++polls == kResolveSpinMax) { atomicOr(a.err, 1u); break; }
-                __builtin_amdgcn_s_sleep(1);
-            }
-            s_prefix = __hip_atomic_load(&W.prefix, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
         if (tid < 256) { hhi[tid] = 0ull; hlo[tid] = 0ull; }
         __syncthreads();
-        const int shft = 8 * (npass - 1 - int(ps));
-        const uint32_t prefix = s_prefix;
+        const uint32_t prefix = W.prefix;
         const ResolveDm<Real> m(a, int64_t(W.s), step);
-        resolve_walk<Real, N, EXACT_G, RB>(a, m, step, lane, uint64_t(slice) * kResolveWaves + w, uint64_t(S) * kResolveWaves,
+        resolve_walk<Real, N, EXACT_G, RB>(a, m, step, lane, uint64_t(u % S) * kResolveWaves + w, uint64_t(S) * kResolveWaves,
                                            [&](uint32_t gid, double P) { hist_add(hhi, hlo, shft, prefix, gid, P); });
         __syncthreads();
         if (tid < 256) {
@@ -3000,26 +2991,21 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve_wide(ResolveArgs a0
         __syncthreads();
         if (s_last && w == 0) {
             __threadfence();
-            unsigned __int128 v[4], below, before, after;
+            unsigned __int128 v[4], before, after;
             for (int k = 0; k < 4; ++k) {   // read and cleared where the adds were made
                 const uint64_t hi = atomicExch(&W.hi[4 * lane + k], 0ull), lo = atomicExch(&W.lo[4 * lane + k], 0ull);
                 v[k] = ((unsigned __int128)hi << 32) + (unsigned __int128)lo;
             }
-            const uint64_t b0 = __hip_atomic_load(&W.below[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint64_t b1 = __hip_atomic_load(&W.below[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            below = ((unsigned __int128)b1 << 64) | b0;
+            const unsigned __int128 below = ((unsigned __int128)W.below[1] << 64) | W.below[0];
             const uint32_t sel = radix_pick(lane, v, below, m.U, &before, &after), pf = (prefix << 8) | sel;
             if (lane == 0) {
-                __hip_atomic_store(&W.prefix, pf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&W.below[0], (unsigned long long)before, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&W.below[1], (unsigned long long)(before >> 64), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&W.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (int(ps) == npass - 1) resolve_finish<Real, RB>(a, m, step, pf, before, after);
+                W.prefix = pf;
+                W.below[0] = (unsigned long long)before;
+                W.below[1] = (unsigned long long)(before >> 64);
+                W.done = 0u;
+                if (ps == npass - 1) resolve_finish<Real, RB>(a, m, step, pf, before, after);
             }
-            __threadfence();
-            if (lane == 0) __hip_atomic_store(&W.pass, ps + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         }
-        __syncthreads();
     }
 }
 
