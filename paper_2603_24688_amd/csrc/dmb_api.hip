@@ -125,7 +125,6 @@ struct dmb_ctx {
     int item_target_per_cu = 32;           // small problems: split candidate lists into about this many
                                            // work items per compute unit, four times as many by the finer
                                            // cuts of either pass (ItemCut; 0: always `split`)
-    bool fp64_sums = false;                // the build under way is for binary64 steps
     int item_share = 1;                    // boxes that share the chip in the build under way (batch)
     int subtile_delta = 1;                 // (tunable) sub-tile cut: Morton level below (median - delta)
     int group_cap = 1024;                  // candidate-search group list capacity (0: no group pass)
@@ -524,8 +523,8 @@ dmb_status cand_subs(dmb_ctx* c, Species& A, Species& B, Pairs& P)
     const bool gas_pass = &P == &c->X->gp;
     const uint32_t split = uint32_t(gas_pass ? 2 * c->split : c->split);
     const uint32_t fine = 4u * target;
-    const ItemCut cut = gas_pass || c->fp64_sums ? ItemCut{split, 1u, fine, 0u, (gas_pass ? 16u : 24u) * fine, target}
-                                                 : ItemCut{split, 4u, target, fine, ~0u, target};
+    const ItemCut cut = gas_pass ? ItemCut{split, 1u, fine, 0u, 16u * fine, target}
+                                 : ItemCut{split, 4u, target, fine, ~0u, target};
     ENSURE(c, P.slices, 4);
     hipLaunchKernelGGL(k_tile_items, dim3(blocks_for(nt + 1, 256)), dim3(256), 0, c->stream, nt,
                        P.off.as<const uint64_t>(), P.soff.as<const uint64_t>(), P.woff.as<const uint64_t>(),
@@ -1712,7 +1711,6 @@ dmb_status build_cells_impl(dmb_ctx* c, const dmb_particles* gas, const dmb_part
 {
     dmb_status s;
     const bool periodic = par->box[0] > 0.0 || par->box[1] > 0.0 || par->box[2] > 0.0;
-    c->fp64_sums = par->precision == DMB_FP64;
     Phase ph(c, DMB_PH_BUILD);
     for (int k = 0; k < 3; ++k) c->X->built_L[k] = periodic ? par->box[k] : 0.0;
     Cells& X = *c->X;

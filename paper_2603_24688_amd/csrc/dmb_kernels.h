@@ -782,14 +782,16 @@ __global__ __launch_bounds__(256) void k_expand(int64_t npairs, const uint32_t* 
 // `split` sub-tiles, fewer in a small problem (down to min_split) so that about
 // `target` pieces keep every compute unit busy; then, while there are fewer than
 // `items` of them, each piece into up to kMaxSlices slices, which share its chunks of
-// sub-tiles and take its groups of 64 slots in turn.  Binary64 sums (the gas pass, and
-// the DM pass of a structure built for binary64) are cut down to one sub-tile.  The DM pass in binary32 adds up to 64 terms of a group
-// in binary32, so where its groups begin is part of its result: its pieces stay as
-// coarse as that order was laid down (32 per compute unit, at least 4 sub-tiles), and
-// slices, which begin no group anew, give the rest: 0.33 instead of 0.59 ms for the DM
-// pass of a galaxy of 12k + 48k.
+// sub-tiles and take its groups of 64 slots in turn.  The gas pass, whose sums are
+// binary64 in either precision, is cut down to one sub-tile.  The DM pass in binary32
+// adds up to 64 terms of a group in binary32, so where its groups begin is part of its
+// result: its pieces stay as coarse as that order was laid down (32 per compute unit, at
+// least 4 sub-tiles), and slices, which begin no group anew, give the rest: 0.33
+// instead of 0.59 ms for the DM pass of a galaxy of 12k + 48k.  A structure serves steps
+// of both precisions, so the DM pass has one cut.
 // Beyond `most` candidate sub-tiles the finer pieces would add partial sums (2 KB per gas
-// item) and no speed: `coarse` pieces of at least 4 sub-tiles there.
+// item, 2.5 KB with the closure) and no speed: `coarse` pieces of at least 4 sub-tiles
+// there.
 struct ItemCut { uint32_t split, min_split, target, items, most, coarse; };
 constexpr uint32_t kMaxSlices = 4;
 
