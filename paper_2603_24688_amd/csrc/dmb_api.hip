@@ -703,6 +703,28 @@ dmb_status both(dmb_ctx* c, FA&& a, FB&& b)
     return sj;
 }
 
+// Blocks of each box in the launches over the boxes of a batch.
+enum { kGridGas, kGridDm, kGridFill, kGridCombineGas, kGridCombineDm, kGrids };
+struct BoxGrids {
+    std::vector<int64_t> first[kGrids];    // [boxes + 1], see BoxBlocks
+    size_t at[kGrids] = {};                // places in the item offsets' buffer
+    void clear()
+    {
+        for (auto& f : first) f.assign(1, 0);
+    }
+    void add(int k, int64_t blocks) { first[k].push_back(first[k].back() + blocks); }
+};
+
+// launch(grid, BoxBlocks) over all blocks of grid k, in parts that one launch can hold.
+template <typename F>
+void by_blocks(const BoxGrids& g, const int64_t* dev, int k, F&& launch)
+{
+    constexpr int64_t kMost = int64_t(1) << 22;
+    const int64_t n = g.first[k].back();
+    for (int64_t base = 0; base < n; base += kMost)
+        launch(dim3(unsigned(std::min(kMost, n - base))), BoxBlocks{dev + g.at[k], int(g.first[k].size()) - 1, base});
+}
+
 // launch(first box, boxes) over the boxes of a batch, a grid row each.
 constexpr int kGridRows = 32768;
 template <typename F>
@@ -771,7 +793,7 @@ dmb_status gather_and_fill(dmb_ctx* c, Cells& X, const dmb_particles* gas, const
     }
     auto gas_gather = [&] {
         hipLaunchKernelGGL(k_gather_gas<Real>, dim3(blocks_for(G.n, 256)), dim3(256), 0, c->stream,
-                           gas_gather_args(G, gas, par), (const GasGatherArgs*)nullptr);
+                           gas_gather_args(G, gas, par), (const GasGatherArgs*)nullptr, BoxBlocks{});
     };
     const bool side = overlap && G.n > 0 && D.n > 0;
     if (side) {
@@ -784,11 +806,12 @@ dmb_status gather_and_fill(dmb_ctx* c, Cells& X, const dmb_particles* gas, const
     }
     if (D.n > 0) {
         hipLaunchKernelGGL(k_gather_dm<Real>, dim3(blocks_for(D.n, 256)), dim3(256), 0, c->stream,
-                           dm_gather_args(D, dm, par), (const DmGatherArgs*)nullptr);
+                           dm_gather_args(D, dm, par), (const DmGatherArgs*)nullptr, BoxBlocks{});
     }
     int64_t nfill = std::max<int64_t>(std::max<int64_t>(G.n, D.n), kQueueWords);
     hipLaunchKernelGGL(k_fill_out, dim3(blocks_for(nfill, 256)), dim3(256), 0, c->stream,
-                       fill_args(G.n, D.n, out, counters, X.qctr.as<uint32_t>(), kQueueWords), (const FillArgs*)nullptr);
+                       fill_args(G.n, D.n, out, counters, X.qctr.as<uint32_t>(), kQueueWords), (const FillArgs*)nullptr,
+                       BoxBlocks{});
     if (side) {
         dmb_status s = join(c);
         if (s != DMB_OK) return s;
@@ -852,7 +875,7 @@ void combine_gas(dmb_ctx* c, Cells& X, const dmb_particles* gas, const dmb_param
 {
     hipLaunchKernelGGL((k_combine_gas<N, RM, false>), dim3(unsigned((X.gas.n_own + kTile - 1) / kTile)),
                        dim3(64 * kCombineWaves), 0, c->stream, gas_combine_args(X, gas, par, out),
-                       (const GasCombineArgs*)nullptr);
+                       (const GasCombineArgs*)nullptr, BoxBlocks{});
 }
 
 DmPassArgs dm_pass_args(dmb_ctx* c, Cells& X, const dmb_params* par, dmb_out* out, uint64_t* counters,
@@ -942,7 +965,7 @@ void combine_dm_and_resolve(dmb_ctx* c, Cells& X, const DmPassArgs& a, const dmb
     {
         Phase ph(c, DMB_PH_COMBINE_DM);
         hipLaunchKernelGGL(k_combine_dm<false>, dim3(unsigned((X.dm.n_own + kTile - 1) / kTile)), dim3(64 * kCombineWaves), 0,
-                           c->stream, dm_combine_args(X, a, out, counters), (const DmCombineArgs*)nullptr);
+                           c->stream, dm_combine_args(X, a, out, counters), (const DmCombineArgs*)nullptr, BoxBlocks{});
     }
     const ResolveArgs r = resolve_args(c, X, a, gas, par, out, counters);
     launch_resolve<Real, N, RB, false>(c, r, nullptr, 1, X.dm.n_own, wide_passes(r));
@@ -1048,8 +1071,8 @@ struct BatchPlan {
     std::vector<GasCombineArgs> gc;
     std::vector<DmCombineArgs> dc;
     size_t at_da = 0, at_ra = 0, at_gg = 0, at_dg = 0, at_fa = 0, at_gc = 0, at_dc = 0;   // offsets in bgeom (ga at 0)
-    int64_t most_gas = 0, most_n = 0;      // active gas, particles of either species of the largest box
-    int64_t most_dm = 0;                   // active DM of the largest box
+    BoxGrids grids;
+    int64_t all_dm = 0;                    // active DM of all boxes
     int wide = 0;                          // most radix passes of k_resolve_wide that a box may need
     int nb_gas = 0, nb_dm = 0;
     bool rb = false;                       // Rao-Blackwellised DM sampling
@@ -1066,9 +1089,9 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
     P.da.resize(nbox);
     P.ra.resize(nbox);
     P.gg.clear(); P.dg.clear(); P.fa.clear(); P.gc.clear(); P.dc.clear();
-    P.most_gas = P.most_n = 0;
+    P.grids.clear();
     P.wide = 0;
-    P.most_dm = 0;
+    P.all_dm = 0;
     std::vector<int64_t> gi(nbox + 1, 0), di(nbox + 1, 0);
     // global queues (gas, DM), then the Philox step offset
     ENSURE(c, c->bstep, kQueueWords * sizeof(uint32_t));
@@ -1102,9 +1125,12 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
         P.da[b] = dm_pass_args(c, X, par + b, out + b, counters, step_off);
         P.ra[b] = resolve_args(c, X, P.da[b], gas + b, par + b, out + b, counters);
         if (X.dp.nitems > 0) P.wide = std::max(P.wide, wide_passes(P.ra[b]));
-        P.most_dm = std::max(P.most_dm, X.dm.n_own);
-        P.most_gas = std::max(P.most_gas, X.gas.n_own);
-        P.most_n = std::max({P.most_n, G.n, D.n});
+        P.all_dm += D.n_own;
+        P.grids.add(kGridGas, blocks_for(G.n, 256));
+        P.grids.add(kGridDm, blocks_for(D.n, 256));
+        P.grids.add(kGridFill, blocks_for(std::max<int64_t>({G.n, D.n, kQueueWords}), 256));
+        P.grids.add(kGridCombineGas, X.gp.nitems > 0 ? blocks_for(G.n_own, kTile) : 0);
+        P.grids.add(kGridCombineDm, X.dp.nitems > 0 ? blocks_for(D.n_own, kTile) : 0);
         P.gg.push_back(gas_gather_args(G, gas + b, par + b));
         P.dg.push_back(dm_gather_args(D, dm + b, par + b));
         P.fa.push_back(fill_args(G.n, D.n, out + b, counters, X.qctr.as<uint32_t>(), kQueueWords));
@@ -1117,6 +1143,7 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
     P.dm_items = di[nbox];
     const dmb_out none{};
     P.fa.push_back(fill_args(0, 0, &none, nullptr, c->bstep.as<uint32_t>(), 2 * kXcd * kQueueStride));
+    P.grids.add(kGridFill, blocks_for(kQueueWords, 256));
     size_t bytes = 0;
     auto place = [&](const auto& v) {
         const size_t at = bytes;
@@ -1127,7 +1154,15 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
     P.at_da = place(P.da); P.at_ra = place(P.ra); P.at_gg = place(P.gg); P.at_dg = place(P.dg); P.at_fa = place(P.fa);
     P.at_gc = place(P.gc); P.at_dc = place(P.dc);
     ENSURE(c, c->bgeom, bytes);
-    ENSURE(c, c->bitem, size_t(2 * (nbox + 1)) * sizeof(int64_t));
+    size_t words = size_t(2 * (nbox + 1));
+    for (int k = 0; k < kGrids; ++k) {
+        P.grids.at[k] = words;
+        words += P.grids.first[k].size();
+    }
+    ENSURE(c, c->bitem, words * sizeof(int64_t));
+    for (int k = 0; k < kGrids; ++k)
+        HIPCHK(c, hipMemcpyAsync(c->bitem.as<int64_t>() + P.grids.at[k], P.grids.first[k].data(),
+                                 P.grids.first[k].size() * sizeof(int64_t), hipMemcpyHostToDevice, c->stream));
     auto upload = [&](const auto& v, size_t at) {
         return hipMemcpyAsync(c->bgeom.as<char>() + at, v.data(), v.size() * sizeof(v[0]), hipMemcpyHostToDevice, c->stream);
     };
@@ -1165,13 +1200,13 @@ void batch_dm_side(dmb_ctx* c, const BatchPlan& P, const DmPassArgs* ddev, const
     const char* const base = c->bgeom.as<const char>();
     {
         Phase ph(c, DMB_PH_COMBINE_DM);
-        by_rows(P.nbox, [&](int b, unsigned rows) {
-            hipLaunchKernelGGL(k_combine_dm<true>, dim3(blocks_for(P.most_dm, kTile), rows), dim3(64 * kCombineWaves), 0,
-                               c->stream, P.dc[0], reinterpret_cast<const DmCombineArgs*>(base + P.at_dc) + b);
+        by_blocks(P.grids, c->bitem.as<const int64_t>(), kGridCombineDm, [&](dim3 grid, BoxBlocks g) {
+            hipLaunchKernelGGL(k_combine_dm<true>, grid, dim3(64 * kCombineWaves), 0, c->stream, P.dc[0],
+                               reinterpret_cast<const DmCombineArgs*>(base + P.at_dc), g);
         });
     }
     launch_resolve<Real, N, RB, true>(c, P.ra[0], reinterpret_cast<const ResolveArgs*>(base + P.at_ra), P.nbox,
-                                      P.most_dm * P.nbox, P.wide);
+                                      P.all_dm, P.wide);
 }
 
 template <typename Real, int N, int RM>
@@ -1186,16 +1221,17 @@ dmb_status batch_enqueue(dmb_ctx* c, const dmb_particles* gas, const dmb_particl
     const DmPassArgs* ddev = reinterpret_cast<const DmPassArgs*>(base + P.at_da);
     const int64_t* gitems = c->bitem.as<const int64_t>();
     const int64_t* ditems = gitems + nbox + 1;
-    const unsigned blocks = blocks_for(std::max<int64_t>(P.most_n, kQueueWords), 256);
-    by_rows(nbox, [&](int b, unsigned rows) {
-        hipLaunchKernelGGL(k_gather_gas<Real>, dim3(blocks, rows), dim3(256), 0, c->stream, P.gg[0],
-                           reinterpret_cast<const GasGatherArgs*>(base + P.at_gg) + b);
-        hipLaunchKernelGGL(k_gather_dm<Real>, dim3(blocks, rows), dim3(256), 0, c->stream, P.dg[0],
-                           reinterpret_cast<const DmGatherArgs*>(base + P.at_dg) + b);
+    by_blocks(P.grids, gitems, kGridGas, [&](dim3 grid, BoxBlocks g) {
+        hipLaunchKernelGGL(k_gather_gas<Real>, grid, dim3(256), 0, c->stream, P.gg[0],
+                           reinterpret_cast<const GasGatherArgs*>(base + P.at_gg), g);
     });
-    by_rows(nbox + 1, [&](int b, unsigned rows) {
-        hipLaunchKernelGGL(k_fill_out, dim3(blocks, rows), dim3(256), 0, c->stream, P.fa[0],
-                           reinterpret_cast<const FillArgs*>(base + P.at_fa) + b);
+    by_blocks(P.grids, gitems, kGridDm, [&](dim3 grid, BoxBlocks g) {
+        hipLaunchKernelGGL(k_gather_dm<Real>, grid, dim3(256), 0, c->stream, P.dg[0],
+                           reinterpret_cast<const DmGatherArgs*>(base + P.at_dg), g);
+    });
+    by_blocks(P.grids, gitems, kGridFill, [&](dim3 grid, BoxBlocks g) {
+        hipLaunchKernelGGL(k_fill_out, grid, dim3(256), 0, c->stream, P.fa[0],
+                           reinterpret_cast<const FillArgs*>(base + P.at_fa), g);
     });
     // as in the single-box step, the DM side (enqueued first) and the gas side run on two
     // streams, forked after the gathers and joined at the end (also inside a captured graph)
@@ -1225,10 +1261,9 @@ dmb_status batch_enqueue(dmb_ctx* c, const dmb_particles* gas, const dmb_particl
                                a0, gdev, gitems, nbox);
         }
         Phase ph(c, DMB_PH_COMBINE_GAS);
-        by_rows(nbox, [&](int b, unsigned rows) {
-            hipLaunchKernelGGL((k_combine_gas<N, RM, true>), dim3(blocks_for(P.most_gas, kTile), rows),
-                               dim3(64 * kCombineWaves), 0, c->stream, P.gc[0],
-                               reinterpret_cast<const GasCombineArgs*>(base + P.at_gc) + b);
+        by_blocks(P.grids, gitems, kGridCombineGas, [&](dim3 grid, BoxBlocks g) {
+            hipLaunchKernelGGL((k_combine_gas<N, RM, true>), grid, dim3(64 * kCombineWaves), 0, c->stream, P.gc[0],
+                               reinterpret_cast<const GasCombineArgs*>(base + P.at_gc), g);
         });
     }
     if (side) {

@@ -866,9 +866,35 @@ __global__ __launch_bounds__(256) void k_item_write(const uint64_t* __restrict__
     it_id[it] = uint32_t(it);
 }
 
+// Box of global work item `it` in a batched pass: box_items[b] is the first
+// item of box b (box_items[nbox] = total).
+__device__ __forceinline__ int box_of_item(const int64_t* __restrict__ box_items, int nbox, int64_t it)
+{
+    int lo = 0, hi = nbox - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (box_items[mid] <= it) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// A launch over the boxes of a batch: box b has blocks first[b] ... first[b + 1] - 1, as many as
+// its own size takes (with the largest box's blocks for each, one box among hundreds of small
+// ones launches mostly empty blocks); base: first block of this launch.
+struct BoxBlocks { const int64_t* first; int nbox; int64_t base; };
+
+// The block's box and its index among the box's blocks.
+__device__ __forceinline__ int64_t box_block(const BoxBlocks& g, int* b)
+{
+    const int64_t k = g.base + int64_t(blockIdx.x);
+    *b = box_of_item(g.first, g.nbox, k);
+    return k - g.first[*b];
+}
+
 // ---------------------------------------------------------------------------
 // Per-step gathers into sorted order.  These kernels and the combines below take one
-// box (boxes null) or, in a batch, row blockIdx.y of the boxes' arguments.
+// box (boxes null) or, in a batch, all boxes (BoxBlocks).
 // Per-pair data of the other species of a pass, one 16-byte-aligned record
 // per sorted particle, so that a pair's reads are a few wide loads from one
 // base pointer.
@@ -918,10 +944,12 @@ __device__ __forceinline__ void gas_derived(double u, double mu, double m_chi, d
 }
 
 template <typename Real>
-__global__ __launch_bounds__(256) void k_gather_gas(GasGatherArgs a0, const GasGatherArgs* __restrict__ boxes)
+__global__ __launch_bounds__(256) void k_gather_gas(GasGatherArgs a0, const GasGatherArgs* __restrict__ boxes, BoxBlocks grid)
 {
-    const GasGatherArgs a = boxes ? boxes[blockIdx.y] : a0;
-    int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    int b = 0;
+    const int64_t blk = boxes ? box_block(grid, &b) : int64_t(blockIdx.x);
+    const GasGatherArgs a = boxes ? boxes[b] : a0;
+    int64_t k = blk * blockDim.x + threadIdx.x;
     if (k >= a.n) return;
     uint32_t o = a.perm[k];
     a.Vx[k] = a.vel[3 * int64_t(o)];
@@ -956,10 +984,12 @@ struct DmGatherArgs {
 };
 
 template <typename Real>
-__global__ __launch_bounds__(256) void k_gather_dm(DmGatherArgs a0, const DmGatherArgs* __restrict__ boxes)
+__global__ __launch_bounds__(256) void k_gather_dm(DmGatherArgs a0, const DmGatherArgs* __restrict__ boxes, BoxBlocks grid)
 {
-    const DmGatherArgs a = boxes ? boxes[blockIdx.y] : a0;
-    int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    int b = 0;
+    const int64_t blk = boxes ? box_block(grid, &b) : int64_t(blockIdx.x);
+    const DmGatherArgs a = boxes ? boxes[b] : a0;
+    int64_t k = blk * blockDim.x + threadIdx.x;
     if (k >= a.n) return;
     uint32_t o = a.perm[k];
     DmRec<Real> r;
@@ -978,10 +1008,12 @@ struct FillArgs {
     uint32_t* queues; int nqueues;
 };
 
-__global__ __launch_bounds__(256) void k_fill_out(FillArgs a0, const FillArgs* __restrict__ boxes)
+__global__ __launch_bounds__(256) void k_fill_out(FillArgs a0, const FillArgs* __restrict__ boxes, BoxBlocks grid)
 {
-    const FillArgs a = boxes ? boxes[blockIdx.y] : a0;
-    int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    int b = 0;
+    const int64_t blk = boxes ? box_block(grid, &b) : int64_t(blockIdx.x);
+    const FillArgs a = boxes ? boxes[b] : a0;
+    int64_t i = blk * blockDim.x + threadIdx.x;
     if (i < a.n_gas) {
         a.dp[3 * i] = 0.0; a.dp[3 * i + 1] = 0.0; a.dp[3 * i + 2] = 0.0;
         a.de[i] = 0.0;
@@ -1581,19 +1613,6 @@ struct StageGas {
 
 // ---------------------------------------------------------------------------
 // Gas (mean-field) pass: owners = active gas, others = DM.
-// Box of global work item `it` in a batched pass: box_items[b] is the first
-// item of box b (box_items[nbox] = total).
-__device__ __forceinline__ int box_of_item(const int64_t* __restrict__ box_items, int nbox, int64_t it)
-{
-    int lo = 0, hi = nbox - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (box_items[mid] <= it) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
 struct GasPassArgs {
     PassGeom g;
     const double* Vx; const double* Vy; const double* Vz;     // gas, sorted
@@ -2318,13 +2337,14 @@ struct GasCombineArgs {
 constexpr int kCombineWaves = 8;
 
 template <int N, int RM, bool BATCH>
-__global__ __launch_bounds__(64 * kCombineWaves) void k_combine_gas(GasCombineArgs a0, const GasCombineArgs* __restrict__ boxes)
+__global__ __launch_bounds__(64 * kCombineWaves) void k_combine_gas(GasCombineArgs a0, const GasCombineArgs* __restrict__ boxes,
+                                                                    BoxBlocks grid)
 {
-    const GasCombineArgs& a = BATCH ? boxes[blockIdx.y] : a0;
-    if (int64_t(blockIdx.x) * kTile >= a.n_own) return;
+    int b = 0;
+    const int64_t t = BATCH ? box_block(grid, &b) : int64_t(blockIdx.x);
+    const GasCombineArgs& a = BATCH ? boxes[b] : a0;
     constexpr int NS = gas_sums<RM>();
     __shared__ double s_acc[kCombineWaves][64][NS];
-    const int64_t t = blockIdx.x;
     const uint32_t i0 = a.item_off[t], i1 = a.item_off[t + 1];
     if (i1 - i0 <= (RM == kRatesClosure ? 0u : 1u)) return;
     const int w = int(threadIdx.x) >> 6, l = lane_id();
@@ -2358,14 +2378,15 @@ struct DmCombineArgs {
 };
 
 template <bool BATCH>
-__global__ __launch_bounds__(64 * kCombineWaves) void k_combine_dm(DmCombineArgs a0, const DmCombineArgs* __restrict__ boxes)
+__global__ __launch_bounds__(64 * kCombineWaves) void k_combine_dm(DmCombineArgs a0, const DmCombineArgs* __restrict__ boxes,
+                                                                   BoxBlocks grid)
 {
-    const DmCombineArgs& a = BATCH ? boxes[blockIdx.y] : a0;
-    if (int64_t(blockIdx.x) * kTile >= a.n_own) return;
+    int b = 0;
+    const int64_t t = BATCH ? box_block(grid, &b) : int64_t(blockIdx.x);
+    const DmCombineArgs& a = BATCH ? boxes[b] : a0;
     __shared__ double s_p[kCombineWaves][64];
     __shared__ float s_m[kCombineWaves][64];
     __shared__ uint32_t s_nb[kCombineWaves][64];
-    const int64_t t = blockIdx.x;
     const uint32_t i0 = a.item_off[t], i1 = a.item_off[t + 1];
     if (i1 - i0 <= 1u) return;
     const int w = int(threadIdx.x) >> 6, l = lane_id();
