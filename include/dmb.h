@@ -226,7 +226,7 @@ dmb_status dmb_run(dmb_ctx *ctx, const dmb_particles *gas, const dmb_particles *
 /* For callers that cannot allocate device memory (code under stream capture,
  * tight serving loops, harnesses that forbid allocation): dmb_build_cells
  * followed by dmb_interact_step in one call, with every scratch buffer of
- * both carved from a static device array of DMB_STATIC_SCRATCH_MIB MiB
+ * both carved from a static device array of DMB_STATIC_SCRATCH_MIB MiB (and 4 more)
  * instead of device allocations.  Each GPU the library runs on holds its own
  * copy of the array until the process ends (looked up by dmb_create).
  * The caller passes inputs and outputs as for dmb_interact_step, and the
@@ -239,7 +239,8 @@ dmb_status dmb_run(dmb_ctx *ctx, const dmb_particles *gas, const dmb_particles *
  * Errors: those of dmb_build_cells / dmb_interact_step; DMB_ERANGE for sizes
  * above the limit; DMB_EINVAL for other rate modes or with phase timing on;
  * DMB_ENOMEM when the inputs need more scratch than the array holds (very
- * dense neighbour structures). */
+ * dense neighbour structures).  A structure that fits only with coarser work
+ * items gets those; its binary64 sums then differ in their order. */
 #define DMB_STATIC_SCRATCH_MIB 256
 #define DMB_STATIC_MAX_N 262144
 dmb_status dmb_step_static(dmb_ctx *ctx, const dmb_particles *gas, const dmb_particles *dm,

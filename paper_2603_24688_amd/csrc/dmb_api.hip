@@ -117,6 +117,7 @@ struct dmb_ctx {
     char* static_ptr = nullptr;
     char* arena = nullptr;
     size_t arena_cap = 0, arena_off = 0;
+    bool coarse_items = false;             // work items without the finer cuts (ItemCut) in the build under way
     Cells static_cells;
     uint64_t* rb_host = nullptr;           // pinned
     bool pass_overlap = true;              // the two pair passes on two streams (dmb_set_pass_overlap)
@@ -489,6 +490,32 @@ dmb_status cand_count(dmb_ctx* c, Species& A, Species& B, Pairs& P)
     return DMB_OK;
 }
 
+// The cut of a pass's candidate lists; coarse: as it is where `most` is passed.
+ItemCut cut_of(const dmb_ctx* c, const Pairs& P, bool coarse)
+{
+    const uint32_t target = uint32_t(int64_t(c->item_target_per_cu) * c->num_cu / std::max(1, c->item_share));
+    const bool gas_pass = &P == &c->X->gp;
+    const uint32_t split = uint32_t(gas_pass ? 2 * c->split : c->split), fine = 4u * target;
+    if (coarse) return ItemCut{split, 4u, target, 0u, ~0u, target};
+    return gas_pass ? ItemCut{split, 1u, fine, 0u, 16u * fine, target} : ItemCut{split, 4u, target, fine, ~0u, target};
+}
+
+// Work-item counts (needs the scanned sub-tile counts).
+dmb_status cand_items(dmb_ctx* c, Species& A, Species& B, Pairs& P)
+{
+    const int64_t nt = A.nown_tile;
+    if (nt == 0 || B.ntile == 0 || P.npairs == 0) return DMB_OK;
+    ENSURE(c, P.slices, 4);
+    hipLaunchKernelGGL(k_tile_items, dim3(blocks_for(nt + 1, 256)), dim3(256), 0, c->stream, nt,
+                       P.off.as<const uint64_t>(), P.soff.as<const uint64_t>(), P.woff.as<const uint64_t>(),
+                       P.scnt.as<uint32_t>(), P.beg.as<uint64_t>(), P.swt.as<uint32_t>(),
+                       cut_of(c, P, c->coarse_items), P.icnt.as<uint32_t>(), P.slices.as<uint32_t>(), P.maxcnt.as<uint32_t>() + 1);
+    dmb_status s = scan_excl(c, P.icnt.as<const uint32_t>(), P.ioff.as<uint32_t>(), nt + 1);
+    if (s != DMB_OK) return s;
+    HIPCHK(c, hipGetLastError());
+    return DMB_OK;
+}
+
 // Pair list, sub-tile masks and counts, work-item counts (needs P.npairs).
 dmb_status cand_subs(dmb_ctx* c, Species& A, Species& B, Pairs& P)
 {
@@ -519,21 +546,7 @@ dmb_status cand_subs(dmb_ctx* c, Species& A, Species& B, Pairs& P)
     dmb_status s = scan_excl<uint32_t, uint64_t>(c, P.pcnt.as<const uint32_t>(), P.soff.as<uint64_t>(), np + 1, np,
                                                  P.pw.as<const uint32_t>(), P.woff.as<uint64_t>());
     if (s != DMB_OK) return s;
-    const uint32_t target = uint32_t(int64_t(c->item_target_per_cu) * c->num_cu / std::max(1, c->item_share));
-    const bool gas_pass = &P == &c->X->gp;
-    const uint32_t split = uint32_t(gas_pass ? 2 * c->split : c->split);
-    const uint32_t fine = 4u * target;
-    const ItemCut cut = gas_pass ? ItemCut{split, 1u, fine, 0u, 16u * fine, target}
-                                 : ItemCut{split, 4u, target, fine, ~0u, target};
-    ENSURE(c, P.slices, 4);
-    hipLaunchKernelGGL(k_tile_items, dim3(blocks_for(nt + 1, 256)), dim3(256), 0, c->stream, nt,
-                       P.off.as<const uint64_t>(), P.soff.as<const uint64_t>(), P.woff.as<const uint64_t>(),
-                       P.scnt.as<uint32_t>(), P.beg.as<uint64_t>(), P.swt.as<uint32_t>(),
-                       cut, P.icnt.as<uint32_t>(), P.slices.as<uint32_t>(), P.maxcnt.as<uint32_t>() + 1);
-    s = scan_excl(c, P.icnt.as<const uint32_t>(), P.ioff.as<uint32_t>(), nt + 1);
-    if (s != DMB_OK) return s;
-    HIPCHK(c, hipGetLastError());
-    return DMB_OK;
+    return cand_items(c, A, B, P);
 }
 
 // Candidate sub-tile lists and work items (needs P.total, P.nitems).
@@ -1496,7 +1509,10 @@ dmb_status build_cells_impl(dmb_ctx* c, const dmb_particles* gas, const dmb_part
 // library is loaded on, held until the process ends.  Host code never uses
 // the array's name as an address: dmb_create looks up each device's copy once
 // (with that device current) and every later use goes through that pointer.
-constexpr size_t kStaticScratchBytes = size_t(DMB_STATIC_SCRATCH_MIB) << 20;
+// Besides DMB_STATIC_SCRATCH_MIB the array has 4 MiB for what a step needs at the most over
+// its particles, candidates and partial sums: the wide list of the partner search (1.1 MB),
+// the items' slices (4 bytes an item of 876 or more) and the scans' second sums.
+constexpr size_t kStaticScratchBytes = size_t(DMB_STATIC_SCRATCH_MIB + 4) << 20;
 constexpr int64_t kStaticMaxN = DMB_STATIC_MAX_N;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
@@ -1816,7 +1832,7 @@ dmb_status build_cells_impl(dmb_ctx* c, const dmb_particles* gas, const dmb_part
     if (s != DMB_OK) return s;
     uint64_t tot[2] = {0, 0};
     uint32_t nit[2] = {0, 0};
-    {
+    auto counts = [&]() -> dmb_status {
         Readback r;
         for (int k = 0; k < 2; ++k) {
             Species& A = k == 0 ? c->X->gas : c->X->dm;
@@ -1826,11 +1842,32 @@ dmb_status build_cells_impl(dmb_ctx* c, const dmb_particles* gas, const dmb_part
         }
         r.u32(X.dm.nown_tile > 0 && X.dp.npairs > 0 ? X.dp.maxcnt.as<uint32_t>() + 1 : nullptr);
         uint64_t v[5];
-        if ((s = readback(c, r, v)) != DMB_OK) return s;
+        const dmb_status st = readback(c, r, v);
+        if (st != DMB_OK) return st;
         X.resolve_wide = v[4] != 0;
         for (int k = 0; k < 2; ++k) {
             tot[k] = v[2 * k];
             nit[k] = uint32_t(v[2 * k + 1]);
+        }
+        return DMB_OK;
+    };
+    if ((s = counts()) != DMB_OK) return s;
+    // finer items only where their partial sums are small: a pass with few candidates beside one
+    // with millions would otherwise take from dmb_step_static what that one needs
+    constexpr uint64_t kFineBytes = uint64_t(112) << 20;
+    if (!c->coarse_items && uint64_t(nit[0]) * kTile * 32 + uint64_t(nit[1]) * kTile * 13 > kFineBytes) {
+        bool finer = false;
+        for (int k = 0; k < 2; ++k) {
+            const Pairs& P = k == 0 ? X.gp : X.dp;
+            uint32_t piece[2], slices[2];
+            for (int q = 0; q < 2; ++q) item_cut(cut_of(c, P, q == 1), tot[k], &piece[q], &slices[q]);
+            finer = finer || piece[0] != piece[1] || slices[0] != slices[1];
+        }
+        if (finer) {
+            c->coarse_items = true;
+            s = both(c, [&] { return cand_items(c, X.gas, X.dm, X.gp); }, [&] { return cand_items(c, X.dm, X.gas, X.dp); });
+            c->coarse_items = false;
+            if (s != DMB_OK || (s = counts()) != DMB_OK) return s;
         }
     }
     c->X->gp.total = int64_t(tot[0]); c->X->gp.nitems = nit[0];
@@ -2062,27 +2099,33 @@ dmb_status dmb_step_static(dmb_ctx* c, const dmb_particles* gas, const dmb_parti
     if (c->prof) return fail(c, DMB_EINVAL, "step_static: phase timing is on (it creates events)");
     if (!c->static_ptr || !c->rb_host) return fail(c, DMB_EHIP, "step_static: no static scratch on this device");
     HIPCHK(c, hipSetDevice(c->device));
-    // the static cell structure and scratch set, carved afresh from the static array
-    Scratch fresh, fresh2;
-    c->static_cells = Cells{};
-    c->S = &fresh;
-    c->S2 = &fresh2;
-    c->X = &c->static_cells;
-    c->arena = c->static_ptr;
-    c->arena_cap = kStaticScratchBytes;
-    c->arena_off = 0;
-    s = build_cells_impl(c, gas, dm, par);
-    if (s == DMB_OK) s = check_step(c, gas, dm, par, out);
-    if (s == DMB_OK) {
-        uint64_t* counters = out->counters;
-        if (!counters && (s = ensure(c, c->S->counters_local, DMB_NCOUNTERS * 8)) == DMB_OK)
-            counters = c->S->counters_local.as<uint64_t>();
+    // the static cell structure and scratch set, carved afresh from the static array; where the
+    // partial sums of the finer work items do not fit, once more with the coarse ones
+    for (int attempt = 0; attempt < 2; ++attempt) {
+        Scratch fresh, fresh2;
+        c->static_cells = Cells{};
+        c->S = &fresh;
+        c->S2 = &fresh2;
+        c->X = &c->static_cells;
+        c->arena = c->static_ptr;
+        c->arena_cap = kStaticScratchBytes;
+        c->arena_off = 0;
+        c->coarse_items = attempt == 1;
+        s = build_cells_impl(c, gas, dm, par);
+        if (s == DMB_OK) s = check_step(c, gas, dm, par, out);
         if (s == DMB_OK) {
-            if (par->precision == DMB_FP64) s = dispatch_rates<double>(c, gas, dm, par, out, counters);
-            else if (par->precision == DMB_FP32) s = dispatch_rates<float>(c, gas, dm, par, out, counters);
-            else s = fail(c, DMB_EINVAL, "precision %d not supported", par->precision);
+            uint64_t* counters = out->counters;
+            if (!counters && (s = ensure(c, c->S->counters_local, DMB_NCOUNTERS * 8)) == DMB_OK)
+                counters = c->S->counters_local.as<uint64_t>();
+            if (s == DMB_OK) {
+                if (par->precision == DMB_FP64) s = dispatch_rates<double>(c, gas, dm, par, out, counters);
+                else if (par->precision == DMB_FP32) s = dispatch_rates<float>(c, gas, dm, par, out, counters);
+                else s = fail(c, DMB_EINVAL, "precision %d not supported", par->precision);
+            }
         }
+        if (s != DMB_ENOMEM) break;
     }
+    c->coarse_items = false;
     c->arena = nullptr;
     c->arena_cap = c->arena_off = 0;
     c->S = &c->heap;

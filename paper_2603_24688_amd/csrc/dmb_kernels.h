@@ -795,6 +795,21 @@ __global__ __launch_bounds__(256) void k_expand(int64_t npairs, const uint32_t* 
 struct ItemCut { uint32_t split, min_split, target, items, most, coarse; };
 constexpr uint32_t kMaxSlices = 4;
 
+// Sub-tiles of a piece (at most) and slices of a piece, for `total` candidate sub-tiles.
+__host__ __device__ inline void item_cut(const ItemCut& cut, uint64_t total, uint32_t* piece, uint32_t* slices)
+{
+    const bool fine = total <= cut.most;
+    const uint64_t target = fine ? cut.target : cut.coarse, least = fine ? cut.min_split : 4u, one = total ? total : 1u;
+    uint64_t s = cut.split;
+    if (target > 0 && s > least) {
+        const uint64_t want = (total + target - 1) / target;
+        s = want < least ? least : (want < s ? want : s);
+    }
+    const uint64_t ns = uint64_t(cut.items) * s / one;
+    *piece = uint32_t(s);
+    *slices = uint32_t(ns < 1 ? 1 : (ns > kMaxSlices ? kMaxSlices : ns));
+}
+
 // What a block of the partner search holds of one scattering DM in LDS (k_resolve).
 constexpr int kResolveList = 2048;    // candidate sub-tiles kept after the point test
 constexpr int kResolvePairs = 8192;   // pairs cached (the registers allow one block per CU anyway)
@@ -813,13 +828,8 @@ __global__ __launch_bounds__(256) void k_tile_items(int64_t nt, const uint64_t* 
 {
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (t > nt) return;
-    const uint64_t total = soff[poff[nt]];
-    const bool fine = total <= cut.most;
-    const uint32_t target = fine ? cut.target : cut.coarse, least = fine ? cut.min_split : 4u;
-    uint32_t s = cut.split;
-    if (target > 0 && s > least)
-        s = uint32_t(max<uint64_t>(least, min<uint64_t>(s, (total + target - 1) / target)));
-    const uint32_t ns = uint32_t(max<uint64_t>(1, min<uint64_t>(kMaxSlices, uint64_t(cut.items) * s / max<uint64_t>(total, 1))));
+    uint32_t s, ns;
+    item_cut(cut, soff[poff[nt]], &s, &ns);
     if (t == nt) { scnt[t] = 0u; icnt[t] = 0u; *slices = ns; return; }
     const uint64_t b = soff[poff[t]], e = soff[poff[t + 1]];
     sbeg[t] = b;
