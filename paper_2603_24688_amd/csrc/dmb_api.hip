@@ -77,7 +77,8 @@ struct Scratch {
 struct Cells {
     Species gas, dm;
     Pairs gp, dp;                          // gas owners x DM tiles; DM owners x gas tiles
-    DevBuf part_gas, part_p, part_pm, part_nb, psum_own;
+    DevBuf part_gas, psum_own;
+    DevBuf part_dm;                        // DM partial sums: P, then max P, then the near-boundary flag of every row
     DevBuf qctr, slist, rwide;
     bool resolve_wide = false;             // some DM may outgrow a block of the partner search (k_resolve_wide)
     int64_t built_ngas = -1, built_ndm = -1;
@@ -797,9 +798,7 @@ dmb_status gather_and_fill(dmb_ctx* c, Cells& X, const dmb_particles* gas, const
     ENSURE(c, X.qctr, kQueueWords * 4);
     if (X.gp.nitems > 0) ENSURE(c, X.part_gas, size_t(X.gp.nitems) * kTile * gas_sums<RM>() * 8);
     if (X.dp.nitems > 0) {
-        ENSURE(c, X.part_p, size_t(X.dp.nitems) * kTile * 8);
-        ENSURE(c, X.part_pm, size_t(X.dp.nitems) * kTile * 4);
-        ENSURE(c, X.part_nb, size_t(X.dp.nitems) * kTile);
+        ENSURE(c, X.part_dm, size_t(X.dp.nitems) * kTile * 13);
         ENSURE(c, X.psum_own, size_t(D.n_own) * 8);
         ENSURE(c, X.slist, size_t(D.n_own) * 4);
         if (X.resolve_wide) ENSURE(c, X.rwide, kResolveWide * sizeof(ResolveWide));
@@ -905,7 +904,10 @@ DmPassArgs dm_pass_args(dmb_ctx* c, Cells& X, const dmb_params* par, dmb_out* ou
     a.gtab = c->gtab.as<const float4>();
     a.k0 = uint32_t(par->seed); a.k1 = uint32_t(par->seed >> 32); a.step = par->step; a.box = par->box_id;
     a.step_off = step_off;
-    a.part_p = X.part_p.as<double>(); a.part_pm = X.part_pm.as<float>(); a.part_nb = X.part_nb.as<uint8_t>();
+    const size_t rows = size_t(X.dp.nitems) * kTile;
+    a.part_p = X.part_dm.as<double>();
+    a.part_pm = reinterpret_cast<float*>(a.part_p + rows);
+    a.part_nb = reinterpret_cast<uint8_t*>(a.part_pm + rows);
     a.psum_own = X.psum_own.as<double>(); a.psum = out->p_sum; a.pmax = out->p_max;
     a.scount = X.qctr.as<uint32_t>() + 2 * kXcd * kQueueStride; a.slist = X.slist.as<uint32_t>();
     return a;
@@ -916,8 +918,7 @@ DmCombineArgs dm_combine_args(Cells& X, const DmPassArgs& a, dmb_out* out, uint6
     Species& D = X.dm;
     DmCombineArgs cb;
     cb.n_own = D.n_own; cb.own = D.own.as<const uint32_t>(); cb.perm = D.perm;
-    cb.item_off = X.dp.ioff.as<const uint32_t>(); cb.part_p = X.part_p.as<const double>();
-    cb.part_pm = X.part_pm.as<const float>(); cb.part_nb = X.part_nb.as<const uint8_t>();
+    cb.item_off = X.dp.ioff.as<const uint32_t>(); cb.part_p = a.part_p; cb.part_pm = a.part_pm; cb.part_nb = a.part_nb;
     cb.k0 = a.k0; cb.k1 = a.k1; cb.step = a.step; cb.box = a.box; cb.step_off = a.step_off;
     cb.psum_own = X.psum_own.as<double>(); cb.psum = out->p_sum; cb.pmax = out->p_max;
     cb.scount = a.scount; cb.slist = X.slist.as<uint32_t>(); cb.counters = counters;
@@ -1114,9 +1115,7 @@ dmb_status batch_prepare(dmb_ctx* c, int nbox, const dmb_particles* gas, const d
         // buffers the step writes (sized here so that enqueueing allocates nothing)
         if (X.gp.nitems > 0) ENSURE(c, X.part_gas, size_t(X.gp.nitems) * kTile * gas_sums<RM>() * 8);
         if (X.dp.nitems > 0) {
-            ENSURE(c, X.part_p, size_t(X.dp.nitems) * kTile * 8);
-            ENSURE(c, X.part_pm, size_t(X.dp.nitems) * kTile * 4);
-            ENSURE(c, X.part_nb, size_t(X.dp.nitems) * kTile);
+            ENSURE(c, X.part_dm, size_t(X.dp.nitems) * kTile * 13);
             ENSURE(c, X.psum_own, size_t(X.dm.n_own) * 8);
             ENSURE(c, X.slist, size_t(X.dm.n_own) * 4);
             if (X.resolve_wide) ENSURE(c, X.rwide, kResolveWide * sizeof(ResolveWide));
@@ -1493,7 +1492,7 @@ void free_cells(Cells& X)
                          &P->it_ord, &P->it_slice, &P->slices, &P->gbox, &P->gh, &P->gsup, &P->gq, &P->gcnt, &P->glist, &P->gmax};
         for (DevBuf* b : all) fr(*b);
     }
-    DevBuf* rest[] = {&X.part_gas, &X.part_p, &X.part_pm, &X.part_nb, &X.psum_own, &X.qctr, &X.slist,
+    DevBuf* rest[] = {&X.part_gas, &X.part_dm, &X.psum_own, &X.qctr, &X.slist,
                       &X.rwide};
     for (DevBuf* b : rest) fr(*b);
 }
