@@ -204,7 +204,7 @@ __device__ __forceinline__ double overlap_g_table(const float4* __restrict__ tab
 // them in binary32 (rounding below 4e-7 of g).  Overlaps under the binary32
 // range (pairs within ~1e-5 h_s of contact) flush to zero, as the binary32
 // P_ij built from them would.  The gas pass (binary64 terms) takes the
-// binary64 lookup for such pairs (overlap_g_gas), so an owner whose every
+// binary64 lookup for such pairs (GasEval::finish), so an owner whose every
 // neighbour is that close to contact keeps its relative accuracy.
 // In two halves, so that a pass can put other work between them: begin() finds
 // the cell and issues its loads, value() takes them.

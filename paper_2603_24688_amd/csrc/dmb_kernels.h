@@ -131,12 +131,6 @@ __device__ __forceinline__ int wave_incl_scan(int v)
     return int(u);
 }
 
-// Value of lane j (wave-uniform j), read into a scalar register.
-__device__ __forceinline__ float lane_get(float v, int j)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), j));
-}
-
 // Inclusive prefix maximum over the wave's lanes of values >= 0 (0 acts as
 // "nothing yet"), in registers.
 __device__ __forceinline__ uint32_t wave_incl_umax(uint32_t u)
@@ -1359,9 +1353,9 @@ __device__ __forceinline__ void test_chunk(PairTest& T, TestLds& S, const PassGe
 
 // Test the next group of slots against the tile's owners.  Returns the group's
 // hit count (wave-uniform), -1 when the item's candidates are exhausted.
-// stage(s, q, write) is called twice per lane that holds a slot s (particle q):
-// first to load what the pass needs of the particle, then, after the test has
-// hidden the loads, to put it into the slot's row in LDS.
+// A lane that holds a slot s (particle q) calls stage.load(q) for what the pass
+// needs of the particle and, after the test has hidden the loads, stage.store(s) to
+// put it into the slot's row in LDS.
 template <int W, typename Stage>
 __device__ __forceinline__ int test_next(PairTest& T, TestLds& S, const PassGeom& G, const double* A,
                                          const double cen[3], const float Lf[3], Stage& stage)
@@ -1577,7 +1571,7 @@ __device__ __forceinline__ void walk_group(TestLds& S, int lane, int H, Acc& acc
 // DM pass (galaxy of 1M + 4M).  The rows take the binary32 passes from 10 to
 // 13 KB per wave, so three waves share a SIMD instead of four; the L1 is then busy
 // 63 %, the vector units 72 %, and the passes take 2.46 and 2.14 ms instead of 2.50
-// and 2.17 (2.68 for the DM pass with four waves and records read per pair). 
+// and 2.17 (2.68 for the DM pass with four waves and records read per pair).
 template <typename Real>
 struct SlotDm {                   // DM, in the gas pass
     double vx[64], vy[64], vz[64];
@@ -3305,8 +3299,8 @@ __global__ __launch_bounds__(64) void k_run_diag_final(RunDiagArgs a)
 // the differences below amplify the rounding of H, so the coefficients, and with
 // them every binary32 result, are those of this rule's rounding.  With
 // overlap_integral, which is exact to rounding too, 101 387 of the 524 288
-// coefficients moved, by up to 2.4e-8, and with them a rare pair (8 of 2e8 in a galaxy of 1M + 4M,
-// a unit or two in the last place of g).
+// coefficients moved, by up to 2.4e-8, and with them a rare pair's g by a unit or two
+// in the last place (8 of 2e8 pairs in a galaxy of 1M + 4M).
 
 // psi(Q) = int_0^Q q w(q) dq differences on one polynomial branch, factored so
 // that a small b - a keeps relative accuracy (Appendix D inner integral).
